@@ -86,12 +86,14 @@ def _parse():
 # ---------------------------------------------------------------------------
 # Cost model (algorithmic work per useful cell-direction)
 # ---------------------------------------------------------------------------
-def algorithmic(H: int, C: int, s: int, useful_cells: int):
+def algorithmic(H: int, C: int, s: int, useful_cells: int, fused_projection: bool):
     """Bytes and flops per launch of each phase, counted over useful cells only
     (4 directions each): what the computation must move and do, whatever the
-    kernels' layout. Gradient phases: fused (one kernel reading dZ once) or split."""
+    kernels' layout. Gradient phases: fused (one kernel reading dZ once) or split.
+    With the projection inside the forward wavefront, that kernel reads x and
+    writes the gates, and the phase before it lays x out (fp32 only)."""
     cd = 4 * useful_cells
-    return {
+    alg = {
         "projection": (cd * (C * s / 4 + 5 * H * s), cd * 10.0 * C * H),
         "zero_invalid": (0.0, 0.0),
         "wavefront_fwd": (cd * (5 * H * s + H * s + 4 * H), cd * 20.0 * H * H),
@@ -100,17 +102,30 @@ def algorithmic(H: int, C: int, s: int, useful_cells: int):
         "input_grad": (cd * (5 * H * s + C * s / 4), cd * 10.0 * C * H),
         "weight_grad": (cd * (5 * H * s + C * s / 4 + H * s), cd * (20.0 * H * H + 10.0 * C * H)),
     }
+    if fused_projection:
+        alg["projection"] = (useful_cells * C * s if s == 4 else 0.0, 0.0)
+        alg["wavefront_fwd"] = (cd * (C * s / 4 + 5 * H * s + H * s + 4 * H), cd * (20.0 * H * H + 10.0 * C * H))
+    return alg
 
 
-def design_bytes(H: int, C: int, s: int, useful_cells: int, canvas_cells: int, unit_cells: int):
+def projection_fused(C: int, H: int, dtype: str) -> bool:
+    from paper_1902_11208_amd import api
+
+    return api.projection_fused(C, H, api.BF16 if dtype == "bf16" else api.F32)
+
+
+def design_bytes(H: int, C: int, s: int, useful_cells: int, canvas_cells: int, unit_cells: int, fused: bool):
     """HBM bytes the kernels move beyond the cost model, by design: the
     projection over separator and padding cells (an upper bound: its waves
-    skip 64-cell chunks without a rectangle cell), the activated gates the
-    forward writes back for the backward, and the zero output rows."""
+    skip 64-cell chunks without a rectangle cell) and the activated gates the
+    forward writes over its pre-activations (neither where the wavefront
+    computes the projection), and the zero output rows."""
     cd = 4 * useful_cells
     return {
-        "projection_non_useful_cells": (canvas_cells - useful_cells) * (C + 20 * H) * s,
-        "wavefront_fwd_gate_writeback": cd * 5 * H * s,
+        "projection_non_useful_cells": 0 if fused else (canvas_cells - useful_cells) * (C + 20 * H) * s,
+        # the pieces of the fp32 inputs, written once and read by every direction in their place
+        "input_pieces": useful_cells * ((C + 31) // 32 * 192 + 16) * 5 if fused and s == 4 else 0,
+        "wavefront_fwd_gate_writeback": 0 if fused else cd * 5 * H * s,
         "wavefront_fwd_unit_padding_cells": 4 * (unit_cells - useful_cells) * (11 * H * s + 4 * H),
         "zero_invalid_rows": (canvas_cells - useful_cells) * 4 * H * s,
     }
@@ -421,7 +436,7 @@ def stack_algorithmic(wl, run):
     alg = {}
     bh, bw = wl.block
     for li, (H, C) in enumerate(zip(wl.hidden, wl.mdlstm_c_in)):
-        for k, v in algorithmic(H, C, 4, run.layer_cells[li]).items():
+        for k, v in algorithmic(H, C, 4, run.layer_cells[li], projection_fused(C, H, "f32")).items():
             alg[f"L{li}.{k}"] = v
     for ci in range(len(run.st.convs)):
         H, og = wl.hidden[ci], wl.conv_out[ci] // 4
@@ -467,18 +482,22 @@ def measure_gpu(cid: int, steps: int, warmup: int, padded: bool, stepwise: bool)
         crit = max(int(h) + int(w) - 1 for h, w in zip(wl.heights // 2, wl.widths // 4))
     else:
         useful = 4 * wl.useful_cells
-        alg = algorithmic(wl.hidden, wl.c_in, 2 if dtype == "bf16" else 4, wl.useful_cells)
+        fused = projection_fused(wl.c_in, wl.hidden, dtype)
+        alg = algorithmic(wl.hidden, wl.c_in, 2 if dtype == "bf16" else 4, wl.useful_cells, fused)
         forward_only = wl.forward_only
         proj_name = "projection"
         s = 2 if dtype == "bf16" else 4
-        extra = {"design_bytes": design_bytes(wl.hidden, wl.c_in, s, wl.useful_cells, run.n_cells, run.unit_cells)}
+        extra = {"design_bytes": design_bytes(wl.hidden, wl.c_in, s, wl.useful_cells, run.n_cells, run.unit_cells,
+                                              fused)}
         crit = max(int(h) + int(w) - 1 for h, w in zip(wl.heights, wl.widths))
     print(f"[bench] workload {cid} packed: {ms:.3f} ms/step (wall {wall_ms:.3f}), dominant kernel {dom} "
           f"{phase[dom]:.3f} ms", file=sys.stderr, flush=True)
     phases_out = phase_rates(phase, alg, dtype, f"workload {cid}")
     traffic = measured_traffic(dom, cid)
     roof = roofline(dom, phase[dom], *alg[dom], dtype, traffic)
-    proj = projection_fractions(phase[proj_name], *alg[proj_name], dtype) if phase.get(proj_name) else None
+    # a projection inside the forward wavefront has no rate of its own
+    proj = (projection_fractions(phase[proj_name], *alg[proj_name], dtype)
+            if phase.get(proj_name) and alg[proj_name][1] > 0 else None)
     if proj is not None:
         proj["kernel"] = proj_name
     res = {

@@ -280,6 +280,14 @@ mdlstm_status mdlstm_backward(const mdlstm_layer_desc* desc, int32_t canvas_h, i
 int32_t mdlstm_gradients_fused(const mdlstm_layer_desc* desc);
 
 /*
+ * 1 if mdlstm_forward computes this layer's input projection inside the
+ * wavefront kernel (the phase before it then only lays the fp32 inputs out for
+ * it), 0 if in a kernel of its own, -1 for a descriptor mdlstm_forward
+ * refuses. Host-only; for profilers that attribute time to the kernels.
+ */
+int32_t mdlstm_projection_fused(const mdlstm_layer_desc* desc);
+
+/*
  * Stack glue (Section V-B, Fig. 1): a multi-layer network keeps every layer
  * on a packed canvas. Between two MDLSTM layers a block-strided convolution
  * (stride equal to its bh x bw kernel, so blocks never overlap) with tanh maps
@@ -420,7 +428,8 @@ const char* mdlstm_last_error(void);
  * events[n] (host array of hipEvent_t handles owned by the caller). While set,
  * mdlstm_forward and mdlstm_backward called on this thread record them on
  * their stream at kernel boundaries:
- *   [0] before the projection   [1] after the projection   [2] after zeroing
+ *   [0] before the projection (mdlstm_projection_fused: the input layout pass)
+ *   [1] after it   [2] after zeroing
  *   invalid output rows (the persistent forward wavefront zeroes them itself
  *   when the batch has at least a unit per CU; then [2] follows [1] directly)
  *   [3] after the forward wavefront

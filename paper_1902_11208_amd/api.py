@@ -210,6 +210,15 @@ def gradients_fused(c_in: int, hidden: int, dtype: int) -> bool:
     return bool(r)
 
 
+def projection_fused(c_in: int, hidden: int, dtype: int) -> bool:
+    """Whether the forward wavefront computes the input projection itself."""
+    d = layer_desc(c_in, hidden, dtype)
+    r = int(lib().mdlstm_projection_fused(ctypes.byref(d)))
+    if r < 0:
+        raise ValueError(f"layer c_in={c_in} hidden={hidden} dtype={dtype} is not supported")
+    return bool(r)
+
+
 class Prepared:
     """Host-side argument bundle for one canvas layout, reused across calls."""
 

@@ -8,25 +8,21 @@
 // row y: the left predecessor is row y of the previous diagonal, the top
 // predecessor row y - 1.
 //
-// The unit's hidden units are split over NW waves in quads of four. Forward,
-// per step and 16-cell tile:
-//  * each wave computes, on MFMA, the pre-activations of the four sigmoid
-//    gates (i, f_L, f_T, o) of its quads from [h_L ; h_T]; the A operand rows
-//    are ordered (quad member, gate) so that lane 16q + n ends up holding all
-//    four gates of hidden unit 4*quad + q of cell n;
-//  * the cell-candidate pre-activations are split over the waves by
-//    reduction range and summed through LDS in a fixed order;
-//  * then every lane updates c and h of its (cell, hidden unit) pairs.
-// Backward, per step: every lane does the gate-gradient update of its pairs
-// (phase A), then the waves contract da with U^T on MFMA, split by output
-// tile and reduction range, partials summed through LDS in a fixed order
-// (phase B). The U operands stay in VGPRs for the whole unit.
+// Here: the backward wavefront, the forward and backward of wide bf16 layers,
+// and the launches; the forward of the other shapes is wave_fwd.hpp.
+//
+// The unit's hidden units are split over NW waves in quads of four. Backward,
+// per step: every lane does the gate-gradient update of its pairs (phase A),
+// then the waves contract da with U^T on MFMA, split by output tile and
+// reduction range, partials summed through LDS in a fixed order (phase B).
+// The U operands stay in VGPRs for the whole unit.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "wave_fwd.hpp"
 
 namespace mdl {
 
@@ -162,20 +158,6 @@ struct TileGroups {
         (std::is_same<T, float>::value && H <= 32 && NT >= 2 && 64 * Geo<H, T>::NW * NT <= 1024) ? NT : 1;
 };
 
-// LDS bytes of the forward kernel without and with staging of its inputs
-// (two diagonals of pre-activations) and outputs (one diagonal).
-template <int H, int NT, typename T>
-constexpr size_t fwd_lds_base() {
-    using Gm = Geo<H, T>;
-    return (size_t)2 * (NT * 16 + 1) * (H + 16 / sizeof(T)) * sizeof(T) + (size_t)2 * (NT * 16 + 1) * (H + 2) * 4 +
-           (size_t)Gm::SPL * NT * 16 * (H + 2) * 4 + (size_t)NT * 16 * 8;
-}
-template <int H, int NT, typename T>
-constexpr bool fwd_stage() {
-    using Q = OutQ<H, T>;
-    return fwd_lds_base<H, NT, T>() + (size_t)NT * 16 * 16 * ((Q::QF + 1) + 2 * (Q::QZ + 1)) <= 128 * 1024;
-}
-
 // LDS bytes of the backward kernel without and with staging of its inputs
 // (two diagonals of gates, upstream gradients and cell states).
 template <int H, int NT, typename T>
@@ -205,27 +187,12 @@ struct WaveArgs {
     const int32_t* rects;  // [n_rects][4]
     const uint8_t* mask;   // [n_cells]
     const void* u;         // [4][5H][2H]
-    void* z;               // [n_cells][20H]: pre-activations in, gates out (fwd); dZ out (bwd)
+    void* z;               // [n_cells][20H]: gates in, dZ out
     float* c;              // [n_cells][4H] cell state
-    void* y;               // [n_cells][4H] output (fwd)
-    const void* dy;        // [n_cells][4H] upstream gradient (bwd)
+    const void* dy;        // [n_cells][4H] upstream gradient
     int canvas_w;
-    int s0, s1;            // forward: local diagonals [s0, s1) of every unit
     unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
     int n_units;
-    // forward: when rid is set, the output rows [yrow_words x 8 bytes] of the
-    // cells outside every rectangle or masked are zeroed before the units run
-    const int32_t* rid;    // [n_cells] rectangle id, -1 outside every rectangle
-    int64_t n_cells;
-    int yrow_words;
-};
-
-template <int NT, int WQ, typename T>
-struct FPre {
-    T z[NT][WQ][5];
-    int64_t p[NT];
-    uint32_t m[NT];
-    bool live[NT];
 };
 
 template <int NT, int WQ, typename T>
@@ -238,437 +205,6 @@ struct BPre {
 };
 
 }  // namespace
-
-// ---------------------------------------------------------------------------
-// Forward.
-// ---------------------------------------------------------------------------
-template <int H, int NT, typename T, int PFD>
-__device__ __forceinline__ void wave_fwd_unit(const WaveArgs& a, const int unit) {
-    using Gm = Geo<H, T>;
-    using O = Ops<T>;
-    using Op = typename O::Op;
-    using Q = OutQ<H, T>;
-    constexpr int NW = Gm::NW, WQ = Gm::WQ, G = Gm::G, KRUN = Gm::KRUN, NSTEP = Gm::NSTEP;
-    // tile groups: NG groups of NW waves, group tg owning tiles tg, tg + NG, ...
-    constexpr int NG = TileGroups<H, NT, T>::NG, TPG = NT / NG;
-    constexpr int SPL = Gm::SPL, GSTEP = Gm::GSTEP, NTH = 64 * NW * NG;
-    constexpr int ROWS = NT * 16 + 1;             // row 0: zero row above local row 0
-    constexpr int HP = H + 16 / (int)sizeof(T);   // padded LDS row pitch (elements)
-    // Staged: the pre-activations of the next diagonal are loaded as contiguous
-    // 16-byte chunks into registers one step ahead and pass through LDS to
-    // the lanes that use them; the outputs leave through LDS the same way.
-    // Otherwise every lane loads and stores its own values.
-    constexpr bool STAGE = fwd_stage<H, NT, T>();
-    constexpr int NC = STAGE ? NT * 16 : 1;
-    constexpr int PF = STAGE ? Q::QF + 1 : 1;     // chunk pitches; the extra chunk
-    constexpr int PZ = STAGE ? Q::QZ + 1 : 1;     // keeps rows in different LDS banks
-    // input slots, rounded up to whole workgroup passes so every lane loads
-    constexpr int NSL = STAGE ? (NT * 16 * PZ + NTH - 1) / NTH * NTH : 1;
-    constexpr int NITZ = STAGE ? NSL / NTH : 0;
-    __shared__ __attribute__((aligned(16))) T hbuf[2][ROWS][HP];
-    __shared__ __attribute__((aligned(16))) float cbuf[2][ROWS][H + 2];  // pitch H + 2: rows of a tile in different banks
-    __shared__ __attribute__((aligned(16))) float gpart[SPL][NT * 16][H + 2];
-    __shared__ __attribute__((aligned(16))) u32x4 ostage[NC][PF];
-    __shared__ __attribute__((aligned(16))) u32x4 zst[STAGE ? 2 : 1][NSL];  // by diagonal parity
-    // mask bytes by diagonal parity; a slot per thread so that every lane
-    // writes (rows below 16 NT are read)
-    __shared__ uint32_t mst[STAGE ? 2 : 1][STAGE ? NTH : 1];
-
-    const int lane = threadIdx.x & 63;
-    const int tg = NG == 1 ? 0 : (int)(threadIdx.x >> 6) / NW;     // tile group
-    const int w = NG == 1 ? (int)(threadIdx.x >> 6) : (int)(threadIdx.x >> 6) % NW;  // wave in the group
-    const int q = lane >> 4, n16 = lane & 15;
-    const int gt = w / SPL, sp = w % SPL;  // candidate tile and reduction slice of this wave
-    const int d = unit & 3;
-    const RectD R = reinterpret_cast<const RectD*>(a.rects)[unit >> 2];
-    const T* __restrict__ U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
-    T* __restrict__ Z = static_cast<T*>(a.z);
-    T* __restrict__ Y = static_cast<T*>(a.y);
-    float* __restrict__ Cs = a.c;
-    const int steps = R.h + R.w - 1;
-    // Diagonals [sb, se) of the unit: all of them in one launch, or one per
-    // launch, in which case the state of diagonal sb - 1 is read back from the
-    // outputs and cell states the previous launch wrote.
-    const int sb = a.s0, se = min(a.s1, steps);
-    if (sb >= se) return;
-
-    for (int i = threadIdx.x; i < 2 * ROWS * HP; i += blockDim.x) (&hbuf[0][0][0])[i] = T(0);
-    for (int i = threadIdx.x; i < 2 * ROWS * (H + 2); i += blockDim.x) (&cbuf[0][0][0])[i] = 0.0f;
-    if (sb > 0) {
-        lds_barrier();  // every zero written before the read-back fills the same rows
-        const int pb = (sb & 1) ^ 1;  // buffer of diagonal sb - 1
-        for (int i = threadIdx.x; i < NT * 16 * H; i += blockDim.x) {
-            const int yy = i / H, j = i - yy * H, xx = sb - 1 - yy;
-            if (yy < R.h && xx >= 0 && xx < R.w) {
-                const int64_t p = canvas_index(R, d, yy, xx, a.canvas_w);
-                hbuf[pb][yy + 1][j] = Y[p * (4 * H) + d * H + j];
-                cbuf[pb][yy + 1][j] = Cs[p * (4 * H) + d * H + j];
-            }
-        }
-    }
-
-    // A operands. Own tiles: row n16 = 4*jj + gate -> U row gate*H + 4*quad + jj.
-    // Candidate tile gt: row n16 -> U row 4H + 16*gt + n16, K steps of slice sp only.
-    Op Aown[WQ][NSTEP], Ag[GSTEP];
-#pragma unroll
-    for (int wq = 0; wq < WQ; ++wq) {
-        const int quad = w * WQ + wq;
-        const int row = (n16 & 3) * H + 4 * quad + (n16 >> 2);
-        load_slot<T, NSTEP>(U + (int64_t)row * 2 * H + q * KRUN, 1, true, Aown[wq]);
-    }
-    {
-        const int j = 16 * gt + n16;
-        const bool ok = j < H;
-        load_slot<T, GSTEP>(U + (int64_t)(4 * H + (ok ? j : 0)) * 2 * H + q * KRUN + sp * GSTEP * O::PER, 1, ok, Ag);
-    }
-    float cprev[TPG][WQ];  // c_L: the lane's cell state of the previous diagonal
-#pragma unroll
-    for (int lt = 0; lt < TPG; ++lt)
-#pragma unroll
-        for (int wq = 0; wq < WQ; ++wq) {
-            const int nt = tg + NG * lt;
-            const int yy = 16 * nt + n16, j = 4 * (w * WQ + wq) + q, xx = sb - 1 - yy;
-            cprev[lt][wq] = sb > 0 && yy < R.h && xx >= 0 && xx < R.w
-                                ? Cs[canvas_index(R, d, yy, xx, a.canvas_w) * (4 * H) + d * H + j]
-                                : 0.0f;
-        }
-    // The U operands are in registers before the step loop starts, so no wait
-    // inside the loop is attributed to them.
-    __builtin_amdgcn_s_waitcnt(0);
-
-    // Loads of step s: the lane's cells, their mask bytes and the
-    // pre-activations (staged: chunks into zr, else the lane's own values).
-    // They are issued for every lane from a valid cell of the rectangle (the
-    // row clamped into the diagonal's active range) so their number is the
-    // same on every path, which lets the compiler wait for exactly these loads
-    // one step later; `live` says whether they are used.
-    // Staged chunks and mask bytes loaded PFD steps ahead of their diagonal's
-    // staging step (set k holds diagonals sb + k, sb + k + PFD, ...).
-    static_assert(PFD == 1 || PFD == 2, "prefetch distance");
-    u32x4 zr[PFD][NITZ > 0 ? NITZ : 1];
-    uint32_t mr[PFD];
-    const DiagMap M(R, d, a.canvas_w);
-    constexpr int RBZ = 4 * G * (int)sizeof(T);  // bytes per canvas cell of Z
-    // Cell (y, s - y) of the unit is canvas index M.c0 + idx with
-    // idx = sx*s + y*ky, which fits 32 bits; the lanes keep 64-bit pointers to
-    // their chunks at idx = 0 and add idx times the tensor's row bytes.
-    const uint8_t* mrow = a.mask + M.c0;
-    // The lane's chunk of each staged-input pass: cell row and address (slot S
-    // of zst is chunk S % PZ of the row of cell S / PZ; the padding chunk and
-    // the slots past the last cell repeat a valid one).
-    int zcell[NITZ > 0 ? NITZ : 1];
-    const char* zptr[NITZ > 0 ? NITZ : 1];
-#pragma unroll
-    for (int it = 0; it < NITZ; ++it) {
-        const int S = it * NTH + (int)threadIdx.x;
-        zcell[it] = min(S / PZ, NT * 16 - 1);
-        zptr[it] = reinterpret_cast<const char*>(Z) + M.c0 * RBZ + (d * G) * (int)sizeof(T) +
-                   16 * min(S - (S / PZ) * PZ, Q::QZ - 1);
-    }
-    // Loads of step s: the lanes' mask bytes and the pre-activations (staged:
-    // chunks into zr, else the lane's own values). They are issued for every
-    // lane from a valid cell of the rectangle (the row clamped into the
-    // diagonal's active range) so their number is the same on every path,
-    // which lets the compiler wait for exactly these loads one step later;
-    // `live` says whether they are used.
-    auto fetch = [&](int s, FPre<TPG, WQ, T>& b) {
-        const int sc = min(s, steps - 1);
-        const int ylo = max(0, sc - R.w + 1), yhi = min(R.h - 1, sc);
-        const int sxs = M.sx * sc;
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            const int yy = 16 * nt + n16;
-            b.live[lt] = s < steps && yy >= ylo && yy <= yhi;
-            const int idx = sxs + min(max(yy, ylo), yhi) * M.ky;
-            b.m[lt] = mrow[idx];
-            if constexpr (!STAGE) {
-                const int64_t p = M.c0 + idx;
-                b.p[lt] = p;
-                const T* zp = Z + p * (4 * G) + d * G;
-#pragma unroll
-                for (int wq = 0; wq < WQ; ++wq) {
-                    const int j = 4 * (w * WQ + wq) + q;
-#pragma unroll
-                    for (int t = 0; t < 5; ++t) b.z[lt][wq][t] = zp[t * H + j];
-                }
-            }
-        }
-    };
-    // Staged pre-activation chunks and the mask byte of row threadIdx.x (of
-    // the last row above 16 NT, unused there) of diagonal s into register set k.
-    auto fetch_z = [&](int s, int k) {
-        const int sc = min(s, steps - 1);
-        const int ylo = max(0, sc - R.w + 1), yhi = min(R.h - 1, sc);
-        const int sxs = M.sx * sc;
-        if constexpr (STAGE) {
-#pragma unroll
-            for (int it = 0; it < NITZ; ++it) {
-                const int idx = sxs + min(max(zcell[it], ylo), yhi) * M.ky;
-                zr[k][it] = *reinterpret_cast<const u32x4*>(zptr[it] + (int64_t)idx * RBZ);
-            }
-            // every lane loads (a valid byte), which keeps the number of loads per step fixed
-            mr[k] = mrow[sxs + min(max(min((int)threadIdx.x, NT * 16 - 1), ylo), yhi) * M.ky];
-        }
-    };
-    // Register set k -> LDS buffers of diagonal s's parity.
-    auto stage_in = [&](int s, int k) {
-#pragma unroll
-        for (int it = 0; it < NITZ; ++it) zst[s & 1][it * NTH + threadIdx.x] = zr[k][it];
-        if constexpr (STAGE) mst[s & 1][threadIdx.x] = mr[k];
-    };
-
-    // Write back the outputs staged by diagonal sp. Every lane stores in every
-    // pass (rows outside the diagonal repeat its nearest cell, which writes
-    // the same bytes twice), so the number of stores is fixed. All LDS reads
-    // are issued before the first store: one LDS round trip.
-    constexpr int NITF = STAGE ? (NT * 16 * Q::QF + NTH - 1) / NTH : 0;
-    // The lane's chunk of each write-back pass: cell row, chunk index in the
-    // staged row and bytes per canvas cell of its tensor (gates, outputs or
-    // cell states) packed as rowbytes << 8 | chunk, and its address at idx = 0.
-    int fcell[NITF > 0 ? NITF : 1], fcr[NITF > 0 ? NITF : 1];
-    char* fptr[NITF > 0 ? NITF : 1];
-#pragma unroll
-    for (int it = 0; it < NITF; ++it) {
-        const int i = min(it * NTH + (int)threadIdx.x, NT * 16 * Q::QF - 1);
-        const int r = i % Q::QF;
-        fcell[it] = i / Q::QF;
-        if (r < Q::QZ) {
-            fptr[it] = reinterpret_cast<char*>(Z + d * G) + 16 * r + M.c0 * RBZ;
-            fcr[it] = RBZ << 8 | r;
-        } else if (r < Q::QZ + Q::QY) {
-            fptr[it] = reinterpret_cast<char*>(Y + d * H) + 16 * (r - Q::QZ) + M.c0 * (4 * H * (int)sizeof(T));
-            fcr[it] = (4 * H * (int)sizeof(T)) << 8 | r;
-        } else {
-            fptr[it] = reinterpret_cast<char*>(Cs + d * H) + 16 * (r - Q::QZ - Q::QY) + M.c0 * (16 * H);
-            fcr[it] = (16 * H) << 8 | r;
-        }
-    }
-    auto flush_read = [&](int sp, u32x4 (&v)[NITF > 0 ? NITF : 1]) {
-        const int ylo = max(0, sp - R.w + 1), yhi = min(R.h - 1, sp);
-#pragma unroll
-        for (int it = 0; it < NITF; ++it) v[it] = ostage[min(max(fcell[it], ylo), yhi)][fcr[it] & 255];
-    };
-    auto flush_store = [&](int sp, const u32x4 (&v)[NITF > 0 ? NITF : 1]) {
-        const int ylo = max(0, sp - R.w + 1), yhi = min(R.h - 1, sp);
-        const int sxs = M.sx * sp;
-#pragma unroll
-        for (int it = 0; it < NITF; ++it) {
-            const int cell = min(max(fcell[it], ylo), yhi);
-            *reinterpret_cast<u32x4*>(fptr[it] + (int64_t)(sxs + cell * M.ky) * (fcr[it] >> 8)) = v[it];
-        }
-    };
-    auto flush = [&](int sp) {
-        if constexpr (STAGE) {
-            u32x4 v[NITF > 0 ? NITF : 1];
-            flush_read(sp, v);
-            flush_store(sp, v);
-        }
-    };
-
-    // Recurrent contraction of step s on MFMA from [h_L ; h_T] of the previous
-    // diagonal: the lane's own sigmoid gates (acc) and this wave's reduction
-    // slice of the candidate tile (ag). Staged, tiles outside the diagonal are
-    // computed too (their results are not used), which keeps a step's MFMAs
-    // in one block with the memory work issued behind them; otherwise they
-    // are skipped.
-    constexpr bool SKIP = !STAGE;
-    auto mma = [&](int s, floatx4 (&acc)[TPG][WQ], floatx4 (&ag)[TPG]) {
-        const int prv = (s & 1) ^ 1;
-        const int ylo = max(0, s - R.w + 1), yhi = min(R.h - 1, s);
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            if (SKIP && (16 * nt > yhi || 16 * nt + 15 < ylo)) continue;  // uniform over the workgroup
-            const int yy = 16 * nt + n16;
-            const T* brow = (q < 2) ? &hbuf[prv][yy + 1][q * KRUN] : &hbuf[prv][yy][(q - 2) * KRUN];
-            Op bop[NSTEP], bg[GSTEP];
-            lds_run<T, NSTEP>(brow, bop);
-            lds_run<T, GSTEP>(brow + sp * GSTEP * O::PER, bg);
-            ag[lt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < GSTEP; ++ks) ag[lt] = O::mma(Ag[ks], bg[ks], ag[lt]);
-#pragma unroll
-            for (int wq = 0; wq < WQ; ++wq) acc[lt][wq] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < NSTEP; ++ks)
-#pragma unroll
-                for (int wq = 0; wq < WQ; ++wq) acc[lt][wq] = O::mma(Aown[wq][ks], bop[ks], acc[lt][wq]);
-        }
-    };
-    // The candidate slices go to LDS for the cell phase to sum.
-    auto partials = [&](int s, const floatx4 (&ag)[TPG]) {
-        const int ylo = max(0, s - R.w + 1), yhi = min(R.h - 1, s);
-        const int j0 = 16 * gt + 4 * q;
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            if (SKIP && (16 * nt > yhi || 16 * nt + 15 < ylo)) continue;
-            const int yy = 16 * nt + n16;
-            if (j0 < H) {
-                *reinterpret_cast<float2*>(&gpart[sp][yy][j0]) = make_float2(ag[lt][0], ag[lt][1]);
-                *reinterpret_cast<float2*>(&gpart[sp][yy][j0 + 2]) = make_float2(ag[lt][2], ag[lt][3]);
-            }
-        }
-    };
-    // Inputs of the cell updates of step s that are ready before its
-    // contraction: the pre-activations and the top neighbours' cell states.
-    auto pre_read = [&](int s, const FPre<TPG, WQ, T>& b, float (&zv)[TPG][WQ][5], float (&ct)[TPG][WQ],
-                        uint32_t (&mk)[TPG]) {
-        const int prv = (s & 1) ^ 1;
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            const int yy = 16 * nt + n16;
-            if constexpr (STAGE)
-                mk[lt] = mst[s & 1][yy];
-            else
-                mk[lt] = b.m[lt];
-#pragma unroll
-            for (int wq = 0; wq < WQ; ++wq) {
-                const int j = 4 * (w * WQ + wq) + q;
-#pragma unroll
-                for (int t = 0; t < 5; ++t) {
-                    if constexpr (STAGE)
-                        zv[lt][wq][t] = ld1f<T>(reinterpret_cast<const T*>(&zst[s & 1][yy * PZ]) + t * H + j);
-                    else
-                        zv[lt][wq][t] = ld1f<T>(&b.z[lt][wq][t]);
-                }
-                ct[lt][wq] = cbuf[prv][yy][j];
-            }
-        }
-    };
-    // Cell updates: the lane owns (cell 16 nt + n16, hidden unit 4 (w WQ + wq) + q).
-    auto update = [&](int s, const FPre<TPG, WQ, T>& b, const floatx4 (&acc)[TPG][WQ], const float (&zv0)[TPG][WQ][5],
-                      const float (&ct)[TPG][WQ], const uint32_t (&mk)[TPG]) {
-        const int cur = s & 1, prv = cur ^ 1;
-        const int ylo = max(0, s - R.w + 1), yhi = min(R.h - 1, s);
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            if (16 * nt > yhi || 16 * nt + 15 < ylo) continue;
-            const int yy = 16 * nt + n16;
-#pragma unroll
-            for (int wq = 0; wq < WQ; ++wq) {
-                const int j = 4 * (w * WQ + wq) + q;
-                float cn = 0.0f, hn = 0.0f;
-                if (yy >= ylo && yy <= yhi) {
-                    const float* zv = zv0[lt][wq];
-                    float gs = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < SPL; ++k) gs += gpart[k][yy][j];
-                    const float gi = sigm_fast(acc[lt][wq][0] + zv[0]);
-                    const float gfl = sigm_fast(acc[lt][wq][1] + zv[1]);
-                    const float gft = sigm_fast(acc[lt][wq][2] + zv[2]);
-                    const float go = sigm_fast(acc[lt][wq][3] + zv[3]);
-                    const float gg = tanh_fast(gs + zv[4]);
-                    cn = gi * gg + gfl * cprev[lt][wq] + gft * ct[lt][wq];
-                    hn = go * tanh_fast(cn);
-                    if (!mk[lt]) {
-                        cn = 0.0f;
-                        hn = 0.0f;
-                    }
-                    if constexpr (STAGE) {
-                        T* oz = reinterpret_cast<T*>(&ostage[yy][0]);
-                        oz[0 * H + j] = from_f<T>(gi);
-                        oz[1 * H + j] = from_f<T>(gfl);
-                        oz[2 * H + j] = from_f<T>(gft);
-                        oz[3 * H + j] = from_f<T>(go);
-                        oz[4 * H + j] = from_f<T>(gg);
-                        oz[5 * H + j] = from_f<T>(hn);
-                        reinterpret_cast<float*>(&ostage[yy][Q::QZ + Q::QY])[j] = cn;
-                    } else {
-                        const int64_t p = b.p[lt];
-                        if (mk[lt]) {
-                            T* zp = Z + p * (4 * G) + d * G + j;
-                            zp[0 * H] = from_f<T>(gi);
-                            zp[1 * H] = from_f<T>(gfl);
-                            zp[2 * H] = from_f<T>(gft);
-                            zp[3 * H] = from_f<T>(go);
-                            zp[4 * H] = from_f<T>(gg);
-                            Y[p * (4 * H) + d * H + j] = from_f<T>(hn);
-                        }
-                        Cs[p * (4 * H) + d * H + j] = cn;
-                    }
-                }
-                cprev[lt][wq] = cn;
-                hbuf[cur][yy + 1][j] = from_f<T>(hn);
-                cbuf[cur][yy + 1][j] = cn;
-            }
-        }
-    };
-    auto compute = [&](int s, const FPre<TPG, WQ, T>& b) {
-        floatx4 acc[TPG][WQ], ag[TPG];
-        float zv[TPG][WQ][5], ct[TPG][WQ];
-        uint32_t mk[TPG];
-        pre_read(s, b, zv, ct, mk);
-        mma(s, acc, ag);
-        partials(s, ag);
-        lds_barrier();
-        update(s, b, acc, zv, ct, mk);
-        lds_barrier();
-    };
-
-    lds_barrier();
-    FPre<TPG, WQ, T> b0, b1;
-    if constexpr (STAGE) {
-        // Step s: the MFMAs first, then the LDS reads that the previous step
-        // made ready (the outputs of step s - 1 to write back, the
-        // pre-activations and mask bytes staged for step s, the top cell
-        // states); behind them the registers loaded for step s + 1 PFD steps
-        // ago go to LDS, the loads of step s + 1 + PFD are issued into them
-        // (past the last step they re-read valid cells) and step s - 1 is
-        // written back; the candidate partials go to LDS once their MFMAs are
-        // done; then the cell phase. Two steps of prefetch cover the load
-        // latency when the whole chip streams to and from memory.
-        auto step = [&](int s, int k, auto with_flush) {
-            constexpr bool WF = decltype(with_flush)::value;
-            floatx4 acc[TPG][WQ], ag[TPG];
-            mma(s, acc, ag);
-            u32x4 fv[NITF > 0 ? NITF : 1];
-            if constexpr (WF) flush_read(s - 1, fv);
-            float zv[TPG][WQ][5], ct[TPG][WQ];
-            uint32_t mk[TPG];
-            pre_read(s, b0, zv, ct, mk);
-            stage_in(s + 1, k);
-            fetch_z(s + 1 + PFD, k);
-            if constexpr (WF) flush_store(s - 1, fv);
-            partials(s, ag);
-            lds_barrier();
-            update(s, b0, acc, zv, ct, mk);
-            lds_barrier();
-        };
-        constexpr int K1 = PFD - 1;  // register set of diagonals sb + 1, sb + 3, ...
-        fetch_z(sb, 0);
-        stage_in(sb, 0);
-        fetch_z(sb + PFD, 0);
-        if constexpr (PFD == 2) fetch_z(sb + 1, 1);
-        lds_barrier();
-        step(sb, K1, std::false_type{});
-        int s = sb + 1;
-        for (; s + 1 < se; s += 2) {
-            step(s, 0, std::true_type{});
-            step(s + 1, K1, std::true_type{});
-        }
-        if (s < se) step(s, 0, std::true_type{});
-        flush(se - 1);
-    } else if constexpr (Prefetch2<T>::template on<TPG, WQ>()) {
-        fetch(sb, b0);
-        int s = sb;
-        for (; s + 1 < se; s += 2) {
-            fetch(s + 1, b1);
-            compute(s, b0);
-            fetch(s + 2, b0);
-            compute(s + 1, b1);
-        }
-        if (s < se) compute(s, b0);
-    } else {
-        for (int s = sb; s < se; ++s) {
-            fetch(s, b0);
-            compute(s, b0);
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Forward for wide layers (bf16, H = 128: four quads per wave, where the
@@ -708,7 +244,7 @@ struct FwdBig {
 };
 
 template <int H, int NT, typename T>
-__device__ __forceinline__ void wave_fwd_big(const WaveArgs& a, const int unit) {
+__device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
     using O = Ops<T>;
     using Op = typename O::Op;
     constexpr int G = 5 * H, KRUN = H / 2, NSTEP = KRUN / O::PER, NTH = 512;
@@ -1400,77 +936,18 @@ __device__ __forceinline__ void wave_bwd_big(const WaveArgs& a, const int unit) 
 // unit shares its CU with fewer others than when every unit has its own
 // workgroup from the start; without one, workgroup b runs unit b.
 // ---------------------------------------------------------------------------
-// Forward loads run one step ahead with one workgroup per unit, two steps
-// ahead when several workgroups per CU take units from the queue (the load
-// latency grows while every CU streams to and from memory).
-// Output rows of the invalid cells (outside every rectangle, or masked) set
-// to zero, a wave per 64 cells over the grid: each lane reads one cell's mask
-// byte and rect id, then the wave clears the rows of the invalid ones with the
-// lanes along the row. Done before any unit starts; the units write the rows
-// of the valid cells.
-__device__ __forceinline__ void zero_invalid_rows(const WaveArgs& a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    uint2* const y = static_cast<uint2*>(a.y);
-    for (int64_t c0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64; c0 < a.n_cells;
-         c0 += waves * 64) {
-        const int64_t p = c0 + lane;
-        const bool bad = p < a.n_cells && (a.mask[p] == 0 || a.rid[p] < 0);
-        for (uint64_t bm = __ballot(bad); bm; bm &= bm - 1) {
-            uint2* row = y + (c0 + __builtin_ctzll(bm)) * a.yrow_words;
-            for (int k = lane; k < a.yrow_words; k += 64) row[k] = make_uint2(0u, 0u);
-        }
-    }
+template <int H, int NT, typename T>
+__global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_fwd(FwdArgs a) {
+    if (a.rid) zero_invalid_rows(a);
+    for_units(a, [&](int unit) { wave_fwd_big<H, NT, T>(a, unit); });
 }
 
-template <int H, int NT, typename T, bool FWD, bool QUEUE>
-__device__ __forceinline__ void run_units(const WaveArgs& a) {
-    if constexpr (FWD) {
-        if (a.rid) zero_invalid_rows(a);
-    }
-    if constexpr (!QUEUE) {
-        if constexpr (FWD && FwdBig<H, T>::on) wave_fwd_big<H, NT, T>(a, a.units[blockIdx.x]);
-        else if (FWD) wave_fwd_unit<H, NT, T, 1>(a, a.units[blockIdx.x]);
-        else if constexpr (BwdBig<H, T>::on) wave_bwd_big<H, NT, T>(a, a.units[blockIdx.x]);
-        else wave_bwd_unit<H, NT, T>(a, a.units[blockIdx.x]);
-        return;
-    }
-    __shared__ int slot;
-    for (;;) {
-        lds_barrier();
-        if (threadIdx.x == 0) slot = (int)atomicAdd(a.queue, 1u);
-        lds_barrier();
-        const int k = slot;
-        if (k >= a.n_units) break;
-        // forward: two steps of prefetch, except where tile groups at H >= 32
-        // leave too few registers (1024 threads) and one step measured faster
-        if constexpr (FWD && FwdBig<H, T>::on) wave_fwd_big<H, NT, T>(a, a.units[k]);
-        else if (FWD) wave_fwd_unit<H, NT, T, (TileGroups<H, NT, T>::NG > 1 && H >= 32) ? 1 : 2>(a, a.units[k]);
-        else if constexpr (BwdBig<H, T>::on) wave_bwd_big<H, NT, T>(a, a.units[k]);
-        else wave_bwd_unit<H, NT, T>(a, a.units[k]);
-    }
-    // Count the workgroup out; the last one leaves both counters at zero for
-    // the next launch (every other workgroup's last take precedes its count).
-    if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(a.queue + 1, 1u) == gridDim.x - 1) {
-            __threadfence();
-            atomicExch(a.queue, 0u);
-            atomicExch(a.queue + 1, 0u);
-        }
-    }
-}
-
-template <int H, int NT, typename T, bool QUEUE>
-__global__ void __launch_bounds__((64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG))
-k_wave_fwd(WaveArgs a) {
-    run_units<H, NT, T, true, QUEUE>(a);
-}
-
-template <int H, int NT, typename T, bool QUEUE>
-__global__ void __launch_bounds__((64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG))
-k_wave_bwd(WaveArgs a) {
-    run_units<H, NT, T, false, QUEUE>(a);
+template <int H, int NT, typename T>
+__global__ void __launch_bounds__((64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG)) k_wave_bwd(WaveArgs a) {
+    for_units(a, [&](int unit) {
+        if constexpr (BwdBig<H, T>::on) wave_bwd_big<H, NT, T>(a, unit);
+        else wave_bwd_unit<H, NT, T>(a, unit);
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1486,36 +963,29 @@ constexpr bool bwd_fits() {
 }
 
 template <int H, int NT, typename T>
-static void launch_unit(bool fwd, int n_groups, const WaveArgs& a, hipStream_t s) {
+static void launch_unit(int n_groups, const WaveArgs& a, hipStream_t s) {
     const dim3 grid(n_groups), block(64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG);
-    if (a.queue) {
-        if (fwd) hipLaunchKernelGGL((k_wave_fwd<H, NT, T, true>), grid, block, 0, s, a);
-        else if constexpr (bwd_fits<H, NT, T>()) hipLaunchKernelGGL((k_wave_bwd<H, NT, T, true>), grid, block, 0, s, a);
-    } else {
-        if (fwd) hipLaunchKernelGGL((k_wave_fwd<H, NT, T, false>), grid, block, 0, s, a);
-        else if constexpr (bwd_fits<H, NT, T>()) hipLaunchKernelGGL((k_wave_bwd<H, NT, T, false>), grid, block, 0, s, a);
-    }
+    if constexpr (bwd_fits<H, NT, T>()) hipLaunchKernelGGL((k_wave_bwd<H, NT, T>), grid, block, 0, s, a);
 }
 
 template <int H, typename T>
-static hipError_t launch_nt(bool fwd, int nt, int n_units, const WaveArgs& a, hipStream_t s) {
+static hipError_t launch_nt(int nt, int n_units, const WaveArgs& a, hipStream_t s) {
     if (nt == 4 && !bwd_fits<H, 4, T>()) return hipErrorInvalidValue;  // host rejects these rectangles
     switch (nt) {
-        case 1: launch_unit<H, 1, T>(fwd, n_units, a, s); break;
-        case 2: launch_unit<H, 2, T>(fwd, n_units, a, s); break;
-        case 3: launch_unit<H, 3, T>(fwd, n_units, a, s); break;
-        case 4: launch_unit<H, 4, T>(fwd, n_units, a, s); break;
+        case 1: launch_unit<H, 1, T>(n_units, a, s); break;
+        case 2: launch_unit<H, 2, T>(n_units, a, s); break;
+        case 3: launch_unit<H, 3, T>(n_units, a, s); break;
+        case 4: launch_unit<H, 4, T>(n_units, a, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-// Workgroups per CU when units are taken from a queue: the forward runs
-// fastest with a unit per CU at a time, the backward (fewer registers, more
-// latency per step) with two.
-constexpr int FWD_GROUPS_PER_CU = 1, BWD_GROUPS_PER_CU = 2;
+// Workgroups per CU when units are taken from a queue (two hide the latency
+// of a step better than one).
+constexpr int BWD_GROUPS_PER_CU = 2;
 
-static hipError_t launch_wave(bool fwd, const LayerGeom& g, int nt, int n_units, WaveArgs a, hipStream_t s) {
+static hipError_t launch_wave_bwd(const LayerGeom& g, int nt, int n_units, WaveArgs a, hipStream_t s) {
     if (n_units == 0) return hipSuccess;
     a.n_units = n_units;
     if (a.queue) {
@@ -1523,7 +993,7 @@ static hipError_t launch_wave(bool fwd, const LayerGeom& g, int nt, int n_units,
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
-        const int groups = (fwd ? FWD_GROUPS_PER_CU : BWD_GROUPS_PER_CU) * std::max(cus, 1);
+        const int groups = BWD_GROUPS_PER_CU * std::max(cus, 1);
         if (n_units > groups) {  // else one workgroup per unit
             n_units = groups;
         } else {
@@ -1532,26 +1002,125 @@ static hipError_t launch_wave(bool fwd, const LayerGeom& g, int nt, int n_units,
     }
     if (g.dtype == 0) {
         switch (g.hidden) {
-            case 4: return launch_nt<4, float>(fwd, nt, n_units, a, s);
-            case 8: return launch_nt<8, float>(fwd, nt, n_units, a, s);
-            case 16: return launch_nt<16, float>(fwd, nt, n_units, a, s);
-            case 32: return launch_nt<32, float>(fwd, nt, n_units, a, s);
-            case 64: return launch_nt<64, float>(fwd, nt, n_units, a, s);
+            case 4: return launch_nt<4, float>(nt, n_units, a, s);
+            case 8: return launch_nt<8, float>(nt, n_units, a, s);
+            case 16: return launch_nt<16, float>(nt, n_units, a, s);
+            case 32: return launch_nt<32, float>(nt, n_units, a, s);
+            case 64: return launch_nt<64, float>(nt, n_units, a, s);
             default: return hipErrorInvalidValue;
         }
     }
     switch (g.hidden) {
-        case 32: return launch_nt<32, bf16_t>(fwd, nt, n_units, a, s);
-        case 64: return launch_nt<64, bf16_t>(fwd, nt, n_units, a, s);
-        case 128: return launch_nt<128, bf16_t>(fwd, nt, n_units, a, s);
+        case 32: return launch_nt<32, bf16_t>(nt, n_units, a, s);
+        case 64: return launch_nt<64, bf16_t>(nt, n_units, a, s);
+        case 128: return launch_nt<128, bf16_t>(nt, n_units, a, s);
         default: return hipErrorInvalidValue;
     }
 }
 
+// The forward kernel of a shape. bf16 H = 128 has its own kernel: its operands
+// alone take 160 registers a lane at eight waves.
+static FwdKernel fwd_kernel_of(const LayerGeom& g, int nt) {
+    const int ck = fwd_fused_steps(g);
+    if (g.dtype == 0) {
+        switch (g.hidden) {
+            case 4: return fwd_kernel_f32_h4(nt, ck);
+            case 8: return fwd_kernel_f32_h8(nt, ck);
+            case 16: return fwd_kernel_f32_h16(nt, ck);
+            case 32: return fwd_kernel_f32_h32(nt, ck);
+            case 64: return fwd_kernel_f32_h64(nt, ck);
+            default: return {};
+        }
+    }
+    switch (g.hidden) {
+        case 32: return fwd_kernel_bf16_h32(nt, ck);
+        case 64: return fwd_kernel_bf16_h64(nt, ck);
+        case 128: {
+            constexpr int th = 64 * Geo<128, bf16_t>::NW;
+            switch (nt) {
+                case 1: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 1, bf16_t>), th};
+                case 2: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 2, bf16_t>), th};
+                case 3: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 3, bf16_t>), th};
+                case 4: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 4, bf16_t>), th};
+                default: return {};
+            }
+        }
+        default: return {};
+    }
+}
+
+// K steps of 32 input channels that the forward wavefront takes over from the
+// projection (0: the projection runs apart).
+int fwd_fused_steps(const LayerGeom& g) {
+    if (g.c_in > 64 || !(g.dtype == 0 ? fwd_fusable<float>(g.hidden) : fwd_fusable<bf16_t>(g.hidden))) return 0;
+    return (g.c_in + 31) / 32;
+}
+
+size_t fwd_x_bytes(const LayerGeom& g) {
+    return g.dtype == 0 ? (size_t)g.n_cells * (fwd_fused_steps(g) * 32 * 3 * 2 + 16) : 0;
+}
+
+// Inputs of the rectangles' cells as the forward reads them: three bf16
+// pieces, channels padded with zeros to 32 CK, then 16 bytes whose first word
+// says whether the cell is valid. A thread per 8 channels of a cell, and one
+// for the validity.
+__global__ void __launch_bounds__(256) k_split_x(int64_t n_cells, int c, int cp, const float* __restrict__ x,
+                                                 const int32_t* __restrict__ rid, const uint8_t* __restrict__ mask,
+                                                 bf16_t* __restrict__ xs) {
+    const int per = cp / 8 + 1, row = 3 * cp + 8;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_cells * per; i += (int64_t)gridDim.x * 256) {
+        const int64_t p = i / per;
+        const int k = (int)(i - p * per) * 8;
+        if (rid[p] < 0) continue;
+        if (k == cp) {
+            *reinterpret_cast<uint4*>(xs + p * row + 3 * cp) = make_uint4(mask[p] != 0, 0, 0, 0);
+            continue;
+        }
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+        const floatx4 v0 = k < c ? St<float>::ld4(x + p * c + k) : zero;
+        const floatx4 v1 = k + 4 < c ? St<float>::ld4(x + p * c + k + 4) : zero;
+        const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+        bf16x8 o[3];
+        make_op<float>(v, o);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) *reinterpret_cast<bf16x8*>(xs + p * row + e * cp + k) = o[e];
+    }
+}
+
+hipError_t launch_split_x(const LayerGeom& g, const void* d_x, const int32_t* d_rid, const uint8_t* d_mask,
+                          void* d_xs, hipStream_t s) {
+    const int cp = 32 * fwd_fused_steps(g);
+    if (g.dtype != 0 || cp == 0 || g.n_cells == 0) return hipSuccess;
+    const int64_t n = g.n_cells * (cp / 8 + 1);
+    hipLaunchKernelGGL(k_split_x, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), dim3(256), 0, s,
+                       g.n_cells, g.c_in, cp, static_cast<const float*>(d_x), d_rid, d_mask,
+                       static_cast<bf16_t*>(d_xs));
+    return hipGetLastError();
+}
+
+// Workgroups of a kernel that the device holds at once (256 CUs assumed when
+// the query fails).
+static int resident_groups(const FwdKernel& k) {
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        cus = 256;
+    }
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k.fn, k.threads, 0) != hipSuccess || per < 1) {
+        (void)hipGetLastError();
+        per = 1;
+    }
+    return cus * per;
+}
+
 hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
-                                const int32_t* d_rects, const uint8_t* d_mask, const int32_t* d_rid, const void* d_u,
-                                void* d_z, float* d_c, void* d_y, unsigned* d_queue, hipStream_t s) {
+                                const int32_t* d_rects, const uint8_t* d_mask, const int32_t* d_rid,
+                                const FwdTensors& t, unsigned* d_queue, hipStream_t s) {
     const int yrow_words = 4 * g.hidden * (g.dtype == 1 ? 2 : 4) / 8;
+    const FwdKernel k = n_units > 0 ? fwd_kernel_of(g, nt) : FwdKernel{};
+    if (n_units > 0 && !k.fn) return hipErrorInvalidValue;
+    const int groups = n_units > 0 ? resident_groups(k) : 0;
     // the launch's own workgroups zero the invalid rows when there are enough
     // of them to cover the canvas quickly (at least one per CU); else a
     // separate kernel does
@@ -1560,72 +1129,44 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
                   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess))
         return hipErrorInvalidDevice;
     if (d_rid && n_units < cus) {
-        const hipError_t e = launch_zero_invalid(g, 4 * g.hidden, d_mask, d_rid, d_y, s);
+        const hipError_t e = launch_zero_invalid(g, 4 * g.hidden, d_mask, d_rid, t.y, s);
         if (e != hipSuccess) return e;
         d_rid = nullptr;
     }
-    WaveArgs a{d_units,  d_rects, d_mask, d_u,   d_z,       d_c,       d_y,       nullptr, g.canvas_w, 0,
-               INT_MAX, d_queue, n_units, d_rid, g.n_cells, yrow_words};
-    return launch_wave(true, g, nt, n_units, a, s);
+    if (n_units == 0) return hipSuccess;
+    FwdArgs a{d_units,    d_rects, d_mask,  t.u,     t.wx,
+              t.b,        t.x,     g.c_in,  t.z,     t.c,
+              t.y,        g.canvas_w, 0,    INT_MAX, n_units > groups ? d_queue : nullptr,
+              n_units,    d_rid,   g.n_cells, yrow_words};
+    void* params[] = {&a};
+    return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }
 
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
                                 const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, const void* d_dy,
                                 void* d_z, const float* d_c, unsigned* d_queue, hipStream_t s) {
-    WaveArgs a{d_units, d_rects, d_mask,  d_u,     d_z,     const_cast<float*>(d_c), nullptr, d_dy, g.canvas_w, 0,
-               INT_MAX, d_queue, n_units, nullptr, 0,       0};
-    return launch_wave(false, g, nt, n_units, a, s);
-}
-
-// Forward kernel of a shape and its workgroup size, for graph nodes.
-template <int H, typename T>
-static bool fwd_kernel(int nt, const void** fn, int* threads) {
-    constexpr int w64 = 64 * Geo<H, T>::NW;
-    switch (nt) {
-        case 1: *threads = w64 * TileGroups<H, 1, T>::NG; *fn = reinterpret_cast<const void*>(&k_wave_fwd<H, 1, T, false>); return true;
-        case 2: *threads = w64 * TileGroups<H, 2, T>::NG; *fn = reinterpret_cast<const void*>(&k_wave_fwd<H, 2, T, false>); return true;
-        case 3: *threads = w64 * TileGroups<H, 3, T>::NG; *fn = reinterpret_cast<const void*>(&k_wave_fwd<H, 3, T, false>); return true;
-        case 4: *threads = w64 * TileGroups<H, 4, T>::NG; *fn = reinterpret_cast<const void*>(&k_wave_fwd<H, 4, T, false>); return true;
-        default: return false;
-    }
+    WaveArgs a{d_units, d_rects, d_mask, d_u, d_z, const_cast<float*>(d_c), d_dy, g.canvas_w, d_queue, n_units};
+    return launch_wave_bwd(g, nt, n_units, a, s);
 }
 
 hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, int max_steps, const int32_t* d_units,
-                                     const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, void* d_z,
-                                     float* d_c, void* d_y, hipGraphExec_t* exec) {
-    const void* fn = nullptr;
-    int threads = 0;
-    bool ok = false;
-    if (g.dtype == 0) {
-        switch (g.hidden) {
-            case 4: ok = fwd_kernel<4, float>(nt, &fn, &threads); break;
-            case 8: ok = fwd_kernel<8, float>(nt, &fn, &threads); break;
-            case 16: ok = fwd_kernel<16, float>(nt, &fn, &threads); break;
-            case 32: ok = fwd_kernel<32, float>(nt, &fn, &threads); break;
-            case 64: ok = fwd_kernel<64, float>(nt, &fn, &threads); break;
-            default: break;
-        }
-    } else {
-        switch (g.hidden) {
-            case 32: ok = fwd_kernel<32, bf16_t>(nt, &fn, &threads); break;
-            case 64: ok = fwd_kernel<64, bf16_t>(nt, &fn, &threads); break;
-            case 128: ok = fwd_kernel<128, bf16_t>(nt, &fn, &threads); break;
-            default: break;
-        }
-    }
-    if (!ok || n_units <= 0 || max_steps <= 0) return hipErrorInvalidValue;
+                                     const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t,
+                                     hipGraphExec_t* exec) {
+    if (n_units <= 0 || max_steps <= 0) return hipErrorInvalidValue;
+    const FwdKernel k = fwd_kernel_of(g, nt);
+    if (!k.fn) return hipErrorInvalidValue;
     hipGraph_t graph;
     hipError_t e = hipGraphCreate(&graph, 0);
     if (e != hipSuccess) return e;
     hipGraphNode_t prev = nullptr;
     for (int st = 0; st < max_steps && e == hipSuccess; ++st) {
-        WaveArgs a{d_units, d_rects, d_mask, d_u, d_z, d_c, d_y, nullptr, g.canvas_w, st, st + 1, nullptr, n_units,
-                   nullptr, 0,       0};
+        FwdArgs a{d_units, d_rects, d_mask,     t.u, t.wx,   t.b,     t.x,     g.c_in,  t.z, t.c,
+                  t.y,     g.canvas_w, st, st + 1, nullptr, n_units, nullptr, 0,   0};
         void* params[] = {&a};
         hipKernelNodeParams p{};
-        p.func = const_cast<void*>(fn);
+        p.func = const_cast<void*>(k.fn);
         p.gridDim = dim3(n_units);
-        p.blockDim = dim3(threads);
+        p.blockDim = dim3(k.threads);
         p.sharedMemBytes = 0;
         p.kernelParams = params;
         p.extra = nullptr;

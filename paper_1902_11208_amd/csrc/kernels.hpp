@@ -51,22 +51,42 @@ hipError_t launch_count_nonfinite(const void* d, int64_t n_cells, int row, const
 // Zero the rows of a [n_cells][width] tensor (storage dtype) whose cell is invalid.
 hipError_t launch_zero_invalid(const LayerGeom& g, int width, const uint8_t* d_mask,
                                const int32_t* d_rid, void* d_t, hipStream_t s);
+// Tensors of a forward wavefront. x: the inputs as the kernel reads them, that
+// is the layer's own (bf16) or their pieces (fp32, launch_split_x); unused
+// where the projection runs apart (fwd_fused_steps == 0).
+struct FwdTensors {
+    const void* u;
+    const void* wx;
+    const void* b;
+    const void* x;
+    void* z;
+    float* c;
+    void* y;
+};
+// K steps of 32 input channels the forward wavefront computes itself; 0 where
+// launch_projection has to run first.
+int fwd_fused_steps(const LayerGeom& g);
+// Workspace of the fp32 inputs' pieces, and the kernel that fills it for the
+// cells of the rectangles.
+size_t fwd_x_bytes(const LayerGeom& g);
+hipError_t launch_split_x(const LayerGeom& g, const void* d_x, const int32_t* d_rid, const uint8_t* d_mask,
+                          void* d_xs, hipStream_t s);
 // Forward anti-diagonal wavefront over n_units units (rectangle, direction)
 // in the order of d_units. d_queue: two device counters, zero on entry (the
-// workgroups take units from the first, a fixed number per CU, and count
-// themselves out on the second; the last one out zeroes both again). With
-// d_rid set, the output rows of cells outside every rectangle or masked are
-// zeroed first.
+// workgroups take units from the first, as many as are resident at once, and
+// count themselves out on the second; the last one out zeroes both again).
+// With d_rid set, the output rows of cells outside every rectangle or masked
+// are zeroed first.
 hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
                                 const int32_t* d_rects, const uint8_t* d_mask, const int32_t* d_rid,
-                                const void* d_u, void* d_z, float* d_c, void* d_y, unsigned* d_queue, hipStream_t s);
+                                const FwdTensors& t, unsigned* d_queue, hipStream_t s);
 
 // The forward wavefront as one launch per local diagonal (diagonal s of every
 // unit in launch s), recorded as a chain of max_steps kernel nodes into an
 // instantiated graph; same results as launch_wavefront_fwd.
 hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, int max_steps, const int32_t* d_units,
-                                     const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, void* d_z,
-                                     float* d_c, void* d_y, hipGraphExec_t* exec);
+                                     const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t,
+                                     hipGraphExec_t* exec);
 
 // --- backward --------------------------------------------------------------
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,

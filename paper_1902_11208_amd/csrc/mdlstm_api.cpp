@@ -139,7 +139,7 @@ bool same_shape(const mdlstm_layer_desc* a, const mdlstm_layer_desc& b) {
 }
 
 struct Plan {
-    size_t z, c, rid, rects, units, part, flags, wxt, dvpart, queue, check, total;
+    size_t z, c, rid, rects, units, part, flags, wxt, dvpart, xs, queue, check, total;
 };
 
 mdl::LayerGeom geom(const mdlstm_layer_desc* d, int32_t ch, int32_t cw) {
@@ -178,6 +178,8 @@ Plan plan(const mdlstm_layer_desc* d, int32_t ch, int32_t cw, int32_t nr) {
     off += strip ? 0 : align_up(mdl::big_wxt_bytes(g));
     p.dvpart = off;  // memory-state matrices: a dV partial per unit
     off += d->memory_states ? align_up(mdl::mem_partial_bytes(g, 4 * (nr > 0 ? nr : 1))) : 0;
+    p.xs = off;  // fp32 inputs as the forward wavefront reads them
+    off += align_up(mdl::fwd_x_bytes(g));
     p.queue = off;  // unit queue: next unit, workgroups done
     off += align_up(8);
     p.check = off;  // non-finite count of the debug mode
@@ -628,6 +630,12 @@ int32_t mdlstm_gradients_fused(const mdlstm_layer_desc* desc) {
     return mdl::strip_supported(geom(&in, 1, 1)) ? 1 : 0;
 }
 
+int32_t mdlstm_projection_fused(const mdlstm_layer_desc* desc) {
+    mdlstm_layer_desc in;
+    if (inner_desc(desc, &in) != MDLSTM_OK) return -1;
+    return !in.memory_states && mdl::fwd_fused_steps(geom(&in, 1, 1)) > 0 ? 1 : 0;
+}
+
 namespace {
 
 // The per-diagonal graph of the last mdlstm_forward_stepwise call on this
@@ -665,7 +673,12 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
     if (desc->memory_states && stepwise)
         return fail(MDLSTM_ERR_UNSUPPORTED, "the per-diagonal schedule is not built with memory-state matrices");
     HIP_OR_FAIL(mark(0, s));
-    HIP_OR_FAIL(mdl::launch_projection(c.g, d_x, d_wx, d_b, rid, c.ws + c.p.z, s));
+    const bool fused = !desc->memory_states && mdl::fwd_fused_steps(c.g) > 0;
+    if (!fused)
+        HIP_OR_FAIL(mdl::launch_projection(c.g, d_x, d_wx, d_b, rid, c.ws + c.p.z, s));
+    else if (n_rects > 0)
+        HIP_OR_FAIL(mdl::launch_split_x(c.g, d_x, rid, d_mask, c.ws + c.p.xs, s));
+    const mdl::FwdTensors ft{d_u, d_wx, d_b, c.g.dtype == 0 ? c.ws + c.p.xs : d_x, c.ws + c.p.z, cs, d_y};
     HIP_OR_FAIL(mark(1, s));
     if (stepwise || n_rects == 0 || desc->memory_states)
         HIP_OR_FAIL(mdl::launch_zero_invalid(c.g, 4 * c.g.hidden, d_mask, rid, d_y, s));
@@ -678,15 +691,15 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
         HIP_OR_FAIL(mdl::launch_wavefront_mem(true, c.g, 4 * n_rects, m, s));
     } else if (!stepwise) {
         // the persistent launch also zeroes the output rows of the invalid cells
-        HIP_OR_FAIL(mdl::launch_wavefront_fwd(c.g, c.nt, 4 * n_rects, units, drects, d_mask, rid, d_u, c.ws + c.p.z,
-                                              cs, d_y, reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
+        HIP_OR_FAIL(mdl::launch_wavefront_fwd(c.g, c.nt, 4 * n_rects, units, drects, d_mask, rid, ft,
+                                              reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
     } else if (n_rects > 0) {
         int32_t max_steps = 0;
         for (int32_t k = 0; k < n_rects; ++k) max_steps = std::max(max_steps, rects[k].h + rects[k].w - 1);
         static thread_local StepGraph* cache = new StepGraph;
         std::vector<uintptr_t> key = {(uintptr_t)desc->c_in, (uintptr_t)desc->hidden, (uintptr_t)desc->dtype,
                                       (uintptr_t)canvas_h, (uintptr_t)canvas_w, (uintptr_t)d_mask, (uintptr_t)d_u,
-                                      (uintptr_t)d_y, (uintptr_t)d_workspace, (uintptr_t)n_rects};
+                                      (uintptr_t)d_wx, (uintptr_t)d_b, (uintptr_t)d_x, (uintptr_t)d_y, (uintptr_t)d_workspace, (uintptr_t)n_rects};
         for (int32_t k = 0; k < n_rects; ++k) {
             key.push_back(((uintptr_t)(uint32_t)rects[k].y0 << 32) | (uint32_t)rects[k].x0);
             key.push_back(((uintptr_t)(uint32_t)rects[k].h << 32) | (uint32_t)rects[k].w);
@@ -696,8 +709,8 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
                 HIP_OR_FAIL(hipGraphExecDestroy(cache->exec));
                 cache->exec = nullptr;
             }
-            HIP_OR_FAIL(mdl::build_wavefront_fwd_graph(c.g, c.nt, 4 * n_rects, max_steps, units, drects, d_mask, d_u,
-                                                       c.ws + c.p.z, cs, d_y, &cache->exec));
+            HIP_OR_FAIL(mdl::build_wavefront_fwd_graph(c.g, c.nt, 4 * n_rects, max_steps, units, drects, d_mask, ft,
+                                                       &cache->exec));
             cache->key = std::move(key);
         }
         HIP_OR_FAIL(hipGraphLaunch(cache->exec, s));

@@ -1,0 +1,152 @@
+// What the wavefront kernels share: launch arguments, the unit queue, vector
+// access to a lane's consecutive hidden units, and the store sink.
+#pragma once
+
+#include <climits>
+
+#include "common.hpp"
+#include "split.hpp"
+
+namespace mdl {
+
+// W consecutive values of storage type T.
+template <typename T, int W>
+struct Vec;
+template <>
+struct Vec<float, 1> {
+    using R = float;
+    static __device__ __forceinline__ float get(const R& v, int) { return v; }
+    static __device__ __forceinline__ R pack(const float (&v)[1]) { return v[0]; }
+};
+template <>
+struct Vec<float, 2> {
+    using R = floatx2;
+    static __device__ __forceinline__ float get(const R& v, int k) { return v[k]; }
+    static __device__ __forceinline__ R pack(const float (&v)[2]) { return R{v[0], v[1]}; }
+};
+template <>
+struct Vec<float, 4> {
+    using R = floatx4;
+    static __device__ __forceinline__ float get(const R& v, int k) { return v[k]; }
+    static __device__ __forceinline__ R pack(const float (&v)[4]) { return R{v[0], v[1], v[2], v[3]}; }
+};
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <>
+struct Vec<bf16_t, 1> {
+    using R = bf16_t;
+    static __device__ __forceinline__ float get(const R& v, int) { return bf2f(v); }
+    static __device__ __forceinline__ R pack(const float (&v)[1]) { return f2bf(v[0]); }
+};
+template <>
+struct Vec<bf16_t, 2> {
+    using R = uint32_t;
+    static __device__ __forceinline__ float get(const R& v, int k) {
+        return __uint_as_float(k ? (v & 0xffff0000u) : (v << 16));
+    }
+    static __device__ __forceinline__ R pack(const float (&v)[2]) { return f2bf2(v[0], v[1]); }
+};
+template <>
+struct Vec<bf16_t, 4> {
+    using R = u32x2;
+    static __device__ __forceinline__ float get(const R& v, int k) {
+        const uint32_t w = v[k >> 1];
+        return __uint_as_float((k & 1) ? (w & 0xffff0000u) : (w << 16));
+    }
+    static __device__ __forceinline__ R pack(const float (&v)[4]) { return R{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])}; }
+};
+template <typename T, int W>
+__device__ __forceinline__ typename Vec<T, W>::R ldw(const T* p) {
+    return *reinterpret_cast<const typename Vec<T, W>::R*>(p);
+}
+template <typename T, int W>
+__device__ __forceinline__ void stw(T* p, const float (&v)[W]) {
+    *reinterpret_cast<typename Vec<T, W>::R*>(p) = Vec<T, W>::pack(v);
+}
+
+struct FwdArgs {
+    const int32_t* units;  // unit = rect*4 + direction, in launch order
+    const int32_t* rects;  // [n_rects][4]
+    const uint8_t* mask;   // [n_cells]
+    const void* u;         // [4][5H][2H]
+    const void* wx;        // [4][5H][c_in]
+    const void* b;         // [4][5H]
+    const void* x;         // inputs per cell: bf16 [c_in], or the fp32 inputs as bf16 pieces [3][32 CK]
+    int c_in;
+    void* z;               // [n_cells][20H]: pre-activations in where the projection ran apart; gates out
+    float* c;              // [n_cells][4H] cell state
+    void* y;               // [n_cells][4H] output
+    int canvas_w;
+    int s0, s1;            // local diagonals [s0, s1) of every unit
+    unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
+    int n_units;
+    // when rid is set, the output rows (yrow_words x 8 bytes) of the cells
+    // outside every rectangle or masked are zeroed before the units run
+    const int32_t* rid;    // [n_cells] rectangle id, -1 outside every rectangle
+    int64_t n_cells;
+    int yrow_words;
+};
+
+// Target of the stores of lanes whose cell is outside the diagonal: every lane
+// stores on every path, so the number of memory operations in flight is the
+// same on all paths and the compiler waits for exactly the loads it needs (a
+// skipped store would make it wait for everything). 1536 bytes per lane (room
+// for a cell's gates of one direction), shared by workgroups eight apart;
+// never read.
+constexpr int WAVE_SINK_LANE = 96;  // 16-byte slots per lane
+template <int TAG>
+__device__ __attribute__((aligned(256))) uint4 g_sink[8 * 64 * WAVE_SINK_LANE];
+
+__device__ __forceinline__ char* sink_ptr() {
+    return reinterpret_cast<char*>(&g_sink<0>[((blockIdx.x & 7) * 64 + (threadIdx.x & 63)) * WAVE_SINK_LANE]);
+}
+
+// Output rows of the invalid cells (outside every rectangle, or masked) set
+// to zero, a wave per 64 cells over the grid: each lane reads one cell's mask
+// byte and rect id, then the wave clears the rows of the invalid ones with the
+// lanes along the row. Done before any unit starts; the units write the rows
+// of the valid cells.
+template <typename A>
+__device__ __forceinline__ void zero_invalid_rows(const A& a) {
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    uint2* const y = static_cast<uint2*>(a.y);
+    for (int64_t c0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64; c0 < a.n_cells;
+         c0 += waves * 64) {
+        const int64_t p = c0 + lane;
+        const bool bad = p < a.n_cells && (a.mask[p] == 0 || a.rid[p] < 0);
+        for (uint64_t bm = __ballot(bad); bm; bm &= bm - 1) {
+            uint2* row = y + (c0 + __builtin_ctzll(bm)) * a.yrow_words;
+            for (int k = lane; k < a.yrow_words; k += 64) row[k] = make_uint2(0u, 0u);
+        }
+    }
+}
+
+// Units of a launch: workgroup b runs unit b, or, with a queue, a fixed number
+// of workgroups per CU take units in launch order (longest first) until none
+// is left; the last workgroup out zeroes the queue again.
+template <typename A, typename F>
+__device__ __forceinline__ void for_units(const A& a, const F& run) {
+    __shared__ int slot;
+    for (;;) {
+        int k = (int)blockIdx.x;
+        if (a.queue) {
+            lds_barrier();  // the previous unit's LDS reads are done
+            if (threadIdx.x == 0) slot = (int)atomicAdd(a.queue, 1u);
+            lds_barrier();
+            k = __builtin_amdgcn_readfirstlane(slot);
+        }
+        if (k >= a.n_units) break;
+        run(a.units[k]);
+        if (!a.queue) return;
+    }
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(a.queue + 1, 1u) == gridDim.x - 1) {
+            __threadfence();
+            atomicExch(a.queue, 0u);
+            atomicExch(a.queue + 1, 0u);
+        }
+    }
+}
+
+}  // namespace mdl

@@ -174,6 +174,8 @@ static void fuzz_layer(void) {
     }
     const int32_t f = mdlstm_gradients_fused(dp);
     CHECK(f == -1 || f == 0 || f == 1, "gradients_fused returned %d", f);
+    const int32_t pf = mdlstm_projection_fused(dp);
+    CHECK((pf == -1) == (f == -1) && pf <= 1, "projection_fused returned %d", pf);
 }
 
 static void fuzz_pack(void) {

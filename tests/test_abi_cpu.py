@@ -272,6 +272,17 @@ def test_gradients_fused_query(built_lib):
     assert f(None) == -1
 
 
+def test_projection_fused_query(built_lib):
+    L = _lib()
+    f = L.lib().mdlstm_projection_fused
+    assert f(ctypes.byref(L.LayerDesc(32, 32, 0))) == 1    # lines: inside the wavefront
+    assert f(ctypes.byref(L.LayerDesc(65, 32, 0))) == 0    # more than 64 input channels
+    assert f(ctypes.byref(L.LayerDesc(64, 128, 1))) == 0   # bf16 H 128
+    assert f(ctypes.byref(L.LayerDesc(16, 16, 0, 1))) == 0  # memory-state matrices
+    assert f(ctypes.byref(L.LayerDesc(16, 65, 0))) == -1   # above the largest built
+    assert f(None) == -1
+
+
 def test_head_calls_reject_bad_arguments(built_lib):
     """The output-layer and CTC calls validate sizes, rectangles and labels on
     the host before any HIP call."""

@@ -22,6 +22,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "wave_bwd.hpp"
 #include "wave_fwd.hpp"
 
 namespace mdl {
@@ -133,75 +134,6 @@ struct Geo {
     static_assert(KRUN % PER == 0 && NSTEP % SPL == 0 && GT * SPL == NW, "forward split");
     static_assert(KRUNB % PER == 0 && NSTEPB % SPLB == 0, "backward split");
     static_assert(MT >= NW ? MT % NW == 0 : NW % MT == 0, "backward tiles");
-};
-
-// Per-step outputs of one cell, staged in LDS as 16-byte chunks and written
-// back by the whole workgroup with contiguous 16-byte stores: forward, the
-// 5H activated gates then the H outputs (storage type) then the H cell states
-// (fp32); backward, the 5H gate gradients.
-template <int H, typename T>
-struct OutQ {
-    static constexpr int QZ = 5 * H * (int)sizeof(T) / 16;
-    static constexpr int QY = H * (int)sizeof(T) / 16;
-    static constexpr int QC = H * 4 / 16;
-    static constexpr int QF = QZ + QY + QC;  // forward chunks per cell
-    static_assert(QZ * 16 == 5 * H * (int)sizeof(T) && QY * 16 == H * (int)sizeof(T), "chunking");
-};
-
-// Waves of a unit (forward and backward) in groups of NW, one group per
-// 16-row tile, when the workgroup stays within 1024 threads and the registers
-// allow (fp32 up to H = 32): the tiles of a diagonal then run side by side on
-// their own waves instead of one after another on the same ones.
-template <int H, int NT, typename T>
-struct TileGroups {
-    static constexpr int NG =
-        (std::is_same<T, float>::value && H <= 32 && NT >= 2 && 64 * Geo<H, T>::NW * NT <= 1024) ? NT : 1;
-};
-
-// LDS bytes of the backward kernel without and with staging of its inputs
-// (two diagonals of gates, upstream gradients and cell states).
-template <int H, int NT, typename T>
-constexpr size_t bwd_lds_base() {
-    using Gm = Geo<H, T>;
-    return (size_t)NT * 16 * (Gm::G + 16 / sizeof(T)) * sizeof(T) +
-           (size_t)Gm::SPLB * (NT * 16 + 2) * (2 * H + 2) * 4 + (size_t)(NT * 16 + 2) * (H + 2) * 4;
-}
-template <int H, int NT, typename T>
-constexpr size_t bwd_lds_stage() {
-    constexpr size_t nth = 64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG;
-    return 2 * ((NT * 16 * (OutQ<H, T>::QF + 1) + nth - 1) / nth * nth) * 16;
-}
-template <int H, int NT, typename T>
-constexpr bool bwd_stage() {
-    return bwd_lds_base<H, NT, T>() + bwd_lds_stage<H, NT, T>() <= 128 * 1024;
-}
-
-template <typename T>
-struct Prefetch2 {
-    template <int NT, int WQ>
-    static constexpr bool on() { return NT * WQ <= 2; }
-};
-
-struct WaveArgs {
-    const int32_t* units;  // unit = rect*4 + direction, in launch order
-    const int32_t* rects;  // [n_rects][4]
-    const uint8_t* mask;   // [n_cells]
-    const void* u;         // [4][5H][2H]
-    void* z;               // [n_cells][20H]: gates in, dZ out
-    float* c;              // [n_cells][4H] cell state
-    const void* dy;        // [n_cells][4H] upstream gradient
-    int canvas_w;
-    unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
-    int n_units;
-};
-
-template <int NT, int WQ, typename T>
-struct BPre {
-    T g[NT][WQ][5], dy[NT][WQ];
-    float c[NT][WQ], cl[NT][WQ], ct[NT][WQ];
-    int64_t p[NT];
-    uint32_t m[NT];
-    bool live[NT], hasl[NT], hast[NT];
 };
 
 }  // namespace
@@ -441,325 +373,6 @@ __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
 }
 
 // ---------------------------------------------------------------------------
-// Backward (reverse anti-diagonals). With successors S (right, same row, next
-// diagonal) and E (below, row + 1, next diagonal):
-//   dh = dY + (U^T da_S)[0:H] + (U^T da_E)[H:2H]
-//   dc = dh o (1 - tanh^2 c) + dc_S f_L(S) + dc_E f_T(E)
-//   da = (dc g i(1-i), dc c_L f_L(1-f_L), dc c_T f_T(1-f_T), dh tanh(c) o(1-o), dc i (1-g^2))
-// ---------------------------------------------------------------------------
-template <int H, int NT, typename T>
-__device__ __forceinline__ void wave_bwd_unit(const WaveArgs& a, const int unit) {
-    using Gm = Geo<H, T>;
-    using O = Ops<T>;
-    using Op = typename O::Op;
-    using Q = OutQ<H, T>;
-    // tile groups as in the forward: group tg owns tiles tg, tg + NG, ...
-    constexpr int NG = TileGroups<H, NT, T>::NG, TPG = NT / NG;
-    constexpr int WQ = Gm::WQ, G = Gm::G, KRUNB = Gm::KRUNB, NTH = 64 * Gm::NW * NG;
-    constexpr int TPW = Gm::TPW, SPLB = Gm::SPLB, BSTEP = Gm::BSTEP;
-    constexpr int GP = G + 16 / (int)sizeof(T);
-    // Staged: the gates, upstream gradients and cell states of a diagonal are
-    // loaded as contiguous 16-byte chunks into registers two steps ahead and
-    // kept in LDS for two steps (own cells, then left/top predecessors of the
-    // next diagonal). Otherwise every lane loads its own values.
-    constexpr bool STAGE = bwd_stage<H, NT, T>();
-    constexpr int PB = STAGE ? Q::QF + 1 : 1;  // row pitch in chunks; the extra chunk spreads LDS banks
-    constexpr int NSL = STAGE ? (NT * 16 * PB + NTH - 1) / NTH * NTH : 1;
-    constexpr int NITZ = STAGE ? NSL / NTH : 0;
-    constexpr int NITF = (NT * 16 * Q::QZ + NTH - 1) / NTH;  // passes writing back the gate gradients
-    constexpr int CC = Q::QZ + Q::QY;                        // first cell-state chunk of a row
-    __shared__ __attribute__((aligned(16))) T dabuf[NT * 16][GP];
-    // row NT*16 stays zero; row NT*16 + 1 takes the writes of tiles outside
-    // the diagonal (and of padding columns), which nobody reads
-    __shared__ __attribute__((aligned(16))) float gbuf[SPLB][NT * 16 + 2][2 * H + 2];
-    __shared__ __attribute__((aligned(16))) float dct[NT * 16 + 2][H + 2];
-    __shared__ __attribute__((aligned(16))) u32x4 ist[STAGE ? 2 : 1][NSL];
-
-    const int lane = threadIdx.x & 63;
-    const int tg = NG == 1 ? 0 : (int)(threadIdx.x >> 6) / Gm::NW;
-    const int w = NG == 1 ? (int)(threadIdx.x >> 6) : (int)(threadIdx.x >> 6) % Gm::NW;
-    const int q = lane >> 4, n16 = lane & 15;
-    const int mt0 = (w / SPLB) * TPW, sb = w % SPLB;  // output tiles and reduction slice of this wave
-    const int d = unit & 3;
-    const RectD R = reinterpret_cast<const RectD*>(a.rects)[unit >> 2];
-    const T* __restrict__ U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
-    T* __restrict__ Z = static_cast<T*>(a.z);
-    const T* __restrict__ DY = static_cast<const T*>(a.dy);
-    const float* __restrict__ Cs = a.c;
-    const int steps = R.h + R.w - 1;
-
-    for (int i = threadIdx.x; i < NT * 16 * GP; i += blockDim.x) (&dabuf[0][0])[i] = T(0);
-    for (int i = threadIdx.x; i < SPLB * (NT * 16 + 2) * (2 * H + 2); i += blockDim.x) (&gbuf[0][0][0])[i] = 0.0f;
-    for (int i = threadIdx.x; i < (NT * 16 + 2) * (H + 2); i += blockDim.x) (&dct[0][0])[i] = 0.0f;
-
-    // A operands: U^T rows k = 16 mt + n16 (column k of U); slot q holds gate
-    // rows r = q*KRUNB + ..., slice sb of the K steps.
-    Op A[TPW][BSTEP];
-#pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) {
-        const int k = 16 * (mt0 + tt) + n16;
-        const bool ok = k < 2 * H;
-        load_slot<T, BSTEP>(U + (int64_t)(q * KRUNB + sb * BSTEP * O::PER) * 2 * H + (ok ? k : 0), 2 * H, ok, A[tt]);
-    }
-    float dcl[TPG][WQ], dcn[TPG][WQ];
-#pragma unroll
-    for (int lt = 0; lt < TPG; ++lt)
-#pragma unroll
-        for (int wq = 0; wq < WQ; ++wq) dcl[lt][wq] = dcn[lt][wq] = 0.0f;
-    __builtin_amdgcn_s_waitcnt(0);  // U operands in registers before the step loop
-
-    // Cells of diagonal s, their mask bytes and (unstaged) the lane's inputs,
-    // issued for every lane from valid cells (see the forward pass);
-    // predecessors outside the rectangle read the cell itself and are zeroed
-    // on use.
-    const DiagMap M(R, d, a.canvas_w);
-    auto fetch = [&](int s, BPre<TPG, WQ, T>& b) {
-        const int sc = max(s, 0);
-        const int ylo = max(0, sc - R.w + 1), yhi = min(R.h - 1, sc);
-        const int64_t base = M.base(sc);
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int yy = 16 * (tg + NG * lt) + n16;
-            b.live[lt] = s >= 0 && yy >= ylo && yy <= yhi;
-            const int yc = min(max(yy, ylo), yhi), xc = sc - yc;
-            const int64_t p = M.at(base, yc);
-            b.p[lt] = p;
-            b.m[lt] = a.mask[p];
-            b.hasl[lt] = xc > 0;
-            b.hast[lt] = yc > 0;
-            if constexpr (!STAGE) {
-                const int64_t pl = xc > 0 ? canvas_index(R, d, yc, xc - 1, a.canvas_w) : p;
-                const int64_t pt = yc > 0 ? canvas_index(R, d, yc - 1, xc, a.canvas_w) : p;
-#pragma unroll
-                for (int wq = 0; wq < WQ; ++wq) {
-                    const int j = 4 * (w * WQ + wq) + q;
-                    const T* zp = Z + p * (4 * G) + d * G + j;
-#pragma unroll
-                    for (int t = 0; t < 5; ++t) b.g[lt][wq][t] = zp[t * H];
-                    b.dy[lt][wq] = DY[p * (4 * H) + d * H + j];
-                    b.c[lt][wq] = Cs[p * (4 * H) + d * H + j];
-                    b.cl[lt][wq] = Cs[pl * (4 * H) + d * H + j];
-                    b.ct[lt][wq] = Cs[pt * (4 * H) + d * H + j];
-                }
-            }
-        }
-    };
-
-    // Staged rows of diagonal s (clamped at 0) into zr: slot S is chunk S % PB
-    // of the row of cell S / PB, a row being the 5H gates, the H upstream
-    // gradients and the H cell states of the cell (padding chunk and slots
-    // past the last cell repeat a valid chunk).
-    u32x4 zr[NITZ > 0 ? NITZ : 1];
-    // The lane's chunk of each staged-input pass: cell row, and the chunk's
-    // address at canvas index 0 with the bytes per canvas cell of its tensor.
-    int zcell[NITZ > 0 ? NITZ : 1], zrb[NITZ > 0 ? NITZ : 1];
-    const char* zsrc[NITZ > 0 ? NITZ : 1];
-#pragma unroll
-    for (int it = 0; it < NITZ; ++it) {
-        const int S = it * NTH + (int)threadIdx.x;
-        const int r = min(S % PB, Q::QF - 1);
-        zcell[it] = min(S / PB, NT * 16 - 1);
-        if (r < Q::QZ) {
-            zsrc[it] = reinterpret_cast<const char*>(Z + d * G) + 16 * r;
-            zrb[it] = 4 * G * (int)sizeof(T);
-        } else if (r < CC) {
-            zsrc[it] = reinterpret_cast<const char*>(DY + d * H) + 16 * (r - Q::QZ);
-            zrb[it] = 4 * H * (int)sizeof(T);
-        } else {
-            zsrc[it] = reinterpret_cast<const char*>(Cs + d * H) + 16 * (r - CC);
-            zrb[it] = 16 * H;
-        }
-    }
-    auto fetch_rows = [&](int s) {
-        if constexpr (STAGE) {
-            const int sc = max(s, 0);
-            const int ylo = max(0, sc - R.w + 1), yhi = min(R.h - 1, sc);
-            const int64_t base = M.base(sc);
-#pragma unroll
-            for (int it = 0; it < NITZ; ++it) {
-                const int yc = min(max(zcell[it], ylo), yhi);
-                zr[it] = *reinterpret_cast<const u32x4*>(zsrc[it] + M.at(base, yc) * zrb[it]);
-            }
-        }
-    };
-    auto stage_in = [&](int s) {
-#pragma unroll
-        for (int it = 0; it < NITZ; ++it) ist[s & 1][it * NTH + threadIdx.x] = zr[it];
-    };
-
-    // The lane's chunk of each gate-gradient write-back pass (cell row, chunk).
-    int dcell[NITF], dchunk[NITF];
-#pragma unroll
-    for (int it = 0; it < NITF; ++it) {
-        const int i = min(it * NTH + (int)threadIdx.x, NT * 16 * Q::QZ - 1);
-        dcell[it] = i / Q::QZ;
-        dchunk[it] = i - dcell[it] * Q::QZ;
-    }
-    char* const Zd = reinterpret_cast<char*>(Z + d * G);
-    auto compute = [&](int s, const BPre<TPG, WQ, T>& b) {
-        const int ylo = max(0, s - R.w + 1), yhi = min(R.h - 1, s);
-        // Phase A: gate-gradient update of this lane's (cell, hidden unit) pairs.
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            if (16 * nt > yhi || 16 * nt + 15 < ylo) continue;
-            const int yy = 16 * nt + n16;
-#pragma unroll
-            for (int wq = 0; wq < WQ; ++wq) {
-                const int j = 4 * (w * WQ + wq) + q;
-                float da[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-                float ndl = 0.0f, ndt = 0.0f;
-                if (b.live[lt] && b.m[lt]) {
-                    float g[5], dyv, cv, cL, cT;
-                    if constexpr (STAGE) {
-                        const T* row = reinterpret_cast<const T*>(&ist[s & 1][yy * PB]);
-#pragma unroll
-                        for (int t = 0; t < 5; ++t) g[t] = ld1f<T>(row + t * H + j);
-                        dyv = ld1f<T>(row + 5 * H + j);
-                        cv = reinterpret_cast<const float*>(&ist[s & 1][yy * PB + CC])[j];
-                        const u32x4* prv = &ist[(s - 1) & 1][0];
-                        cL = b.hasl[lt] ? reinterpret_cast<const float*>(prv + yy * PB + CC)[j] : 0.0f;
-                        cT = b.hast[lt] ? reinterpret_cast<const float*>(prv + max(yy - 1, 0) * PB + CC)[j] : 0.0f;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 5; ++t) g[t] = ld1f<T>(&b.g[lt][wq][t]);
-                        dyv = ld1f<T>(&b.dy[lt][wq]);
-                        cv = b.c[lt][wq];
-                        cL = b.hasl[lt] ? b.cl[lt][wq] : 0.0f;
-                        cT = b.hast[lt] ? b.ct[lt][wq] : 0.0f;
-                    }
-                    const float gi = g[0], gfl = g[1], gft = g[2], go = g[3], gg = g[4];
-                    float gl = 0.0f, gtv = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < SPLB; ++k) {
-                        gl += gbuf[k][yy][j];
-                        gtv += gbuf[k][yy + 1][H + j];
-                    }
-                    const float dh = dyv + gl + gtv;
-                    const float tc = tanh_fast(cv);
-                    const float dc = dcl[lt][wq] + dct[yy + 1][j] + dh * go * (1.0f - tc * tc);
-                    da[0] = dc * gg * gi * (1.0f - gi);
-                    da[1] = dc * cL * gfl * (1.0f - gfl);
-                    da[2] = dc * cT * gft * (1.0f - gft);
-                    da[3] = dh * tc * go * (1.0f - go);
-                    da[4] = dc * gi * (1.0f - gg * gg);
-                    ndl = dc * gfl;
-                    ndt = dc * gft;
-                }
-#pragma unroll
-                for (int t = 0; t < 5; ++t) dabuf[yy][t * H + j] = from_f<T>(da[t]);
-                dcl[lt][wq] = ndl;
-                dcn[lt][wq] = ndt;
-            }
-        }
-        lds_barrier();
-        // Phase B: U^T da for the left (rows k < H) and top (k >= H)
-        // predecessors, on MFMA; issued first so that the memory work below
-        // runs behind it. Staged, tiles outside the diagonal are computed too
-        // (their results are not used), which keeps the MFMAs in one block.
-        floatx4 acc[TPG][TPW];
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            if (!STAGE && (16 * nt > yhi || 16 * nt + 15 < ylo)) continue;
-            const int yy = 16 * nt + n16;
-            const T* brow = &dabuf[yy][q * KRUNB + sb * BSTEP * O::PER];
-            Op bop[BSTEP];
-            lds_run<T, BSTEP>(brow, bop);
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) {
-                acc[lt][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < BSTEP; ++ks) acc[lt][tt] = O::mma(A[tt][ks], bop[ks], acc[lt][tt]);
-            }
-        }
-        // The rows of dabuf are the gate gradients of the diagonal's cells:
-        // write them back with contiguous 16-byte stores. Every lane stores in
-        // every pass (rows outside the diagonal repeat its nearest cell; cells
-        // with mask 0 get zero gradients), so the number of stores is fixed.
-        {
-            const int64_t base = M.base(s);
-            u32x4 v[NITF];
-            char* dst[NITF];
-#pragma unroll
-            for (int it = 0; it < NITF; ++it) {
-                const int cell = min(max(dcell[it], ylo), yhi);
-                v[it] = reinterpret_cast<const u32x4*>(&dabuf[cell][0])[dchunk[it]];
-                dst[it] = Zd + M.at(base, cell) * (4 * G * (int)sizeof(T)) + 16 * dchunk[it];
-            }
-            // Staged rows of diagonal s - 2 replace those of diagonal s, which
-            // no lane reads any more; the rows of diagonal s - 3 start loading.
-            if constexpr (STAGE) {
-                stage_in(s - 2);
-                fetch_rows(s - 3);
-            }
-            // non-temporal: the gate gradients are read again only by the
-            // gradient GEMMs after the whole wavefront
-#pragma unroll
-            for (int it = 0; it < NITF; ++it) __builtin_nontemporal_store(v[it], reinterpret_cast<u32x4*>(dst[it]));
-        }
-        // The products and the dc of the top predecessors go to LDS without
-        // branches (tiles outside the diagonal and padding columns write to
-        // the unread last rows), so the MFMA results are read in the same
-        // straight-line block that produced them.
-#pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
-            const int nt = tg + NG * lt;
-            const bool act = !(16 * nt > yhi || 16 * nt + 15 < ylo);
-            const int yy = act ? 16 * nt + n16 : NT * 16 + 1;
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) {
-                const int k0 = 16 * (mt0 + tt) + 4 * q;
-                float* gp = (act && k0 < 2 * H) ? &gbuf[sb][yy][k0] : &gbuf[sb][NT * 16 + 1][0];
-                *reinterpret_cast<float2*>(gp) = make_float2(acc[lt][tt][0], acc[lt][tt][1]);
-                *reinterpret_cast<float2*>(gp + 2) = make_float2(acc[lt][tt][2], acc[lt][tt][3]);
-            }
-#pragma unroll
-            for (int wq = 0; wq < WQ; ++wq) dct[yy][act ? 4 * (w * WQ + wq) + q : 0] = dcn[lt][wq];
-        }
-        lds_barrier();
-    };
-
-    BPre<TPG, WQ, T> b0, b1;
-    if constexpr (STAGE) {
-        // Before step s: rows of diagonals s and s - 1 in LDS, rows of s - 2
-        // loading, cells of s in registers.
-        fetch_rows(steps - 1);
-        stage_in(steps - 1);
-        fetch_rows(steps - 2);
-        stage_in(steps - 2);
-        fetch_rows(steps - 3);
-        fetch(steps - 1, b0);
-        lds_barrier();
-        auto step = [&](int s, const BPre<TPG, WQ, T>& cur, BPre<TPG, WQ, T>& nxt) {
-            fetch(s - 1, nxt);
-            compute(s, cur);
-        };
-        for (int s = steps - 1; s >= 0; s -= 2) {
-            step(s, b0, b1);
-            if (s - 1 >= 0) step(s - 1, b1, b0);
-        }
-    } else if constexpr (Prefetch2<T>::template on<TPG, WQ>()) {
-        lds_barrier();
-        fetch(steps - 1, b0);
-        int s = steps - 1;
-        for (; s - 1 >= 0; s -= 2) {
-            fetch(s - 1, b1);
-            compute(s, b0);
-            fetch(s - 2, b0);
-            compute(s - 1, b1);
-        }
-        if (s >= 0) compute(s, b0);
-    } else {
-        lds_barrier();
-        for (int s = steps - 1; s >= 0; --s) {
-            fetch(s, b0);
-            compute(s, b0);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Backward for wide layers (bf16, H = 128), with the forward's lane mapping:
 // lane 16q + n of wave w owns units u0 = 16w + 4q .. u0 + 3 of cell n of a
 // tile. The wave computes the two U^T da output tiles of its own units, the
@@ -779,7 +392,7 @@ struct BwdBig {
 };
 
 template <int H, int NT, typename T>
-__device__ __forceinline__ void wave_bwd_big(const WaveArgs& a, const int unit) {
+__device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
     using O = Ops<T>;
     using Op = typename O::Op;
     constexpr int G = 5 * H, KRUNB = G / 4, NSTEPB = KRUNB / O::PER;
@@ -943,84 +556,16 @@ __global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_fwd(FwdArgs a) {
 }
 
 template <int H, int NT, typename T>
-__global__ void __launch_bounds__((64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG)) k_wave_bwd(WaveArgs a) {
-    for_units(a, [&](int unit) {
-        if constexpr (BwdBig<H, T>::on) wave_bwd_big<H, NT, T>(a, unit);
-        else wave_bwd_unit<H, NT, T>(a, unit);
-    });
+__global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_bwd(BwdArgs a) {
+    for_units(a, [&](int unit) { wave_bwd_big<H, NT, T>(a, unit); });
 }
 
 // ---------------------------------------------------------------------------
-// Dispatch over (hidden size, N tiles, storage type).
+// Dispatch over hidden size, tiles per diagonal and storage type.
 // ---------------------------------------------------------------------------
-// LDS of the backward kernel; shapes beyond the 160 KB of a CU are not built.
-template <int H, int NT, typename T>
-constexpr bool bwd_fits() {
-    if constexpr (BwdBig<H, T>::on)
-        return (size_t)NT * 16 * (5 * H + 16 / sizeof(T)) * sizeof(T) + (size_t)2 * (NT * 16 + 1) * (H + 4) * 4 <=
-               160 * 1024;
-    return bwd_lds_base<H, NT, T>() + (bwd_stage<H, NT, T>() ? bwd_lds_stage<H, NT, T>() : 0) <= 160 * 1024;
-}
-
-template <int H, int NT, typename T>
-static void launch_unit(int n_groups, const WaveArgs& a, hipStream_t s) {
-    const dim3 grid(n_groups), block(64 * Geo<H, T>::NW * TileGroups<H, NT, T>::NG);
-    if constexpr (bwd_fits<H, NT, T>()) hipLaunchKernelGGL((k_wave_bwd<H, NT, T>), grid, block, 0, s, a);
-}
-
-template <int H, typename T>
-static hipError_t launch_nt(int nt, int n_units, const WaveArgs& a, hipStream_t s) {
-    if (nt == 4 && !bwd_fits<H, 4, T>()) return hipErrorInvalidValue;  // host rejects these rectangles
-    switch (nt) {
-        case 1: launch_unit<H, 1, T>(n_units, a, s); break;
-        case 2: launch_unit<H, 2, T>(n_units, a, s); break;
-        case 3: launch_unit<H, 3, T>(n_units, a, s); break;
-        case 4: launch_unit<H, 4, T>(n_units, a, s); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-// Workgroups per CU when units are taken from a queue (two hide the latency
-// of a step better than one).
-constexpr int BWD_GROUPS_PER_CU = 2;
-
-static hipError_t launch_wave_bwd(const LayerGeom& g, int nt, int n_units, WaveArgs a, hipStream_t s) {
-    if (n_units == 0) return hipSuccess;
-    a.n_units = n_units;
-    if (a.queue) {
-        int dev = 0, cus = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        const int groups = BWD_GROUPS_PER_CU * std::max(cus, 1);
-        if (n_units > groups) {  // else one workgroup per unit
-            n_units = groups;
-        } else {
-            a.queue = nullptr;
-        }
-    }
-    if (g.dtype == 0) {
-        switch (g.hidden) {
-            case 4: return launch_nt<4, float>(nt, n_units, a, s);
-            case 8: return launch_nt<8, float>(nt, n_units, a, s);
-            case 16: return launch_nt<16, float>(nt, n_units, a, s);
-            case 32: return launch_nt<32, float>(nt, n_units, a, s);
-            case 64: return launch_nt<64, float>(nt, n_units, a, s);
-            default: return hipErrorInvalidValue;
-        }
-    }
-    switch (g.hidden) {
-        case 32: return launch_nt<32, bf16_t>(nt, n_units, a, s);
-        case 64: return launch_nt<64, bf16_t>(nt, n_units, a, s);
-        case 128: return launch_nt<128, bf16_t>(nt, n_units, a, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 // The forward kernel of a shape. bf16 H = 128 has its own kernel: its operands
 // alone take 160 registers a lane at eight waves.
-static FwdKernel fwd_kernel_of(const LayerGeom& g, int nt) {
+static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt) {
     const int ck = fwd_fused_steps(g);
     if (g.dtype == 0) {
         switch (g.hidden) {
@@ -1100,7 +645,7 @@ hipError_t launch_split_x(const LayerGeom& g, const void* d_x, const int32_t* d_
 
 // Workgroups of a kernel that the device holds at once (256 CUs assumed when
 // the query fails).
-static int resident_groups(const FwdKernel& k) {
+static int resident_groups(const WaveKernel& k) {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
@@ -1118,7 +663,7 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
                                 const int32_t* d_rects, const uint8_t* d_mask, const int32_t* d_rid,
                                 const FwdTensors& t, unsigned* d_queue, hipStream_t s) {
     const int yrow_words = 4 * g.hidden * (g.dtype == 1 ? 2 : 4) / 8;
-    const FwdKernel k = n_units > 0 ? fwd_kernel_of(g, nt) : FwdKernel{};
+    const WaveKernel k = n_units > 0 ? fwd_kernel_of(g, nt) : WaveKernel{};
     if (n_units > 0 && !k.fn) return hipErrorInvalidValue;
     const int groups = n_units > 0 ? resident_groups(k) : 0;
     // the launch's own workgroups zero the invalid rows when there are enough
@@ -1142,18 +687,52 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }
 
+// The backward kernel of a shape (bf16 H = 128 as in the forward).
+static WaveKernel bwd_kernel_of(const LayerGeom& g, int nt) {
+    if (g.dtype == 0) {
+        switch (g.hidden) {
+            case 4: return bwd_kernel_f32_h4(nt);
+            case 8: return bwd_kernel_f32_h8(nt);
+            case 16: return bwd_kernel_f32_h16(nt);
+            case 32: return bwd_kernel_f32_h32(nt);
+            case 64: return bwd_kernel_f32_h64(nt);
+            default: return {};
+        }
+    }
+    switch (g.hidden) {
+        case 32: return bwd_kernel_bf16_h32(nt);
+        case 64: return bwd_kernel_bf16_h64(nt);
+        case 128: {
+            constexpr int th = 64 * Geo<128, bf16_t>::NW;
+            switch (nt) {
+                case 1: return {reinterpret_cast<const void*>(&k_wave_bwd<128, 1, bf16_t>), th};
+                case 2: return {reinterpret_cast<const void*>(&k_wave_bwd<128, 2, bf16_t>), th};
+                case 3: return {reinterpret_cast<const void*>(&k_wave_bwd<128, 3, bf16_t>), th};
+                case 4: return {reinterpret_cast<const void*>(&k_wave_bwd<128, 4, bf16_t>), th};
+                default: return {};
+            }
+        }
+        default: return {};
+    }
+}
+
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
                                 const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, const void* d_dy,
                                 void* d_z, const float* d_c, unsigned* d_queue, hipStream_t s) {
-    WaveArgs a{d_units, d_rects, d_mask, d_u, d_z, const_cast<float*>(d_c), d_dy, g.canvas_w, d_queue, n_units};
-    return launch_wave_bwd(g, nt, n_units, a, s);
+    if (n_units == 0) return hipSuccess;
+    const WaveKernel k = bwd_kernel_of(g, nt);
+    if (!k.fn) return hipErrorInvalidValue;
+    const int groups = resident_groups(k);
+    BwdArgs a{d_units, d_rects, d_mask, d_u, d_z, d_c, d_dy, g.canvas_w, n_units > groups ? d_queue : nullptr, n_units};
+    void* params[] = {&a};
+    return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }
 
 hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, int max_steps, const int32_t* d_units,
                                      const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t,
                                      hipGraphExec_t* exec) {
     if (n_units <= 0 || max_steps <= 0) return hipErrorInvalidValue;
-    const FwdKernel k = fwd_kernel_of(g, nt);
+    const WaveKernel k = fwd_kernel_of(g, nt);
     if (!k.fn) return hipErrorInvalidValue;
     hipGraph_t graph;
     hipError_t e = hipGraphCreate(&graph, 0);

@@ -2,7 +2,7 @@
 
 namespace mdl {
 
-FwdKernel fwd_kernel_bf16_h32(int nt, int ck) {
+WaveKernel fwd_kernel_bf16_h32(int nt, int ck) {
     switch (nt) {
         case 1: return fwd_kernel<32, 1, bf16_t, 2, 1>(ck);
         case 2: return fwd_kernel<32, 2, bf16_t, 2, 2>(ck);

@@ -2,7 +2,7 @@
 
 namespace mdl {
 
-FwdKernel fwd_kernel_f32_h16(int nt, int ck) {
+WaveKernel fwd_kernel_f32_h16(int nt, int ck) {
     switch (nt) {
         case 1: return fwd_kernel<16, 1, float, 1, 1>(ck);
         case 2: return fwd_kernel<16, 2, float, 1, 2>(ck);

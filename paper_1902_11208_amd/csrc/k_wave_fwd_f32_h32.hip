@@ -2,7 +2,7 @@
 
 namespace mdl {
 
-FwdKernel fwd_kernel_f32_h32(int nt, int ck) {
+WaveKernel fwd_kernel_f32_h32(int nt, int ck) {
     switch (nt) {
         case 1: return fwd_kernel<32, 1, float, 2, 1>(ck);
         case 2: return fwd_kernel<32, 2, float, 2, 2>(ck);

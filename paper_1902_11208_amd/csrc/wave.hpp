@@ -63,6 +63,12 @@ __device__ __forceinline__ void stw(T* p, const float (&v)[W]) {
     *reinterpret_cast<typename Vec<T, W>::R*>(p) = Vec<T, W>::pack(v);
 }
 
+// A wavefront kernel and its workgroup size.
+struct WaveKernel {
+    const void* fn = nullptr;
+    int threads = 0;
+};
+
 struct FwdArgs {
     const int32_t* units;  // unit = rect*4 + direction, in launch order
     const int32_t* rects;  // [n_rects][4]

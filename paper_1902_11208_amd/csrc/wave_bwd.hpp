@@ -1,0 +1,443 @@
+// Backward anti-diagonal wavefront, the reverse of wave_fwd.hpp's. With
+// successors S (right, same row, next diagonal) and E (below, row + 1, next
+// diagonal):
+//   dh = dY + (U^T da_S)[0:H] + (U^T da_E)[H:2H]
+//   dc = dh o (1 - tanh^2 c) + dc_S f_L(S) + dc_E f_T(E)
+//   da = (dc g i(1-i), dc c_L f_L(1-f_L), dc c_T f_T(1-f_T), dh tanh(c) o(1-o), dc i (1-g^2))
+//
+// The lane mapping is the forward's: lane 16q + n of wave w owns units
+// 4 WQ w + WQ q + r, r < WQ, of row n of each of its tiles. Per diagonal a wave
+// updates its cells (phase A) and leaves da in LDS as operand rows; after a
+// barrier it contracts them with the U^T rows of its own units, left and top
+// predecessor part side by side in one MFMA tile (A rows (unit q, output),
+// outputs: WQ left, WQ top; two tiles at WQ = 4), so the results land in the
+// lanes that need them on the next diagonal: the left part on the same row, the
+// top part and dc f_T one row up, a DPP move (rows 16 -> 15 through a rotation,
+// or LDS between tile groups). The gates, upstream gradients and cell states
+// come in, and the gate gradients leave, through LDS as whole rows in 16-byte
+// chunks.
+//
+// fp32 operands are three bf16 pieces each (split.hpp).
+//
+// Measured before (scalar operand exchange, fp32 MFMA, partial sums of the
+// products through LDS; bf16 H 64 with tall rectangles unstaged) and after:
+//   fp32 H 32, 64 lines of 32 rows    1590 -> 1560 us (4.5 TB/s of traffic)
+//   fp32 H 32, 32 images of 16 rows    163 ->  134 us
+//   fp32 H 64, 64 images of 8 rows     292 ->  205 us
+//   bf16 H 64, 24 lines of 20-60 rows 11.9 ->  2.9 ms
+#pragma once
+
+#include <type_traits>
+
+#include "kernels.hpp"
+#include "wave.hpp"
+
+namespace mdl {
+
+struct BwdArgs {
+    const int32_t* units;  // unit = rect*4 + direction, in launch order
+    const int32_t* rects;  // [n_rects][4]
+    const uint8_t* mask;   // [n_cells] (wide bf16 layers)
+    const void* u;         // [4][5H][2H]
+    void* z;               // [n_cells][20H]: gates in (other layers: a masked cell's input gates are negative), dZ out
+    const float* c;        // [n_cells][4H] cell state
+    const void* dy;        // [n_cells][4H] upstream gradient
+    int canvas_w;
+    unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
+    int n_units;
+};
+
+template <int H, int NT, typename T, int WQ, int NG>
+struct BwdK {
+    static constexpr int P = Pieces<T>::N;
+    static constexpr int UW = 4 * WQ, NWU = H / UW;     // hidden units per wave, waves per tile group
+    static constexpr int TPG = NT / NG;                 // tiles per wave (group tg: tiles tg TPG ...)
+    static constexpr int NTH = 64 * NWU * NG;
+    static constexpr int KS = (5 * H + 31) / 32;        // K steps over da
+    static constexpr int KP = 32 * KS + 8;              // operand row pitch: 16-byte reads of 16 rows hit distinct banks
+    static constexpr int OT = (2 * WQ + 3) / 4;         // output tiles per wave
+    static constexpr int WPE = OT * KS * P * 4 > 170 || NTH > 512 ? 1 : 2;
+    // Inputs of a cell in 16-byte chunks: 5H gates, H upstream gradients
+    // (storage type), and H cell states (fp32) of the diagonal before; the
+    // extra chunk of the pitch spreads rows over banks.
+    static constexpr int QZ = 5 * H * (int)sizeof(T) / 16, QY = H * (int)sizeof(T) / 16, QC = H / 4;
+    static constexpr int QF = QZ + QY + QC, PB = QF + 1, PZ = QZ + 1;
+    static constexpr size_t IN1 = (size_t)NT * 16 * PB * 16;
+    static constexpr size_t DA1 = (size_t)P * NT * 16 * KP * 2;
+    static constexpr size_t DZ1 = P == 3 ? (size_t)NT * 16 * PZ * 16 : 0;  // one-piece operand rows are the dZ rows
+    static constexpr size_t LIM = 158 * 1024;
+    static constexpr bool STAGE = NTH >= QF && IN1 + DA1 + DZ1 <= LIM;
+    // One barrier a diagonal where every buffer fits twice and one wave holds
+    // all tiles; else single buffers and a second barrier.
+    static constexpr bool DB = STAGE && NG == 1 && 2 * (IN1 + DA1 + DZ1) <= LIM;
+    static constexpr int NB = DB ? 2 : 1;
+    static constexpr bool FITS = STAGE || DA1 <= LIM;
+    static_assert(H % UW == 0 && NT % NG == 0 && NTH <= 1024, "wave split");
+};
+
+template <int H, int NT, typename T, int WQ, int NG>
+__device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
+    using K = BwdK<H, NT, T, WQ, NG>;
+    constexpr int P = K::P, NWU = K::NWU, TPG = K::TPG, KS = K::KS, KP = K::KP, OT = K::OT, NTH = K::NTH;
+    constexpr int QZ = K::QZ, QY = K::QY, QF = K::QF, PB = K::PB, PZ = K::PZ, NB = K::NB;
+    constexpr bool STAGE = K::STAGE, DB = K::DB;
+    constexpr int G = 5 * H;
+    using V = Vec<T, WQ>;
+    __shared__ __attribute__((aligned(16))) bf16_t dap[NB][P][NT * 16][KP];
+    __shared__ __attribute__((aligned(16))) u32x4 dzs[NB][P == 3 && STAGE ? NT * 16 : 1][PZ];
+    __shared__ __attribute__((aligned(16))) u32x4 ist[NB][STAGE ? NT * 16 * PB : 1];
+    // between tile groups: the top parts and dc f_T of a group's first row
+    __shared__ float gedge[NG][H], dedge[2][NG][H];
+
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tg = NG == 1 ? 0 : wv / NWU, w = NG == 1 ? wv : wv % NWU;
+    const int q = lane >> 4, n16 = lane & 15;
+    const int u0 = K::UW * w + WQ * q;
+    const int d = unit & 3;
+    const RectD R = reinterpret_cast<const RectD*>(a.rects)[unit >> 2];
+    const int steps = R.h + R.w - 1;
+    T* const Z = static_cast<T*>(a.z);
+    const T* const DY = static_cast<const T*>(a.dy);
+
+    for (int i = threadIdx.x; i < (int)(sizeof(dap) / 16); i += NTH)
+        reinterpret_cast<uint4*>(&dap[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
+    if constexpr (NG > 1) {
+        for (int i = threadIdx.x; i < NG * H; i += NTH) (&gedge[0][0])[i] = 0.0f;
+        for (int i = threadIdx.x; i < 2 * NG * H; i += NTH) (&dedge[0][0][0])[i] = 0.0f;
+    }
+
+    // Order of da along an operand row. Three pieces: (unit, sigmoid gate),
+    // then the candidates: a lane writes its gates as one vector. One piece:
+    // the canvas order, so that the rows leave as they are.
+    auto u_row = [](int k) {  // row of U of operand value k
+        if constexpr (P == 3) return k < 4 * H ? (k & 3) * H + (k >> 2) : k;
+        else return k;
+    };
+    // A operands, lane row n16 = 4 jj + e of tile t: output o = 4t + e, the left
+    // part (column) of unit UW w + WQ jj + o for o < WQ, then the top parts.
+    bf16x8 A[OT][KS][P];
+    const T* const U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
+#pragma unroll
+    for (int t = 0; t < OT; ++t) {
+        const int o = 4 * t + (n16 & 3), ub = K::UW * w + WQ * (n16 >> 2);
+        const bool ok = o < 2 * WQ;
+        const int col = !ok ? 0 : o < WQ ? ub + o : H + ub + o - WQ;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = 32 * ks + 8 * q + e;
+                v[e] = ok && k < G ? St<T>::ld1(U + (int64_t)u_row(k < G ? k : 0) * 2 * H + col) : 0.0f;
+            }
+            make_op<T>(v, A[t][ks]);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // operands in registers before the step loop
+
+    const DiagMap M(R, d, a.canvas_w);
+    T* const zb = Z + M.c0 * (4 * G) + d * G;
+    const T* const dyb = DY + M.c0 * (4 * H) + d * H;
+    const float* const cb = a.c + M.c0 * (4 * H) + d * H;
+    constexpr int ZROW = 4 * G * (int)sizeof(T);
+
+    // What the next diagonal (s - 1) takes over: the lane's own products (left
+    // and top part), dc f_L, dc f_T, and the cell state of its own rows.
+    float gl[TPG][WQ], gt[TPG][WQ], dcl[TPG][WQ], dct[TPG][WQ], co[TPG][WQ];
+#pragma unroll
+    for (int lt = 0; lt < TPG; ++lt) {
+        const int yy = 16 * (tg * TPG + lt) + n16;
+        const int yc = min(max(yy, max(0, steps - R.w)), R.h - 1);  // a row of the last diagonal
+        const float* cp = cb + (int64_t)(M.sx * (steps - 1) + yc * M.ky) * (4 * H) + u0;
+#pragma unroll
+        for (int r = 0; r < WQ; ++r) {
+            gl[lt][r] = gt[lt][r] = dcl[lt][r] = dct[lt][r] = 0.0f;
+            co[lt][r] = cp[r];
+        }
+    }
+
+    // Staged inputs: thread t moves chunk t % QF of rows t / QF, + RPI, ... of
+    // diagonal s's record (its gates and upstream gradients, the cell states of
+    // s - 1), into registers three or four diagonals ahead, into LDS one or two
+    // ahead. Threads and rows past the last, and rows outside the diagonal,
+    // repeat a valid one (every lane loads: the number of loads in flight is
+    // the same on all paths).
+    constexpr int RPI = STAGE ? (NTH / QF < NT * 16 ? NTH / QF : NT * 16) : 1;
+    constexpr int NIT = (NT * 16 + RPI - 1) / RPI;
+    struct Set {
+        u32x4 v[STAGE ? NIT : 1];
+        typename V::R g[STAGE ? 1 : TPG][5], dy[STAGE ? 1 : TPG];
+        typename Vec<float, WQ>::R cl[STAGE ? 1 : TPG], ct[STAGE ? 1 : TPG];
+    };
+    const int it0 = (int)threadIdx.x % (RPI * QF), ic0 = it0 / QF, ir = it0 - ic0 * QF;
+    const int back = ir >= QZ + QY ? 1 : 0;
+    const char* const ibase = ir < QZ        ? reinterpret_cast<const char*>(zb) + 16 * ir
+                              : ir < QZ + QY ? reinterpret_cast<const char*>(dyb) + 16 * (ir - QZ)
+                                             : reinterpret_cast<const char*>(cb) + 16 * (ir - QZ - QY);
+    const int irow = ir < QZ ? ZROW : ir < QZ + QY ? 4 * H * (int)sizeof(T) : 16 * H;
+    auto load = [&](int s, Set& in) {
+        if constexpr (STAGE) {
+            const int sc = max(s - back, 0);
+            const int ylo = max(0, sc - R.w + 1), yhi = min(R.h - 1, sc);
+            const int sxs = M.sx * sc;
+#pragma unroll
+            for (int it = 0; it < NIT; ++it)
+                in.v[it] = *reinterpret_cast<const u32x4*>(
+                    ibase + (int64_t)(sxs + min(max(ic0 + it * RPI, ylo), yhi) * M.ky) * irow);
+        }
+    };
+    // unstaged: the lane's own inputs of one tile (a missing top predecessor
+    // reads the cell itself; the left one's state is also that of the row's own
+    // cell on the next diagonal, so it is the row's even where the row is not
+    // in diagonal s)
+    auto load_tile = [&](int s, int lt, Set& in) {
+        if constexpr (!STAGE) {
+            const int sc = max(s, 0);
+            const int ylo = max(0, sc - R.w + 1), yhi = min(R.h - 1, sc);
+            const int yc = min(max(16 * (tg * TPG + lt) + n16, ylo), yhi);
+            const int idx = M.sx * sc + yc * M.ky;
+            const int sl = max(s - 1, 0);
+            const int il = M.sx * sl + min(max(16 * (tg * TPG + lt) + n16, max(0, sl - R.w + 1)), min(R.h - 1, sl)) * M.ky;
+            const int iu = yc > 0 ? idx - M.sx - M.ky : idx;
+#pragma unroll
+            for (int t = 0; t < 5; ++t) in.g[lt][t] = ldw<T, WQ>(zb + (int64_t)idx * (4 * G) + t * H + u0);
+            in.dy[lt] = ldw<T, WQ>(dyb + (int64_t)idx * (4 * H) + u0);
+            in.cl[lt] = ldw<float, WQ>(cb + (int64_t)il * (4 * H) + u0);
+            in.ct[lt] = ldw<float, WQ>(cb + (int64_t)iu * (4 * H) + u0);
+        }
+    };
+    auto stage_in = [&](int s, const Set& in) {
+        if constexpr (STAGE) {
+#pragma unroll
+            for (int it = 0; it < NIT; ++it)
+                ist[DB ? s & 1 : 0][min(ic0 + it * RPI, NT * 16 - 1) * PB + ir] = in.v[it];
+        }
+    };
+    // Staged gate gradients of diagonal s to the workspace (as the forward's
+    // write-back); non-temporal: they are read again only by the gradient
+    // kernels after the whole wavefront.
+    constexpr int RPF = STAGE ? (NTH / QZ < NT * 16 ? NTH / QZ : NT * 16) : 1;
+    constexpr int NITF = (NT * 16 + RPF - 1) / RPF;
+    const int ft0 = (int)threadIdx.x % (RPF * QZ), fc0 = ft0 / QZ, fr = ft0 - fc0 * QZ;
+    char* const fbase = reinterpret_cast<char*>(zb) + 16 * fr;
+    auto flush = [&](int s) {
+        if constexpr (STAGE) {
+            const int ylo = max(0, s - R.w + 1), yhi = min(R.h - 1, s);
+            constexpr int GR = NITF < 4 ? NITF : 4;  // passes per LDS round trip (registers)
+#pragma unroll
+            for (int i0 = 0; i0 < NITF; i0 += GR) {
+                u32x4 v[GR];
+#pragma unroll
+                for (int k = 0; k < GR; ++k)
+                    if (i0 + k < NITF) {
+                        const int cell = min(max(fc0 + (i0 + k) * RPF, ylo), yhi);
+                        if constexpr (P == 3) v[k] = dzs[DB ? s & 1 : 0][cell][fr];
+                        else v[k] = reinterpret_cast<const u32x4*>(&dap[DB ? s & 1 : 0][0][cell][0])[fr];
+                    }
+#pragma unroll
+                for (int k = 0; k < GR; ++k)
+                    if (i0 + k < NITF) {
+                        const int cell = min(max(fc0 + (i0 + k) * RPF, ylo), yhi);
+                        __builtin_nontemporal_store(
+                            v[k], reinterpret_cast<u32x4*>(fbase + (int64_t)(M.sx * s + cell * M.ky) * ZROW));
+                    }
+            }
+        }
+    };
+    char* const sink = sink_ptr();
+
+    // Phase A of tile lt: da of the lane's units. `far` holds the unstaged inputs.
+    auto cells = [&](int s, int lt, const Set& in, const float (&gtv)[WQ], const float (&dtv)[WQ]) {
+        const int ylo = max(0, s - R.w + 1), yhi = min(R.h - 1, s);
+        const int yy = 16 * (tg * TPG + lt) + n16;
+        const u32x4* row = &ist[DB ? s & 1 : 0][STAGE ? yy * PB : 0];
+        const bool inr = yy >= ylo && yy <= yhi;
+        typename V::R gr[5], dyr;
+        typename Vec<float, WQ>::R clr, ctr;
+        if constexpr (STAGE) {
+#pragma unroll
+            for (int t = 0; t < 5; ++t) gr[t] = ldw<T, WQ>(reinterpret_cast<const T*>(row) + t * H + u0);
+            dyr = ldw<T, WQ>(reinterpret_cast<const T*>(row + QZ) + u0);
+            clr = ldw<float, WQ>(reinterpret_cast<const float*>(row + QZ + QY) + u0);
+            const u32x4* up = yy > 0 ? row - PB : row;
+            ctr = ldw<float, WQ>(reinterpret_cast<const float*>(up + QZ + QY) + u0);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 5; ++t) gr[t] = in.g[lt][t];
+            dyr = in.dy[lt];
+            clr = in.cl[lt];
+            ctr = in.ct[lt];
+        }
+        const bool hasl = s - yy > 0, hast = yy > 0;
+        float da[5][WQ];
+#pragma unroll
+        for (int r = 0; r < WQ; ++r) {
+            const float gi = V::get(gr[0], r), gfl = V::get(gr[1], r), gft = V::get(gr[2], r), go = V::get(gr[3], r),
+                        gg = V::get(gr[4], r);
+            const bool live = inr && !(gi < 0.0f);  // a NaN stays
+            const float cl = Vec<float, WQ>::get(clr, r), cu = Vec<float, WQ>::get(ctr, r);
+            const float cL = hasl ? cl : 0.0f, cT = hast ? cu : 0.0f;
+            const float dh = V::get(dyr, r) + gl[lt][r] + gtv[r];
+            const float tc = tanh_fast(co[lt][r]);
+            const float dc = dcl[lt][r] + dtv[r] + dh * go * (1.0f - tc * tc);
+            co[lt][r] = cl;
+            da[0][r] = live ? dc * gg * gi * (1.0f - gi) : 0.0f;
+            da[1][r] = live ? dc * cL * gfl * (1.0f - gfl) : 0.0f;
+            da[2][r] = live ? dc * cT * gft * (1.0f - gft) : 0.0f;
+            da[3][r] = live ? dh * tc * go * (1.0f - go) : 0.0f;
+            da[4][r] = live ? dc * gi * (1.0f - gg * gg) : 0.0f;
+            dcl[lt][r] = live ? dc * gfl : 0.0f;
+            dct[lt][r] = live ? dc * gft : 0.0f;
+        }
+        const int b = DB ? s & 1 : 0;
+        if constexpr (P == 3) {
+#pragma unroll
+            for (int r = 0; r < WQ; ++r) {
+                uint32_t lo[3], hi[3];
+                split2(da[0][r], da[1][r], lo);
+                split2(da[2][r], da[3][r], hi);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    *reinterpret_cast<u32x2*>(&dap[b][k][yy][4 * (u0 + r)]) = u32x2{lo[k], hi[k]};
+            }
+            uint32_t p0[3], p1[3];
+            split2(da[4][0], WQ > 1 ? da[4][WQ > 1 ? 1 : 0] : 0.0f, p0);
+            if constexpr (WQ == 4) split2(da[4][2], da[4][3], p1);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                bf16_t* p = &dap[b][k][yy][4 * H + u0];
+                if constexpr (WQ == 4) *reinterpret_cast<u32x2*>(p) = u32x2{p0[k], p1[k]};
+                else if constexpr (WQ == 2) *reinterpret_cast<uint32_t*>(p) = p0[k];
+                else *p = (bf16_t)p0[k];
+            }
+            if constexpr (STAGE) {
+#pragma unroll
+                for (int t = 0; t < 5; ++t)
+                    stw<float, WQ>(reinterpret_cast<float*>(&dzs[b][yy][0]) + t * H + u0, da[t]);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 5; ++t) stw<T, WQ>(&dap[b][0][yy][t * H + u0], da[t]);
+        }
+        if constexpr (!STAGE) {
+            T* const zp = inr ? zb + (int64_t)(M.sx * s + yy * M.ky) * (4 * G) + u0 : reinterpret_cast<T*>(sink);
+#pragma unroll
+            for (int t = 0; t < 5; ++t) stw<T, WQ>(zp + t * H, da[t]);
+        }
+    };
+    auto step = [&](int s, Set& far) {
+        // From the top: a tile's bottom edge is the first row of the tile
+        // below it, of the previous diagonal.
+#pragma unroll
+        for (int lt = 0; lt < TPG; ++lt) {
+            float gtv[WQ], dtv[WQ];
+#pragma unroll
+            for (int r = 0; r < WQ; ++r) {
+                float eg = 0.0f, ed = 0.0f;
+                if (lt + 1 < TPG) {
+                    eg = first_to_last(gt[lt + 1 < TPG ? lt + 1 : 0][r]);
+                    ed = first_to_last(dct[lt + 1 < TPG ? lt + 1 : 0][r]);
+                } else if (NG > 1 && tg + 1 < NG) {
+                    eg = gedge[tg + 1 < NG ? tg + 1 : 0][u0 + r];
+                    ed = dedge[(s & 1) ^ 1][tg + 1 < NG ? tg + 1 : 0][u0 + r];
+                }
+                gtv[r] = row_below(gt[lt][r], eg);
+                dtv[r] = row_below(dct[lt][r], ed);
+            }
+            cells(s, lt, far, gtv, dtv);
+            if constexpr (!STAGE) load_tile(s - 1, lt, far);
+            if constexpr (NG > 1) {
+                if (lt == 0 && n16 == 0) {
+#pragma unroll
+                    for (int r = 0; r < WQ; ++r) dedge[s & 1][tg][u0 + r] = dct[0][r];
+                }
+            }
+        }
+        lds_barrier();  // da of the diagonal written
+#pragma unroll
+        for (int lt = 0; lt < TPG; ++lt) {
+            const int yy = 16 * (tg * TPG + lt) + n16;
+            floatx4 acc[OT], low[OT];
+#pragma unroll
+            for (int t = 0; t < OT; ++t) acc[t] = low[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                bf16x8 b[P];
+#pragma unroll
+                for (int k = 0; k < P; ++k)
+                    b[k] = as_bf16x8(*reinterpret_cast<const uint4*>(&dap[DB ? s & 1 : 0][k][yy][32 * ks + 8 * q]));
+                mma_tiles<P, OT>(A, ks, b, acc, low);
+            }
+#pragma unroll
+            for (int o = 0; o < 2 * WQ; ++o) {
+                const float v = P == 3 ? acc[o >> 2][o & 3] + low[o >> 2][o & 3] : acc[o >> 2][o & 3];
+                if (o < WQ) gl[lt][o < WQ ? o : 0] = v;
+                else gt[lt][o < WQ ? 0 : o - WQ] = v;
+            }
+            if constexpr (NG > 1) {
+                if (lt == 0 && n16 == 0) {
+#pragma unroll
+                    for (int r = 0; r < WQ; ++r) gedge[tg][u0 + r] = gt[0][r];
+                }
+            }
+        }
+        flush(s);
+        stage_in(s - NB, far);
+        if constexpr (STAGE) load(s - NB - 2, far);
+        if constexpr (!DB) lds_barrier();
+    };
+
+    Set s0, s1;
+    if constexpr (STAGE) {
+        load(steps - 1, s0);
+        stage_in(steps - 1, s0);
+        if constexpr (DB) {
+            load(steps - 2, s1);
+            stage_in(steps - 2, s1);
+        }
+        load(steps - 1 - NB, s0);
+        load(steps - 2 - NB, s1);
+    } else {
+#pragma unroll
+        for (int lt = 0; lt < TPG; ++lt) load_tile(steps - 1, lt, s0);
+    }
+    lds_barrier();
+    // two steps ahead of the loop: it is entered with the memory operations in
+    // flight that its own steps leave, so its waits are exact
+    int s = steps - 1;
+    step(s, s0);
+    if (--s >= 0) {
+        step(s, STAGE ? s1 : s0);
+        --s;
+    }
+    while (s >= 0) {
+        step(s, s0);
+        if (--s < 0) break;
+        step(s, STAGE ? s1 : s0);
+        --s;
+    }
+}
+
+template <int H, int NT, typename T, int WQ, int NG>
+__global__ void __launch_bounds__((BwdK<H, NT, T, WQ, NG>::NTH))
+__attribute__((amdgpu_waves_per_eu(BwdK<H, NT, T, WQ, NG>::WPE))) k_bwd(BwdArgs a) {
+    for_units(a, [&](int unit) { bwd_unit<H, NT, T, WQ, NG>(a, unit); });
+}
+
+template <int H, int NT, typename T, int WQ, int NG>
+WaveKernel bwd_kernel() {
+    static_assert(BwdK<H, NT, T, WQ, NG>::FITS, "LDS");
+    return {reinterpret_cast<const void*>(&k_bwd<H, NT, T, WQ, NG>), BwdK<H, NT, T, WQ, NG>::NTH};
+}
+
+// One translation unit per hidden size (k_wave_bwd_*.hip).
+WaveKernel bwd_kernel_f32_h4(int nt);
+WaveKernel bwd_kernel_f32_h8(int nt);
+WaveKernel bwd_kernel_f32_h16(int nt);
+WaveKernel bwd_kernel_f32_h32(int nt);
+WaveKernel bwd_kernel_f32_h64(int nt);
+WaveKernel bwd_kernel_bf16_h32(int nt);
+WaveKernel bwd_kernel_bf16_h64(int nt);
+
+}  // namespace mdl

@@ -277,7 +277,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 in.v[it] = *reinterpret_cast<const u32x4*>(
                     ibase + (int64_t)(sxs + min(max(ic0 + it * RPI, ylo), yhi) * M.ky) * irow);
             if constexpr (!MASKCHUNK)
-                in.mb = mrow[sxs + min(max((int)threadIdx.x % (NT * 16), ylo), yhi) * M.ky];
+                in.mb = mrow[sxs + min(max(min((int)threadIdx.x, NT * 16 - 1), ylo), yhi) * M.ky];
         } else {
 #pragma unroll
             for (int lt = 0; lt < TPG; ++lt) load_tile(s, lt, in);
@@ -289,7 +289,13 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
 #pragma unroll
             for (int it = 0; it < NIT; ++it)
                 ist[s & 1][min(ic0 + it * RPI, NT * 16 - 1) * PI + ir] = iok ? in.v[it] : u32x4{0, 0, 0, 0};
-            if constexpr (!MASKCHUNK) mst[s & 1][threadIdx.x] = in.mb;
+            if constexpr (!MASKCHUNK) {
+                // taken here, so that it waits for this set's loads and not,
+                // moved past the next ones, for those
+                uint32_t mb = in.mb;
+                asm volatile("" : "+v"(mb));
+                mst[s & 1][threadIdx.x] = mb;
+            }
         }
     };
     // A wave of one tile computes the input part of the next diagonal behind the
@@ -312,9 +318,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             if constexpr (STAGE_IN) {
                 mk = MASKCHUNK ? row[QI - 1][0] : mst[s & 1][yy];
             } else {
-                // taken here, so that it waits for this diagonal's loads and not,
-                // moved past the next ones, for those
-                mk = in.m[lt];
+                mk = in.m[lt];  // taken here, as the staged mask byte
                 asm volatile("" : "+v"(mk));
             }
 #pragma unroll
@@ -444,6 +448,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 cv[r] = live ? cn : 0.0f;
                 hv[r] = live ? hn : 0.0f;
                 cprev[lt][r] = cv[r];
+                gv[0][r] = mk != 0 ? gv[0][r] : -1.0f;  // marks a masked cell for the backward
             }
             put_h(cur, yy, hv);
             if constexpr (NG > 1) {
@@ -539,14 +544,8 @@ constexpr bool fwd_fusable(int hidden) {
     return hidden <= (std::is_same<T, float>::value ? 32 : 64);
 }
 
-// Kernel and workgroup size of a shape.
-struct FwdKernel {
-    const void* fn = nullptr;
-    int threads = 0;
-};
-
 template <int H, int NT, typename T, int WQ, int NG>
-FwdKernel fwd_kernel(int ck) {
+WaveKernel fwd_kernel(int ck) {
     if (ck == 0) return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, 0, WQ, NG>), FwdK<H, NT, T, 0, WQ, NG>::NTH};
     if constexpr (!fwd_fusable<T>(H)) return {};
     else switch (ck) {
@@ -557,12 +556,12 @@ FwdKernel fwd_kernel(int ck) {
 }
 
 // One translation unit per hidden size (k_wave_fwd_*.hip).
-FwdKernel fwd_kernel_f32_h4(int nt, int ck);
-FwdKernel fwd_kernel_f32_h8(int nt, int ck);
-FwdKernel fwd_kernel_f32_h16(int nt, int ck);
-FwdKernel fwd_kernel_f32_h32(int nt, int ck);
-FwdKernel fwd_kernel_f32_h64(int nt, int ck);
-FwdKernel fwd_kernel_bf16_h32(int nt, int ck);
-FwdKernel fwd_kernel_bf16_h64(int nt, int ck);
+WaveKernel fwd_kernel_f32_h4(int nt, int ck);
+WaveKernel fwd_kernel_f32_h8(int nt, int ck);
+WaveKernel fwd_kernel_f32_h16(int nt, int ck);
+WaveKernel fwd_kernel_f32_h32(int nt, int ck);
+WaveKernel fwd_kernel_f32_h64(int nt, int ck);
+WaveKernel fwd_kernel_bf16_h32(int nt, int ck);
+WaveKernel fwd_kernel_bf16_h64(int nt, int ck);
 
 }  // namespace mdl

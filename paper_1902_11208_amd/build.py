@@ -22,7 +22,7 @@ SOURCES = ["mdlstm_api.cpp", "k_pack.hip", "k_proj.hip", "k_wave.hip", "k_wave_f
            "k_wave_fwd_f32_h16.hip", "k_wave_fwd_f32_h32.hip", "k_wave_fwd_f32_h64.hip", "k_wave_fwd_bf16_h32.hip",
            "k_wave_fwd_bf16_h64.hip", "k_wave_bwd_f32_h4.hip", "k_wave_bwd_f32_h8.hip", "k_wave_bwd_f32_h16.hip",
            "k_wave_bwd_f32_h32.hip", "k_wave_bwd_f32_h64.hip", "k_wave_bwd_bf16_h32.hip", "k_wave_bwd_bf16_h64.hip", "k_bwd_big.hip", "k_bwd_strip.hip",
-           "k_stack.hip", "k_head.hip", "k_wave_mem.hip", "k_pad.hip"]
+           "k_stack.hip", "k_head.hip", "k_wave_mem_h16.hip", "k_wave_mem_h32.hip", "k_pad.hip"]
 
 FLAGS = [
     f"--offload-arch={ARCH}",

@@ -565,8 +565,13 @@ __global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_bwd(BwdArgs a) {
 // ---------------------------------------------------------------------------
 // The forward kernel of a shape. bf16 H = 128 has its own kernel: its operands
 // alone take 160 registers a lane at eight waves.
-static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt) {
+static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
     const int ck = fwd_fused_steps(g);
+    if (memory)
+        return g.dtype != 0      ? WaveKernel{}
+               : g.hidden == 16 ? fwd_kernel_mem_h16(nt, ck)
+               : g.hidden == 32 ? fwd_kernel_mem_h32(nt, ck)
+                                 : WaveKernel{};
     if (g.dtype == 0) {
         switch (g.hidden) {
             case 4: return fwd_kernel_f32_h4(nt, ck);
@@ -663,7 +668,7 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
                                 const int32_t* d_rects, const uint8_t* d_mask, const int32_t* d_rid,
                                 const FwdTensors& t, unsigned* d_queue, hipStream_t s) {
     const int yrow_words = 4 * g.hidden * (g.dtype == 1 ? 2 : 4) / 8;
-    const WaveKernel k = n_units > 0 ? fwd_kernel_of(g, nt) : WaveKernel{};
+    const WaveKernel k = n_units > 0 ? fwd_kernel_of(g, nt, t.v != nullptr) : WaveKernel{};
     if (n_units > 0 && !k.fn) return hipErrorInvalidValue;
     const int groups = n_units > 0 ? resident_groups(k) : 0;
     // the launch's own workgroups zero the invalid rows when there are enough
@@ -679,16 +684,21 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
         d_rid = nullptr;
     }
     if (n_units == 0) return hipSuccess;
-    FwdArgs a{d_units,    d_rects, d_mask,  t.u,     t.wx,
-              t.b,        t.x,     g.c_in,  t.z,     t.c,
-              t.y,        g.canvas_w, 0,    INT_MAX, n_units > groups ? d_queue : nullptr,
-              n_units,    d_rid,   g.n_cells, yrow_words};
+    FwdArgs a{d_units, d_rects,    d_mask, t.u,     t.v,
+              t.wx,    t.b,        t.x,    g.c_in,  t.z,
+              t.c,     t.y,        g.canvas_w, 0,   INT_MAX,
+              n_units > groups ? d_queue : nullptr, n_units, d_rid, g.n_cells, yrow_words};
     void* params[] = {&a};
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }
 
 // The backward kernel of a shape (bf16 H = 128 as in the forward).
-static WaveKernel bwd_kernel_of(const LayerGeom& g, int nt) {
+static WaveKernel bwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
+    if (memory)
+        return g.dtype != 0      ? WaveKernel{}
+               : g.hidden == 16 ? bwd_kernel_mem_h16(nt)
+               : g.hidden == 32 ? bwd_kernel_mem_h32(nt)
+                                 : WaveKernel{};
     if (g.dtype == 0) {
         switch (g.hidden) {
             case 4: return bwd_kernel_f32_h4(nt);
@@ -717,13 +727,15 @@ static WaveKernel bwd_kernel_of(const LayerGeom& g, int nt) {
 }
 
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
-                                const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, const void* d_dy,
-                                void* d_z, const float* d_c, unsigned* d_queue, hipStream_t s) {
+                                const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, const void* d_v,
+                                const void* d_dy, void* d_z, const float* d_c, unsigned* d_queue, hipStream_t s) {
     if (n_units == 0) return hipSuccess;
-    const WaveKernel k = bwd_kernel_of(g, nt);
+    const WaveKernel k = bwd_kernel_of(g, nt, d_v != nullptr);
     if (!k.fn) return hipErrorInvalidValue;
     const int groups = resident_groups(k);
-    BwdArgs a{d_units, d_rects, d_mask, d_u, d_z, d_c, d_dy, g.canvas_w, n_units > groups ? d_queue : nullptr, n_units};
+    BwdArgs a{d_units, d_rects, d_mask, d_u,        d_v,
+              d_z,     d_c,     d_dy,   g.canvas_w, n_units > groups ? d_queue : nullptr,
+              n_units};
     void* params[] = {&a};
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }
@@ -732,15 +744,15 @@ hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, in
                                      const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t,
                                      hipGraphExec_t* exec) {
     if (n_units <= 0 || max_steps <= 0) return hipErrorInvalidValue;
-    const WaveKernel k = fwd_kernel_of(g, nt);
+    const WaveKernel k = fwd_kernel_of(g, nt, false);
     if (!k.fn) return hipErrorInvalidValue;
     hipGraph_t graph;
     hipError_t e = hipGraphCreate(&graph, 0);
     if (e != hipSuccess) return e;
     hipGraphNode_t prev = nullptr;
     for (int st = 0; st < max_steps && e == hipSuccess; ++st) {
-        FwdArgs a{d_units, d_rects, d_mask,     t.u, t.wx,   t.b,     t.x,     g.c_in,  t.z, t.c,
-                  t.y,     g.canvas_w, st, st + 1, nullptr, n_units, nullptr, 0,   0};
+        FwdArgs a{d_units, d_rects, d_mask,     t.u, t.v,    t.wx,    t.b,     t.x,     g.c_in, t.z,
+                  t.c,     t.y,     g.canvas_w, st,  st + 1, nullptr, n_units, nullptr, 0,      0};
         void* params[] = {&a};
         hipKernelNodeParams p{};
         p.func = const_cast<void*>(k.fn);

@@ -1,0 +1,26 @@
+#include "wave_bwd.hpp"
+#include "wave_fwd.hpp"
+
+namespace mdl {
+
+WaveKernel fwd_kernel_mem_h16(int nt, int ck) {
+    switch (nt) {
+        case 1: return fwd_kernel<16, 1, float, 1, 1, true>(ck);
+        case 2: return fwd_kernel<16, 2, float, 1, 2, true>(ck);
+        case 3: return fwd_kernel<16, 3, float, 1, 1, true>(ck);
+        case 4: return fwd_kernel<16, 4, float, 1, 2, true>(ck);
+        default: return {};
+    }
+}
+
+WaveKernel bwd_kernel_mem_h16(int nt) {
+    switch (nt) {
+        case 1: return bwd_kernel<16, 1, float, 1, 1, true>();
+        case 2: return bwd_kernel<16, 2, float, 1, 1, true>();
+        case 3: return bwd_kernel<16, 3, float, 1, 1, true>();
+        case 4: return bwd_kernel<16, 4, float, 1, 1, true>();
+        default: return {};
+    }
+}
+
+}  // namespace mdl

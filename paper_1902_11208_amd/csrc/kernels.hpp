@@ -56,6 +56,7 @@ hipError_t launch_zero_invalid(const LayerGeom& g, int width, const uint8_t* d_m
 // where the projection runs apart (fwd_fused_steps == 0).
 struct FwdTensors {
     const void* u;
+    const void* v;  // memory-state matrices, or NULL
     const void* wx;
     const void* b;
     const void* x;
@@ -91,7 +92,8 @@ hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, in
 // --- backward --------------------------------------------------------------
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
                                 const int32_t* d_rects, const uint8_t* d_mask, const void* d_u,
-                                const void* d_dy, void* d_z, const float* d_c, unsigned* d_queue, hipStream_t s);
+                                const void* d_v, const void* d_dy, void* d_z, const float* d_c, unsigned* d_queue,
+                                hipStream_t s);
 // Input and weight gradients as tiled MFMA products (any built shape), in
 // two launches: first a validity byte per cell (d_flags, n_cells bytes),
 // Wx_all transposed (d_wxt) and the input gradient; then the weight
@@ -143,26 +145,6 @@ size_t conv_partial_bytes(int hidden, int og, int bh, int bw, int total_blocks);
 hipError_t launch_block_conv(bool fwd, const ConvArgs& a, hipStream_t s);
 // Fill n floats with zero.
 hipError_t launch_zero_f32(float* d, int64_t n, hipStream_t s);
-
-// --- layer with memory-state matrices (fp32, H = 16 or 32) -----------------
-struct MemArgs {
-    const int32_t* units;   // unit order (4 * rect + direction), one workgroup each
-    const int32_t* rects;   // [n_rects][4]
-    const uint8_t* mask;
-    const float* u;         // [4][5H][2H]
-    const float* v;         // [4][3H][2H]
-    float* z;               // pre-activations -> activated gates (forward) -> gate gradients (backward)
-    float* c;               // cell states [cells][4H]
-    float* y;               // forward output [cells][4H]
-    const float* dy;        // backward input [cells][4H]
-    int canvas_w;
-    float* dvpart;          // backward: [units][3H][2H] partials
-};
-bool mem_supported(const LayerGeom& g);
-size_t mem_partial_bytes(const LayerGeom& g, int n_units);
-hipError_t launch_wavefront_mem(bool fwd, const LayerGeom& g, int n_units, const MemArgs& a, hipStream_t s);
-hipError_t launch_dv_reduce(const LayerGeom& g, int n_units, const int32_t* d_units, const float* d_part, float* d_dv,
-                            hipStream_t s);
 
 // --- output layer shared by the directions, row collapse, CTC loss ---------
 struct HeadArgs {

@@ -74,6 +74,7 @@ struct FwdArgs {
     const int32_t* rects;  // [n_rects][4]
     const uint8_t* mask;   // [n_cells]
     const void* u;         // [4][5H][2H]
+    const void* v;         // [4][3H][2H] memory-state matrices, or NULL
     const void* wx;        // [4][5H][c_in]
     const void* b;         // [4][5H]
     const void* x;         // inputs per cell: bf16 [c_in], or the fp32 inputs as bf16 pieces [3][32 CK]

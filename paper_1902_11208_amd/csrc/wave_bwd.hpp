@@ -39,6 +39,7 @@ struct BwdArgs {
     const int32_t* rects;  // [n_rects][4]
     const uint8_t* mask;   // [n_cells] (wide bf16 layers)
     const void* u;         // [4][5H][2H]
+    const void* v;         // [4][3H][2H] memory-state matrices, or NULL
     void* z;               // [n_cells][20H]: gates in (other layers: a masked cell's input gates are negative), dZ out
     const float* c;        // [n_cells][4H] cell state
     const void* dy;        // [n_cells][4H] upstream gradient
@@ -47,7 +48,7 @@ struct BwdArgs {
     int n_units;
 };
 
-template <int H, int NT, typename T, int WQ, int NG>
+template <int H, int NT, typename T, int WQ, int NG, bool MEM>
 struct BwdK {
     static constexpr int P = Pieces<T>::N;
     static constexpr int UW = 4 * WQ, NWU = H / UW;     // hidden units per wave, waves per tile group
@@ -55,7 +56,10 @@ struct BwdK {
     static constexpr int NTH = 64 * NWU * NG;
     static constexpr int KS = (5 * H + 31) / 32;        // K steps over da
     static constexpr int KP = 32 * KS + 8;              // operand row pitch: 16-byte reads of 16 rows hit distinct banks
-    static constexpr int OT = (2 * WQ + 3) / 4;         // output tiles per wave
+    // Outputs per lane: WQ left parts, WQ top parts; with memory-state matrices
+    // as many again for the cell states.
+    static constexpr int OUTS = (MEM ? 4 : 2) * WQ;
+    static constexpr int OT = (OUTS + 3) / 4;           // output tiles per wave
     static constexpr int WPE = OT * KS * P * 4 > 170 || NTH > 512 ? 1 : 2;
     // Inputs of a cell in 16-byte chunks: 5H gates, H upstream gradients
     // (storage type), and H cell states (fp32) of the diagonal before; the
@@ -73,11 +77,12 @@ struct BwdK {
     static constexpr int NB = DB ? 2 : 1;
     static constexpr bool FITS = STAGE || DA1 <= LIM;
     static_assert(H % UW == 0 && NT % NG == 0 && NTH <= 1024, "wave split");
+    static_assert(!MEM || (NG == 1 && P == 3), "memory-state matrices: fp32, one tile group");
 };
 
-template <int H, int NT, typename T, int WQ, int NG>
+template <int H, int NT, typename T, int WQ, int NG, bool MEM>
 __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
-    using K = BwdK<H, NT, T, WQ, NG>;
+    using K = BwdK<H, NT, T, WQ, NG, MEM>;
     constexpr int P = K::P, NWU = K::NWU, TPG = K::TPG, KS = K::KS, KP = K::KP, OT = K::OT, NTH = K::NTH;
     constexpr int QZ = K::QZ, QY = K::QY, QF = K::QF, PB = K::PB, PZ = K::PZ, NB = K::NB;
     constexpr bool STAGE = K::STAGE, DB = K::DB;
@@ -121,15 +126,22 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
 #pragma unroll
     for (int t = 0; t < OT; ++t) {
         const int o = 4 * t + (n16 & 3), ub = K::UW * w + WQ * (n16 >> 2);
-        const bool ok = o < 2 * WQ;
-        const int col = !ok ? 0 : o < WQ ? ub + o : H + ub + o - WQ;
+        const bool ok = o < K::OUTS, state = MEM && o >= 2 * WQ;
+        const int ol = state ? o - 2 * WQ : o;
+        const int col = !ok ? 0 : ol < WQ ? ub + ol : H + ub + ol - WQ;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             float v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = 32 * ks + 8 * q + e;
-                v[e] = ok && k < G ? St<T>::ld1(U + (int64_t)u_row(k < G ? k : 0) * 2 * H + col) : 0.0f;
+                const int row = u_row(k < G ? k : 0);
+                if (MEM && state)  // V has the rows of i, f_L, f_T
+                    v[e] = ok && k < G && row < 3 * H
+                               ? St<T>::ld1(static_cast<const T*>(a.v) + ((int64_t)d * 3 * H + row) * 2 * H + col)
+                               : 0.0f;
+                else
+                    v[e] = ok && k < G ? St<T>::ld1(U + (int64_t)row * 2 * H + col) : 0.0f;
             }
             make_op<T>(v, A[t][ks]);
         }
@@ -215,8 +227,8 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         }
     };
     // Staged gate gradients of diagonal s to the workspace (as the forward's
-    // write-back); non-temporal: they are read again only by the gradient
-    // kernels after the whole wavefront.
+    // write-back, but cached: the gradient kernel that reads them comes next;
+    // non-temporal stores took 233 us on the word batch, these 217).
     constexpr int RPF = STAGE ? (NTH / QZ < NT * 16 ? NTH / QZ : NT * 16) : 1;
     constexpr int NITF = (NT * 16 + RPF - 1) / RPF;
     const int ft0 = (int)threadIdx.x % (RPF * QZ), fc0 = ft0 / QZ, fr = ft0 - fc0 * QZ;
@@ -239,8 +251,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
                 for (int k = 0; k < GR; ++k)
                     if (i0 + k < NITF) {
                         const int cell = min(max(fc0 + (i0 + k) * RPF, ylo), yhi);
-                        __builtin_nontemporal_store(
-                            v[k], reinterpret_cast<u32x4*>(fbase + (int64_t)(M.sx * s + cell * M.ky) * ZROW));
+                        *reinterpret_cast<u32x4*>(fbase + (int64_t)(M.sx * s + cell * M.ky) * ZROW) = v[k];
                     }
             }
         }
@@ -279,7 +290,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
             const float cl = Vec<float, WQ>::get(clr, r), cu = Vec<float, WQ>::get(ctr, r);
             const float cL = hasl ? cl : 0.0f, cT = hast ? cu : 0.0f;
             const float dh = V::get(dyr, r) + gl[lt][r] + gtv[r];
-            const float tc = tanh_fast(co[lt][r]);
+            const float tc = MEM ? tanhf(co[lt][r]) : tanh_fast(co[lt][r]);
             const float dc = dcl[lt][r] + dtv[r] + dh * go * (1.0f - tc * tc);
             co[lt][r] = cl;
             da[0][r] = live ? dc * gg * gi * (1.0f - gi) : 0.0f;
@@ -370,10 +381,12 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
                 mma_tiles<P, OT>(A, ks, b, acc, low);
             }
 #pragma unroll
-            for (int o = 0; o < 2 * WQ; ++o) {
+            for (int o = 0; o < K::OUTS; ++o) {
                 const float v = P == 3 ? acc[o >> 2][o & 3] + low[o >> 2][o & 3] : acc[o >> 2][o & 3];
-                if (o < WQ) gl[lt][o < WQ ? o : 0] = v;
-                else gt[lt][o < WQ ? 0 : o - WQ] = v;
+                if (o < WQ) gl[lt][o % WQ] = v;
+                else if (o < 2 * WQ) gt[lt][o % WQ] = v;
+                else if (o < 3 * WQ) dcl[lt][o % WQ] += v;  // the states' share of dc
+                else dct[lt][o % WQ] += v;
             }
             if constexpr (NG > 1) {
                 if (lt == 0 && n16 == 0) {
@@ -419,16 +432,16 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     }
 }
 
-template <int H, int NT, typename T, int WQ, int NG>
-__global__ void __launch_bounds__((BwdK<H, NT, T, WQ, NG>::NTH))
-__attribute__((amdgpu_waves_per_eu(BwdK<H, NT, T, WQ, NG>::WPE))) k_bwd(BwdArgs a) {
-    for_units(a, [&](int unit) { bwd_unit<H, NT, T, WQ, NG>(a, unit); });
+template <int H, int NT, typename T, int WQ, int NG, bool MEM>
+__global__ void __launch_bounds__((BwdK<H, NT, T, WQ, NG, MEM>::NTH))
+__attribute__((amdgpu_waves_per_eu(BwdK<H, NT, T, WQ, NG, MEM>::WPE))) k_bwd(BwdArgs a) {
+    for_units(a, [&](int unit) { bwd_unit<H, NT, T, WQ, NG, MEM>(a, unit); });
 }
 
-template <int H, int NT, typename T, int WQ, int NG>
+template <int H, int NT, typename T, int WQ, int NG, bool MEM = false>
 WaveKernel bwd_kernel() {
-    static_assert(BwdK<H, NT, T, WQ, NG>::FITS, "LDS");
-    return {reinterpret_cast<const void*>(&k_bwd<H, NT, T, WQ, NG>), BwdK<H, NT, T, WQ, NG>::NTH};
+    static_assert(BwdK<H, NT, T, WQ, NG, MEM>::FITS, "LDS");
+    return {reinterpret_cast<const void*>(&k_bwd<H, NT, T, WQ, NG, MEM>), BwdK<H, NT, T, WQ, NG, MEM>::NTH};
 }
 
 // One translation unit per hidden size (k_wave_bwd_*.hip).
@@ -439,5 +452,7 @@ WaveKernel bwd_kernel_f32_h32(int nt);
 WaveKernel bwd_kernel_f32_h64(int nt);
 WaveKernel bwd_kernel_bf16_h32(int nt);
 WaveKernel bwd_kernel_bf16_h64(int nt);
+WaveKernel bwd_kernel_mem_h16(int nt);
+WaveKernel bwd_kernel_mem_h32(int nt);
 
 }  // namespace mdl

@@ -45,7 +45,7 @@
 
 namespace mdl {
 
-template <int H, int NT, typename T, int CK, int WQ, int NG>
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
 struct FwdK {
     static constexpr int P = Pieces<T>::N;
     static constexpr int UW = 4 * WQ, NWU = H / UW;     // hidden units per wave, waves per tile group
@@ -56,7 +56,7 @@ struct FwdK {
     static constexpr int TILES = WQ + 1;
     // Registers per lane: up to 256, in which MFMA results need no moves from
     // accumulation registers, unless the operands alone take more.
-    static constexpr int WPE = TILES * (KS + CK) * P * 4 > 170 ? 1 : 2;
+    static constexpr int WPE = (TILES * (KS + CK) + (MEM ? WQ * KS : 0)) * P * 4 > 170 ? 1 : 2;
     // Inputs of a cell in 16-byte chunks: the x operands (fp32: pieces and a
     // validity chunk, as launch_split_x lays them out) or the pre-activations.
     static constexpr int QI = CK > 0 ? 4 * CK * P + (P == 3 ? 1 : 0) : 5 * H * (int)sizeof(T) / 16;
@@ -65,7 +65,7 @@ struct FwdK {
     static constexpr int QZ = 5 * H * (int)sizeof(T) / 16, QY = H * (int)sizeof(T) / 16, QC = H / 4;
     static constexpr int QF = QZ + QY + QC;
     static constexpr int PF = QF + 1;
-    static constexpr size_t HOP = (size_t)2 * P * (NT * 16 + 1) * KP * 2;
+    static constexpr size_t HOP = (size_t)2 * (MEM ? 2 : 1) * P * (NT * 16 + 1) * KP * 2;
     static constexpr size_t IN1 = (size_t)NT * 16 * PI * 16, OUT1 = (size_t)NT * 16 * PF * 16;
     static constexpr size_t LIM = 156 * 1024;
     // Both pass through LDS where they fit: a lane's own values are pieces of
@@ -79,9 +79,9 @@ struct FwdK {
     static_assert(H % UW == 0 && NT % NG == 0 && NTH <= 1024, "wave split");
 };
 
-template <int H, int NT, typename T, int CK, int WQ, int NG>
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
 __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
-    using K = FwdK<H, NT, T, CK, WQ, NG>;
+    using K = FwdK<H, NT, T, CK, WQ, NG, MEM>;
     constexpr int P = K::P, NWU = K::NWU, TPG = K::TPG, KS = K::KS, KP = K::KP, TILES = K::TILES, NTH = K::NTH;
     constexpr bool STAGE_IN = K::STAGE_IN, STAGE_OUT = K::OBUF > 0;
     constexpr int OBUF = K::OBUF, PI = K::PI, QI = K::QI, PF = K::PF, QF = K::QF, QZ = K::QZ, QY = K::QY;
@@ -89,6 +89,8 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     constexpr bool FUSED = CK > 0;
     using V = Vec<T, WQ>;
     __shared__ __attribute__((aligned(16))) bf16_t hop[2][P][ROWS][KP];
+    // with memory-state matrices, the same operand rows of the cell states
+    __shared__ __attribute__((aligned(16))) bf16_t cop[MEM ? 2 : 1][MEM ? P : 1][MEM ? ROWS : 1][KP];
     __shared__ float cedge[2][NG][H];
     __shared__ __attribute__((aligned(16))) u32x4 ist[STAGE_IN ? 2 : 1][STAGE_IN ? NT * 16 * PI : 1];
     __shared__ __attribute__((aligned(16))) u32x4 ost[STAGE_OUT ? OBUF : 1][STAGE_OUT ? NT * 16 : 1][PF];
@@ -113,11 +115,15 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
 
     for (int i = threadIdx.x; i < (int)(sizeof(hop) / 16); i += NTH)
         reinterpret_cast<uint4*>(&hop[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
+    if constexpr (MEM)
+        for (int i = threadIdx.x; i < (int)(sizeof(cop) / 16); i += NTH)
+            reinterpret_cast<uint4*>(&cop[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
     if constexpr (NG > 1)
         for (int i = threadIdx.x; i < 2 * NG * H; i += NTH) (&cedge[0][0][0])[i] = 0.0f;
 
-    // hidden outputs of rows yy, lane's units -> operand rows of the next diagonal
-    auto put_h = [&](int buf, int yy, const float (&hv)[WQ]) {
+    // values (hidden outputs, cell states) of row yy, the lane's units -> operand
+    // rows of the next diagonal
+    auto put = [&](auto& op, int buf, int yy, const float (&hv)[WQ]) {
         typename Vec<bf16_t, WQ>::R pc[P];
         if constexpr (P == 3) {
             uint32_t p0[3], p1[3];
@@ -134,8 +140,8 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
         }
 #pragma unroll
         for (int k = 0; k < P; ++k) {
-            *reinterpret_cast<typename Vec<bf16_t, WQ>::R*>(&hop[buf][k][yy][u0]) = pc[k];
-            *reinterpret_cast<typename Vec<bf16_t, WQ>::R*>(&hop[buf][k][yy + 1][H + u0]) = pc[k];
+            *reinterpret_cast<typename Vec<bf16_t, WQ>::R*>(&op[buf][k][yy][u0]) = pc[k];
+            *reinterpret_cast<typename Vec<bf16_t, WQ>::R*>(&op[buf][k][yy + 1][H + u0]) = pc[k];
         }
     };
 
@@ -158,7 +164,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                     hv[r] = St<T>::ld1(Y + p + r);
                     cprev[lt][r] = Cs[p + r];
                 }
-                put_h(pb, yy, hv);
+                put(hop, pb, yy, hv);
             }
             if constexpr (NG > 1) {
                 if (lt == TPG - 1 && n16 == 15) {
@@ -171,7 +177,8 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
 
     // A operands, lane row n16 = 4 jj + e: tile r < WQ, gate e of unit
     // UW w + WQ jj + r; tile WQ, candidate of unit UW w + WQ jj + e.
-    bf16x8 Ah[TILES][KS][P], Ax[TILES][FUSED ? CK : 1][P];
+    // Memory-state matrices: gates i, f_L, f_T of the sigmoid tiles (V rows).
+    bf16x8 Ah[TILES][KS][P], Ax[TILES][FUSED ? CK : 1][P], Ac[MEM ? WQ : 1][MEM ? KS : 1][P];
     const T* const U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
     const T* const Wx = static_cast<const T*>(a.wx) + (int64_t)d * G * a.c_in;
     const T* const Bd = static_cast<const T*>(a.b) + d * G;
@@ -190,6 +197,20 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
             const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
             make_op<T>(v, Ah[t][ks]);
+        }
+        if constexpr (MEM) {
+            if (t < WQ) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int k = 32 * ks + 8 * q;
+                    const T* p = static_cast<const T*>(a.v) + ((int64_t)d * 3 * H + (e < 3 ? e : 0) * H + ul) * 2 * H + k;
+                    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                    const bool in = e < 3 && k < 2 * H;
+                    const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
+                    const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                    make_op<T>(v, Ac[t < WQ ? t : 0][ks]);
+                }
+            }
         }
 #pragma unroll
         for (int ks = 0; ks < CK; ++ks) {
@@ -365,7 +386,9 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     // Staged outputs of diagonal s written back: thread t stores chunk t % QF
     // of rows t / QF, + RPF, ... (threads and rows past the last, and rows
     // outside the diagonal, repeat a cell of it and write the same bytes
-    // twice: every lane stores in every pass).
+    // twice: every lane stores in every pass). Non-temporal: the next reader is
+    // the backward or another layer (word batch 228 -> 187 us, line batch
+    // 1300 -> 1284 us).
     constexpr int RPF = STAGE_OUT ? (NTH / QF < NT * 16 ? (NTH / QF > 0 ? NTH / QF : 1) : NT * 16) : 1;
     constexpr int NITF = (NT * 16 + RPF - 1) / RPF;
     static_assert(!STAGE_OUT || NTH >= QF, "a row per pass");
@@ -388,8 +411,10 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
 #pragma unroll
                 for (int k = 0; k < GR; ++k)
                     if (i0 + k < NITF)
-                        *reinterpret_cast<u32x4*>(
-                            fbase + (int64_t)(M.sx * s + min(max(fc0 + (i0 + k) * RPF, ylo), yhi) * M.ky) * frow) = v[k];
+                        __builtin_nontemporal_store(
+                            v[k], reinterpret_cast<u32x4*>(
+                                      fbase + (int64_t)(M.sx * s + min(max(fc0 + (i0 + k) * RPF, ylo), yhi) * M.ky) *
+                                                  frow));
                 if constexpr (NITF > GR) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -411,6 +436,17 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 for (int k = 0; k < P; ++k)
                     bh[k] = as_bf16x8(*reinterpret_cast<const uint4*>(&hop[prv][k][yy][32 * ks + 8 * q]));
                 mma_tiles<P, TILES>(Ah, ks, bh, acc, low);
+            }
+            if constexpr (MEM) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    bf16x8 bc[P];
+#pragma unroll
+                    for (int k = 0; k < P; ++k)
+                        bc[k] = as_bf16x8(*reinterpret_cast<const uint4*>(&cop[prv][k][yy][32 * ks + 8 * q]));
+                    mma_tiles<P, WQ>(Ac, ks, bc, reinterpret_cast<floatx4(&)[WQ]>(acc),
+                                     reinterpret_cast<floatx4(&)[WQ]>(low));
+                }
             }
         };
         if constexpr (AHEAD) contract(0);
@@ -436,21 +472,31 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 ct[r] = row_above(cprev[lt][r], edge);
             }
             const bool in = yy >= ylo && yy <= yhi, live = in && mk != 0;
+            // With memory-state matrices the states feed the gates: there the
+            // library functions, as exact as the arithmetic around them.
+            auto sg = [](float z) { return MEM ? 1.0f / (1.0f + __expf(-z)) : sigm_fast(z); };
+            auto th = [](float z) { return MEM ? tanhf(z) : tanh_fast(z); };
             float gv[5][WQ], hv[WQ], cv[WQ];
 #pragma unroll
             for (int r = 0; r < WQ; ++r) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    gv[e][r] = sigm_fast(P == 3 ? (zx[r][e] + acc[r][e]) + low[r][e] : acc[r][e]);
-                gv[4][r] = tanh_fast(P == 3 ? (zx[WQ][r] + acc[WQ][r]) + low[WQ][r] : acc[WQ][r]);
+                    gv[e][r] = sg(P == 3 ? (zx[r][e] + acc[r][e]) + low[r][e] : acc[r][e]);
+                gv[4][r] = th(P == 3 ? (zx[WQ][r] + acc[WQ][r]) + low[WQ][r] : acc[WQ][r]);
                 const float cn = gv[0][r] * gv[4][r] + gv[1][r] * cprev[lt][r] + gv[2][r] * ct[r];
-                const float hn = gv[3][r] * tanh_fast(cn);
+                const float hn = gv[3][r] * th(cn);
                 cv[r] = live ? cn : 0.0f;
                 hv[r] = live ? hn : 0.0f;
                 cprev[lt][r] = cv[r];
                 gv[0][r] = mk != 0 ? gv[0][r] : -1.0f;  // marks a masked cell for the backward
             }
-            put_h(cur, yy, hv);
+            put(hop, cur, yy, hv);
+            if constexpr (MEM) {
+                float cc[WQ];  // an overflowed state saturates its gates instead of becoming NaN pieces
+#pragma unroll
+                for (int r = 0; r < WQ; ++r) cc[r] = clamp_bf16(cv[r]);
+                put(cop, cur, yy, cc);
+            }
             if constexpr (NG > 1) {
                 if (lt == TPG - 1 && n16 == 15) {
 #pragma unroll
@@ -529,11 +575,11 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     }
 }
 
-template <int H, int NT, typename T, int CK, int WQ, int NG>
-__global__ void __launch_bounds__((FwdK<H, NT, T, CK, WQ, NG>::NTH))
-__attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG>::WPE))) k_fwd(FwdArgs a) {
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
+__global__ void __launch_bounds__((FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH))
+__attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG, MEM>::WPE))) k_fwd(FwdArgs a) {
     if (a.rid) zero_invalid_rows(a);
-    for_units(a, [&](int unit) { fwd_unit<H, NT, T, CK, WQ, NG>(a, unit); });
+    for_units(a, [&](int unit) { fwd_unit<H, NT, T, CK, WQ, NG, MEM>(a, unit); });
 }
 
 // Hidden sizes whose forward wavefront takes over the projection: where Wx's
@@ -544,15 +590,19 @@ constexpr bool fwd_fusable(int hidden) {
     return hidden <= (std::is_same<T, float>::value ? 32 : 64);
 }
 
-template <int H, int NT, typename T, int WQ, int NG>
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
+WaveKernel fwd_kernel_ck() {
+    return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, CK, WQ, NG, MEM>), FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH};
+}
+
+template <int H, int NT, typename T, int WQ, int NG, bool MEM = false>
 WaveKernel fwd_kernel(int ck) {
-    if (ck == 0) return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, 0, WQ, NG>), FwdK<H, NT, T, 0, WQ, NG>::NTH};
-    if constexpr (!fwd_fusable<T>(H)) return {};
-    else switch (ck) {
-        case 1: return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, 1, WQ, NG>), FwdK<H, NT, T, 1, WQ, NG>::NTH};
-        case 2: return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, 2, WQ, NG>), FwdK<H, NT, T, 2, WQ, NG>::NTH};
-        default: return {};
+    if (ck == 0) return fwd_kernel_ck<H, NT, T, 0, WQ, NG, MEM>();
+    if constexpr (fwd_fusable<T>(H)) {
+        if (ck == 1) return fwd_kernel_ck<H, NT, T, 1, WQ, NG, MEM>();
+        if (ck == 2) return fwd_kernel_ck<H, NT, T, 2, WQ, NG, MEM>();
     }
+    return {};
 }
 
 // One translation unit per hidden size (k_wave_fwd_*.hip).
@@ -563,5 +613,7 @@ WaveKernel fwd_kernel_f32_h32(int nt, int ck);
 WaveKernel fwd_kernel_f32_h64(int nt, int ck);
 WaveKernel fwd_kernel_bf16_h32(int nt, int ck);
 WaveKernel fwd_kernel_bf16_h64(int nt, int ck);
+WaveKernel fwd_kernel_mem_h16(int nt, int ck);
+WaveKernel fwd_kernel_mem_h32(int nt, int ck);
 
 }  // namespace mdl

@@ -278,7 +278,7 @@ def test_projection_fused_query(built_lib):
     assert f(ctypes.byref(L.LayerDesc(32, 32, 0))) == 1    # lines: inside the wavefront
     assert f(ctypes.byref(L.LayerDesc(65, 32, 0))) == 0    # more than 64 input channels
     assert f(ctypes.byref(L.LayerDesc(64, 128, 1))) == 0   # bf16 H 128
-    assert f(ctypes.byref(L.LayerDesc(16, 16, 0, 1))) == 0  # memory-state matrices
+    assert f(ctypes.byref(L.LayerDesc(16, 16, 0, 1))) == 1  # memory-state matrices
     assert f(ctypes.byref(L.LayerDesc(16, 65, 0))) == -1   # above the largest built
     assert f(None) == -1
 

@@ -81,13 +81,17 @@ k_head_fwd(int H, int K, int canvas_w, const float* __restrict__ Y, const int32_
            const int32_t* __restrict__ frame_off, const int32_t* __restrict__ tiles, const float* __restrict__ W,
            const float* __restrict__ b, float* __restrict__ logits, float* __restrict__ S) {
     extern __shared__ __attribute__((aligned(16))) float hsm[];
-    float* sW = hsm;         // [K][H]
-    float* sS = sW + K * H;  // [HC][H]
+    // W rows at a pitch of H + 4: consecutive classes read as 16-byte vectors
+    // fall on different banks (at pitch H sixteen lanes shared one; with the
+    // row loop unrolled, word batch 49 -> 23 us, 2.3 TB/s)
+    const int WP = H + 4;
+    float* sW = hsm;          // [K][WP]
+    float* sS = sW + K * WP;  // [HC][H]
     const int tid = threadIdx.x;
     const int ex = tiles[2 * blockIdx.x], t0 = tiles[2 * blockIdx.x + 1];
     const int y0 = rects[4 * ex], x0 = rects[4 * ex + 1], h = rects[4 * ex + 2], w = rects[4 * ex + 3];
     const int nc = min(HC, w - t0);
-    for (int e = tid; e < K * H; e += HT) sW[e] = W[e];
+    for (int e = tid; e < K * H; e += HT) sW[e / H * WP + e % H] = W[e];
     // column sums: slot e = (cell c, hidden units 4 j4 .. 4 j4 + 3); each slot
     // sums its four directions' channels d*H + 4 j4 over the rows, then the
     // directions in a fixed order
@@ -99,6 +103,7 @@ k_head_fwd(int H, int K, int canvas_w, const float* __restrict__ Y, const int32_
         for (int d = 0; d < 4; ++d) a[d] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (c < nc) {
             const float* p = Y + ((int64_t)y0 * canvas_w + x0 + t0 + c) * (4 * H) + 4 * j4;
+#pragma unroll 4  // sixteen loads in flight: a tile has one slot per thread
             for (int y = 0; y < h; ++y) {
                 const float* q = p + (int64_t)y * canvas_w * (4 * H);
 #pragma unroll
@@ -127,10 +132,15 @@ k_head_fwd(int H, int K, int canvas_w, const float* __restrict__ Y, const int32_
     }
     for (int e = tid; e < nc * K; e += HT) {
         const int c = e / K, k = e - c * K;
-        const float* wk = &sW[k * H];
-        const float* sv = &sS[c * H];
         float acc = 0.0f;
-        for (int j = 0; j < H; ++j) acc = fmaf(wk[j], sv[j], acc);
+        for (int j = 0; j < H; j += 4) {
+            const float4 wk = *reinterpret_cast<const float4*>(&sW[k * WP + j]);
+            const float4 sv = *reinterpret_cast<const float4*>(&sS[c * H + j]);
+            acc = fmaf(wk.x, sv.x, acc);
+            acc = fmaf(wk.y, sv.y, acc);
+            acc = fmaf(wk.z, sv.z, acc);
+            acc = fmaf(wk.w, sv.w, acc);
+        }
         logits[(int64_t)(f0 + c) * K + k] = acc + 4.0f * h * b[k];
     }
 }
@@ -497,7 +507,7 @@ __global__ void k_zero_f(float* __restrict__ p, int n) {
 int head_tile_frames() { return HC; }
 int head_dw_chunk_frames() { return DWF; }
 
-size_t head_fwd_lds(int H, int K) { return (size_t)(K * H + HC * H) * 4; }
+size_t head_fwd_lds(int H, int K) { return (size_t)(K * (H + 4) + HC * H) * 4; }
 size_t head_bwd_lds(int H, int K) { return (size_t)(K * H + HC * H) * 4; }
 size_t head_dw_lds(int H, int K) { return (size_t)(DWF * K + DWF * (H + 4)) * 4; }
 int ctc_states_per_lane(int max_labels) {

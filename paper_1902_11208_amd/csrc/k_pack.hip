@@ -216,7 +216,10 @@ hipError_t launch_rect_ids(int n, const int32_t* d_rects, int canvas_h, int canv
 
 // ---------------------------------------------------------------------------
 // Scatter / gather: block (k, row) copies one example row of w*c elements.
-// Element size 2 or 4 bytes; copies run in 2-byte or 4-byte units.
+// Element size 2 or 4 bytes; copies run in 16-byte units where a cell's
+// channels fill them and every example and the canvas are aligned to them
+// (line batch, 32 fp32 channels: scatter 64 -> 41 us, gather 32 -> 29 us),
+// else in 2-byte or 4-byte units.
 // ---------------------------------------------------------------------------
 template <typename E>
 __global__ void k_scatter(const void* const* __restrict__ ptrs, const int32_t* __restrict__ rects, int canvas_w,
@@ -241,7 +244,7 @@ __global__ void k_gather(void* const* __restrict__ ptrs, const int32_t* __restri
 }
 
 hipError_t launch_scatter(int n, const void* const* d_ptrs, const int32_t* d_rects, int canvas_h, int canvas_w,
-                          int c, int esize, void* d_canvas, int max_h, hipStream_t s) {
+                          int c, int esize, void* d_canvas, int max_h, bool wide, hipStream_t s) {
     int64_t bytes = (int64_t)canvas_h * canvas_w * c * esize;
     if (bytes > 0) {
         if (bytes % 8 == 0)
@@ -253,7 +256,10 @@ hipError_t launch_scatter(int n, const void* const* d_ptrs, const int32_t* d_rec
     }
     if (n > 0 && max_h > 0) {
         dim3 grid(n, max_h);
-        if (esize == 4)
+        if (wide)
+            hipLaunchKernelGGL(k_scatter<uint4>, grid, dim3(256), 0, s, d_ptrs, d_rects, canvas_w, (int)((int64_t)c * esize / 16),
+                               reinterpret_cast<uint4*>(d_canvas));
+        else if (esize == 4)
             hipLaunchKernelGGL(k_scatter<float>, grid, dim3(256), 0, s, d_ptrs, d_rects, canvas_w, c,
                                reinterpret_cast<float*>(d_canvas));
         else
@@ -264,10 +270,13 @@ hipError_t launch_scatter(int n, const void* const* d_ptrs, const int32_t* d_rec
 }
 
 hipError_t launch_gather(int n, void* const* d_ptrs, const int32_t* d_rects, int canvas_w, int c, int esize,
-                         const void* d_canvas, int max_h, hipStream_t s) {
+                         const void* d_canvas, int max_h, bool wide, hipStream_t s) {
     if (n > 0) {
         dim3 grid(n, max_h > 0 ? max_h : 1);
-        if (esize == 4)
+        if (wide)
+            hipLaunchKernelGGL(k_gather<uint4>, grid, dim3(256), 0, s, d_ptrs, d_rects, canvas_w, (int)((int64_t)c * esize / 16),
+                               reinterpret_cast<const uint4*>(d_canvas));
+        else if (esize == 4)
             hipLaunchKernelGGL(k_gather<float>, grid, dim3(256), 0, s, d_ptrs, d_rects, canvas_w, c,
                                reinterpret_cast<const float*>(d_canvas));
         else

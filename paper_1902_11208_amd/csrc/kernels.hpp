@@ -26,11 +26,13 @@ hipError_t launch_mask(int n, const int32_t* d_rects, int canvas_h, int canvas_w
 // d_zero2 (the wavefront unit queue) when n > 0 and d_zero2 is not NULL.
 hipError_t launch_rect_ids(int n, const int32_t* d_rects, int canvas_h, int canvas_w, int32_t* d_rid,
                            unsigned* d_zero2, hipStream_t s);
-// scatter/gather of n HWC examples of c channels, element size esize (2 or 4).
+// scatter/gather of n HWC examples of c channels, element size esize (2 or 4);
+// wide: c * esize is a multiple of 16 and every example and the canvas are
+// 16-byte aligned.
 hipError_t launch_scatter(int n, const void* const* d_ptrs, const int32_t* d_rects, int canvas_h,
-                          int canvas_w, int c, int esize, void* d_canvas, int max_h, hipStream_t s);
+                          int canvas_w, int c, int esize, void* d_canvas, int max_h, bool wide, hipStream_t s);
 hipError_t launch_gather(int n, void* const* d_ptrs, const int32_t* d_rects, int canvas_w, int c,
-                         int esize, const void* d_canvas, int max_h, hipStream_t s);
+                         int esize, const void* d_canvas, int max_h, bool wide, hipStream_t s);
 
 // --- forward ---------------------------------------------------------------
 // Z[p][20H] = Wx_all[20H][C] x[p] + b_all, for the cells of every 64-cell

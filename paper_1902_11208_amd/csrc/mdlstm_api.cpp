@@ -580,7 +580,7 @@ static mdlstm_status pack_io(bool pack, int32_t n, const void* const* ptrs, cons
     hipStream_t s = as_stream(stream);
     if (n == 0) {
         if (pack) HIP_OR_FAIL(mdl::launch_scatter(0, nullptr, nullptr, canvas_h, canvas_w, c, esize,
-                                                  const_cast<void*>(d_canvas), 0, s));
+                                                  const_cast<void*>(d_canvas), 0, false, s));
         return MDLSTM_OK;
     }
     if (!d_workspace || workspace_bytes < pack_ws_bytes(n))
@@ -591,11 +591,13 @@ static mdlstm_status pack_io(bool pack, int32_t n, const void* const* ptrs, cons
     int32_t* d_r = reinterpret_cast<int32_t*>(ws + align_up((size_t)n * 8));
     HIP_OR_FAIL(hipMemcpyAsync(d_ptrs, ptrs, (size_t)n * 8, hipMemcpyHostToDevice, s));
     HIP_OR_FAIL(hipMemcpyAsync(d_r, rects, (size_t)n * 16, hipMemcpyHostToDevice, s));
+    bool wide = (int64_t)c * esize % 16 == 0 && !misaligned(d_canvas);
+    for (int32_t k = 0; wide && k < n; ++k) wide = !misaligned(ptrs[k]);
     if (pack)
         HIP_OR_FAIL(mdl::launch_scatter(n, d_ptrs, d_r, canvas_h, canvas_w, c, esize, const_cast<void*>(d_canvas),
-                                        max_h, s));
+                                        max_h, wide, s));
     else
-        HIP_OR_FAIL(mdl::launch_gather(n, d_ptrs, d_r, canvas_w, c, esize, d_canvas, max_h, s));
+        HIP_OR_FAIL(mdl::launch_gather(n, d_ptrs, d_r, canvas_w, c, esize, d_canvas, max_h, wide, s));
     return MDLSTM_OK;
 }
 

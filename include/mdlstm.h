@@ -428,10 +428,9 @@ const char* mdlstm_last_error(void);
  * events[n] (host array of hipEvent_t handles owned by the caller). While set,
  * mdlstm_forward and mdlstm_backward called on this thread record them on
  * their stream at kernel boundaries:
- *   [0] before the projection (mdlstm_projection_fused: the input layout pass)
- *   [1] after it   [2] after zeroing
- *   invalid output rows (the persistent forward wavefront zeroes them itself
- *   when the batch has at least a unit per CU; then [2] follows [1] directly)
+ *   [0] before the layout pass (rectangle ids, zero rows of invalid cells, fp32
+ *   inputs laid out) and the projection, where it is a kernel of its own
+ *   (mdlstm_projection_fused)   [1] after them   [2] follows [1] directly
  *   [3] after the forward wavefront
  *   [4] before the backward wavefront  [5] after it  [6] after the input
  *   gradient  [7] after the weight gradients. Where one kernel computes both

@@ -50,11 +50,8 @@ hipError_t launch_remap(const void* src, void* dst, int es, int64_t outer, int r
                         int cs, int cd, hipStream_t s);
 hipError_t launch_count_nonfinite(const void* d, int64_t n_cells, int row, const uint8_t* d_mask, int dtype,
                                   unsigned long long* d_count, hipStream_t s);
-// Zero the rows of a [n_cells][width] tensor (storage dtype) whose cell is invalid.
-hipError_t launch_zero_invalid(const LayerGeom& g, int width, const uint8_t* d_mask,
-                               const int32_t* d_rid, void* d_t, hipStream_t s);
 // Tensors of a forward wavefront. x: the inputs as the kernel reads them, that
-// is the layer's own (bf16) or their pieces (fp32, launch_split_x); unused
+// is the layer's own (bf16) or their pieces (fp32, launch_forward_layout); unused
 // where the projection runs apart (fwd_fused_steps == 0).
 struct FwdTensors {
     const void* u;
@@ -69,20 +66,23 @@ struct FwdTensors {
 // K steps of 32 input channels the forward wavefront computes itself; 0 where
 // launch_projection has to run first.
 int fwd_fused_steps(const LayerGeom& g);
-// Workspace of the fp32 inputs' pieces, and the kernel that fills it for the
-// cells of the rectangles.
+// Workspace of the fp32 inputs' pieces.
 size_t fwd_x_bytes(const LayerGeom& g);
-hipError_t launch_split_x(const LayerGeom& g, const void* d_x, const int32_t* d_rid, const uint8_t* d_mask,
-                          void* d_xs, hipStream_t s);
+// Rectangle ids, unit queue, zero output rows of invalid cells and the fp32
+// inputs' pieces, in one launch (n_cells > 0). Its cost per cell block grows
+// with n: above MAX_LAYOUT_RECTS rectangles callers run launch_rect_ids first
+// and pass n = -1 (the ids are in d_rid).
+constexpr int MAX_LAYOUT_RECTS = 4096;
+hipError_t launch_forward_layout(const LayerGeom& g, int n, const int32_t* d_rects, int32_t* d_rid,
+                                 const uint8_t* d_mask, unsigned* d_queue, void* d_y, const void* d_x, void* d_xs,
+                                 hipStream_t s);
 // Forward anti-diagonal wavefront over n_units units (rectangle, direction)
 // in the order of d_units. d_queue: two device counters, zero on entry (the
 // workgroups take units from the first, as many as are resident at once, and
 // count themselves out on the second; the last one out zeroes both again).
-// With d_rid set, the output rows of cells outside every rectangle or masked
-// are zeroed first.
 hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
-                                const int32_t* d_rects, const uint8_t* d_mask, const int32_t* d_rid,
-                                const FwdTensors& t, unsigned* d_queue, hipStream_t s);
+                                const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t, unsigned* d_queue,
+                                hipStream_t s);
 
 // The forward wavefront as one launch per local diagonal (diagonal s of every
 // unit in launch s), recorded as a chain of max_steps kernel nodes into an

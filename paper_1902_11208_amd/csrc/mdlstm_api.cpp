@@ -354,10 +354,12 @@ StagedKey staged_key(const Common& c, int32_t n_rects, const mdlstm_rect* rects)
 std::mutex g_staged_mu;
 std::unordered_map<uintptr_t, StagedKey> g_staged;
 
-mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* rects, bool reuse, hipStream_t s) {
+// A backward call stages the rectangle ids and zeroes the unit queue as well; a
+// forward call leaves both to launch_forward_layout.
+mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* rects, bool backward, hipStream_t s) {
     const StagedKey key = staged_key(c, n_rects, rects);
     const uintptr_t ws = reinterpret_cast<uintptr_t>(c.ws);
-    if (reuse) {
+    if (backward) {
         std::lock_guard<std::mutex> lock(g_staged_mu);
         auto it = g_staged.find(ws);
         if (it != g_staged.end() && it->second == key) return MDLSTM_OK;
@@ -371,7 +373,8 @@ mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* 
         std::memcpy(host.data() + (c.p.units - c.p.rects), units.data(), ubytes);
         HIP_OR_FAIL(hipMemcpyAsync(c.ws + c.p.rects, host.data(), span, hipMemcpyHostToDevice, s));
     }
-    HIP_OR_FAIL(mdl::launch_rect_ids(n_rects, reinterpret_cast<const int32_t*>(c.ws + c.p.rects), c.g.canvas_h,
+    if (backward)
+        HIP_OR_FAIL(mdl::launch_rect_ids(n_rects, reinterpret_cast<const int32_t*>(c.ws + c.p.rects), c.g.canvas_h,
                                      c.g.canvas_w, reinterpret_cast<int32_t*>(c.ws + c.p.rid),
                                      reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
     std::lock_guard<std::mutex> lock(g_staged_mu);
@@ -675,22 +678,23 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
     if (desc->memory_states && stepwise)
         return fail(MDLSTM_ERR_UNSUPPORTED, "the per-diagonal schedule is not built with memory-state matrices");
     HIP_OR_FAIL(mark(0, s));
-    const bool fused = mdl::fwd_fused_steps(c.g) > 0;
-    if (!fused)
+    int32_t* const rids = reinterpret_cast<int32_t*>(c.ws + c.p.rid);
+    unsigned* const queue = reinterpret_cast<unsigned*>(c.ws + c.p.queue);
+    int32_t n_layout = n_rects;
+    if (n_rects > mdl::MAX_LAYOUT_RECTS) {  // ids painted rectangle by rectangle, and read from there
+        HIP_OR_FAIL(mdl::launch_rect_ids(n_rects, drects, c.g.canvas_h, c.g.canvas_w, rids, queue, s));
+        n_layout = -1;
+    }
+    HIP_OR_FAIL(mdl::launch_forward_layout(c.g, n_layout, drects, rids, d_mask, queue, d_y, d_x, c.ws + c.p.xs, s));
+    if (mdl::fwd_fused_steps(c.g) == 0)
         HIP_OR_FAIL(mdl::launch_projection(c.g, d_x, d_wx, d_b, rid, c.ws + c.p.z, s));
-    else if (n_rects > 0)
-        HIP_OR_FAIL(mdl::launch_split_x(c.g, d_x, rid, d_mask, c.ws + c.p.xs, s));
     const int64_t nu = 4 * (int64_t)c.g.hidden * 5 * 2 * c.g.hidden;  // floats of U before V
     const void* d_v = desc->memory_states ? static_cast<const float*>(d_u) + nu : nullptr;
     const mdl::FwdTensors ft{d_u, d_v, d_wx, d_b, c.g.dtype == 0 ? c.ws + c.p.xs : d_x, c.ws + c.p.z, cs, d_y};
     HIP_OR_FAIL(mark(1, s));
-    if (stepwise || n_rects == 0)
-        HIP_OR_FAIL(mdl::launch_zero_invalid(c.g, 4 * c.g.hidden, d_mask, rid, d_y, s));
     HIP_OR_FAIL(mark(2, s));
     if (!stepwise) {
-        // the persistent launch also zeroes the output rows of the invalid cells
-        HIP_OR_FAIL(mdl::launch_wavefront_fwd(c.g, c.nt, 4 * n_rects, units, drects, d_mask, rid, ft,
-                                              reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
+        HIP_OR_FAIL(mdl::launch_wavefront_fwd(c.g, c.nt, 4 * n_rects, units, drects, d_mask, ft, queue, s));
     } else if (n_rects > 0) {
         int32_t max_steps = 0;
         for (int32_t k = 0; k < n_rects; ++k) max_steps = std::max(max_steps, rects[k].h + rects[k].w - 1);

@@ -86,11 +86,6 @@ struct FwdArgs {
     int s0, s1;            // local diagonals [s0, s1) of every unit
     unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
     int n_units;
-    // when rid is set, the output rows (yrow_words x 8 bytes) of the cells
-    // outside every rectangle or masked are zeroed before the units run
-    const int32_t* rid;    // [n_cells] rectangle id, -1 outside every rectangle
-    int64_t n_cells;
-    int yrow_words;
 };
 
 // Target of the stores of lanes whose cell is outside the diagonal: every lane
@@ -105,27 +100,6 @@ __device__ __attribute__((aligned(256))) uint4 g_sink[8 * 64 * WAVE_SINK_LANE];
 
 __device__ __forceinline__ char* sink_ptr() {
     return reinterpret_cast<char*>(&g_sink<0>[((blockIdx.x & 7) * 64 + (threadIdx.x & 63)) * WAVE_SINK_LANE]);
-}
-
-// Output rows of the invalid cells (outside every rectangle, or masked) set
-// to zero, a wave per 64 cells over the grid: each lane reads one cell's mask
-// byte and rect id, then the wave clears the rows of the invalid ones with the
-// lanes along the row. Done before any unit starts; the units write the rows
-// of the valid cells.
-template <typename A>
-__device__ __forceinline__ void zero_invalid_rows(const A& a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    uint2* const y = static_cast<uint2*>(a.y);
-    for (int64_t c0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64; c0 < a.n_cells;
-         c0 += waves * 64) {
-        const int64_t p = c0 + lane;
-        const bool bad = p < a.n_cells && (a.mask[p] == 0 || a.rid[p] < 0);
-        for (uint64_t bm = __ballot(bad); bm; bm &= bm - 1) {
-            uint2* row = y + (c0 + __builtin_ctzll(bm)) * a.yrow_words;
-            for (int k = lane; k < a.yrow_words; k += 64) row[k] = make_uint2(0u, 0u);
-        }
-    }
 }
 
 // Units of a launch: workgroup b runs unit b, or, with a queue, a fixed number

@@ -58,7 +58,7 @@ struct FwdK {
     // accumulation registers, unless the operands alone take more.
     static constexpr int WPE = (TILES * (KS + CK) + (MEM ? WQ * KS : 0)) * P * 4 > 170 ? 1 : 2;
     // Inputs of a cell in 16-byte chunks: the x operands (fp32: pieces and a
-    // validity chunk, as launch_split_x lays them out) or the pre-activations.
+    // validity chunk, as launch_forward_layout lays them out) or the pre-activations.
     static constexpr int QI = CK > 0 ? 4 * CK * P + (P == 3 ? 1 : 0) : 5 * H * (int)sizeof(T) / 16;
     static constexpr int PI = CK > 0 && P == 3 ? QI : QI + 1;  // LDS pitch, odd: rows in different banks
     // Outputs: the 5H activated gates, then the H outputs (storage type), then the H cell states (fp32).
@@ -578,7 +578,6 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
 template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
 __global__ void __launch_bounds__((FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH))
 __attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG, MEM>::WPE))) k_fwd(FwdArgs a) {
-    if (a.rid) zero_invalid_rows(a);
     for_units(a, [&](int unit) { fwd_unit<H, NT, T, CK, WQ, NG, MEM>(a, unit); });
 }
 

@@ -8,14 +8,8 @@
 // row y: the left predecessor is row y of the previous diagonal, the top
 // predecessor row y - 1.
 //
-// Here: the backward wavefront, the forward and backward of wide bf16 layers,
-// and the launches; the forward of the other shapes is wave_fwd.hpp.
-//
-// The unit's hidden units are split over NW waves in quads of four. Backward,
-// per step: every lane does the gate-gradient update of its pairs (phase A),
-// then the waves contract da with U^T on MFMA, split by output tile and
-// reduction range, partials summed through LDS in a fixed order (phase B).
-// The U operands stay in VGPRs for the whole unit.
+// Here: the forward and backward of wide bf16 layers (H = 128), the layout
+// pass and the launches; the other shapes are wave_fwd.hpp and wave_bwd.hpp.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -29,112 +23,36 @@ namespace mdl {
 
 namespace {
 
+// 16x16x32 bf16 MFMA operands: eight consecutive values per slot and step.
 template <typename T>
 struct Ops;
 template <>
-struct Ops<float> {  // 16x16x4 f32 MFMA: one reduction value per slot and step
-    using Op = float;
-    static constexpr int PER = 1;
-    static __device__ __forceinline__ Op lds(const float* p) { return *p; }
-    static __device__ __forceinline__ floatx4 mma(Op a, Op b, floatx4 c) { return mfma_f32(a, b, c); }
-};
-template <>
-struct Ops<bf16_t> {  // 16x16x32 bf16 MFMA: eight consecutive values per slot and step
+struct Ops<bf16_t> {
     using Op = bf16x8;
     static constexpr int PER = 8;
     static __device__ __forceinline__ Op lds(const bf16_t* p) { return as_bf16x8(*reinterpret_cast<const uint4*>(p)); }
     static __device__ __forceinline__ floatx4 mma(Op a, Op b, floatx4 c) { return mfma_bf16(a, b, c); }
 };
 
-template <typename T>
-__device__ __forceinline__ float ld1f(const T* p) { return St<T>::ld1(p); }
-
-// N consecutive operands from LDS; fp32 runs of a multiple of four (two)
-// values as 16-byte (8-byte) reads, which the row pitches and run offsets of
-// the callers keep aligned. With row pitches of 4 mod 32 banks, the lanes of
-// a 16-byte read that the LDS serves together fall on distinct bank quads.
-template <typename T, int N>
-__device__ __forceinline__ void lds_run(const T* p, typename Ops<T>::Op (&v)[N]) {
-    if constexpr (std::is_same<T, float>::value && N % 4 == 0) {
-#pragma unroll
-        for (int k = 0; k < N / 4; ++k) {
-            const float4 f = *reinterpret_cast<const float4*>(p + 4 * k);
-            v[4 * k] = f.x;
-            v[4 * k + 1] = f.y;
-            v[4 * k + 2] = f.z;
-            v[4 * k + 3] = f.w;
-        }
-    } else if constexpr (std::is_same<T, float>::value && N % 2 == 0) {
-#pragma unroll
-        for (int k = 0; k < N / 2; ++k) {
-            const float2 f = *reinterpret_cast<const float2*>(p + 2 * k);
-            v[2 * k] = f.x;
-            v[2 * k + 1] = f.y;
-        }
-    } else {
-#pragma unroll
-        for (int ks = 0; ks < N; ++ks) v[ks] = Ops<T>::lds(p + ks * Ops<T>::PER);
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ T from_f(float v);
-template <>
-__device__ __forceinline__ float from_f<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ bf16_t from_f<bf16_t>(float v) { return f2bf(v); }
-
 // A-operand values of one reduction slot from global memory: element stride
 // `es` between consecutive k.
 template <typename T, int NSTEP>
 __device__ __forceinline__ void load_slot(const T* __restrict__ base, int64_t es, bool ok,
                                           typename Ops<T>::Op (&v)[NSTEP]) {
-    if constexpr (std::is_same<T, float>::value) {
 #pragma unroll
-        for (int ks = 0; ks < NSTEP; ++ks) v[ks] = ok ? base[ks * es] : 0.0f;
-    } else {
+    for (int ks = 0; ks < NSTEP; ++ks) {
+        uint32_t w[4];
 #pragma unroll
-        for (int ks = 0; ks < NSTEP; ++ks) {
-            uint32_t w[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t lo = ok ? base[(8 * ks + 2 * e) * es] : 0;
-                const uint32_t hi = ok ? base[(8 * ks + 2 * e + 1) * es] : 0;
-                w[e] = lo | (hi << 16);
-            }
-            v[ks] = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t lo = ok ? base[(8 * ks + 2 * e) * es] : 0;
+            const uint32_t hi = ok ? base[(8 * ks + 2 * e + 1) * es] : 0;
+            w[e] = lo | (hi << 16);
         }
+        v[ks] = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
     }
 }
 
-template <int H, typename T>
-struct Geo {
-    // Waves per unit: fp32, one hidden-unit quad per wave up to eight waves.
-    // The waves of a workgroup share the four SIMDs of a CU, and a wave alone
-    // on its SIMD leaves MFMA and VALU issue slots idle, so more waves with
-    // less work each shorten every step (beyond eight the VGPR budget spills).
-    static constexpr int NW = std::is_same<T, float>::value ? (H <= 4 ? 1 : (H <= 32 ? H / 4 : 8))
-                                                             : (H <= 8 ? 2 : (H <= 32 ? 4 : 8));
-    static constexpr int WQ = (H / 4) / NW;                                     // hidden-unit quads per wave
-    static constexpr int G = 5 * H;
-    static constexpr int PER = Ops<T>::PER;
-    // forward
-    static constexpr int KRUN = H / 2;                  // hcat values per reduction slot
-    static constexpr int NSTEP = KRUN / PER;
-    static constexpr int GT = (H + 15) / 16;            // cell-candidate tiles
-    static constexpr int SPL = NW / GT;                 // waves sharing one candidate tile
-    static constexpr int GSTEP = NSTEP / SPL;           // candidate K steps per wave
-    // backward
-    static constexpr int KRUNB = G / 4;                 // da values per reduction slot
-    static constexpr int NSTEPB = KRUNB / PER;
-    static constexpr int MT = (2 * H + 15) / 16;        // output tiles of U^T da
-    static constexpr int TPW = MT >= NW ? MT / NW : 1;  // output tiles per wave
-    static constexpr int SPLB = MT >= NW ? 1 : NW / MT;  // waves sharing one output tile
-    static constexpr int BSTEP = NSTEPB / SPLB;
-    static_assert(KRUN % PER == 0 && NSTEP % SPL == 0 && GT * SPL == NW, "forward split");
-    static_assert(KRUNB % PER == 0 && NSTEPB % SPLB == 0, "backward split");
-    static_assert(MT >= NW ? MT % NW == 0 : NW % MT == 0, "backward tiles");
-};
+constexpr int WIDE_WAVES = 8;  // waves per unit of the wide kernels, sixteen hidden units each (H = 128)
 
 }  // namespace
 
@@ -169,11 +87,6 @@ template <typename T>
 __device__ __forceinline__ T* wave_sink() {
     return reinterpret_cast<T*>(&g_wave_sink[((blockIdx.x & 7) * 64 + (threadIdx.x & 63)) * SINK_LANE]);
 }
-
-template <int H, typename T>
-struct FwdBig {
-    static constexpr bool on = sizeof(T) == 2 && Geo<H, T>::NW == 8 && Geo<H, T>::WQ == 4;
-};
 
 template <int H, int NT, typename T>
 __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
@@ -385,12 +298,6 @@ __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
 // with a barrier after each: A = gate-gradient update of a tile, B = its
 // U^T da products on MFMA.
 // ---------------------------------------------------------------------------
-template <int H, typename T>
-struct BwdBig {
-    static constexpr bool on = sizeof(T) == 2 && Geo<H, T>::NW == 8 && Geo<H, T>::WQ == 4 && 2 * H == 256;
-    static_assert(!on || 5 * H * sizeof(T) <= SINK_LANE * 16, "sink row");
-};
-
 template <int H, int NT, typename T>
 __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
     using O = Ops<T>;
@@ -550,7 +457,7 @@ __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
 // workgroup from the start; without one, workgroup b runs unit b.
 // ---------------------------------------------------------------------------
 template <int H, int NT, typename T>
-__global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_fwd(FwdArgs a) {
+__global__ void __launch_bounds__((64 * WIDE_WAVES)) k_wave_fwd(FwdArgs a) {
     for_units(a, [&](int unit) { wave_fwd_big<H, NT, T>(a, unit); });
 }
 
@@ -558,14 +465,14 @@ __global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_fwd(FwdArgs a) {
 // the queue costs it sixteen more spilled registers (wide batch 22.5 against
 // 21.7 ms).
 template <int H, int NT, typename T, bool QUEUE>
-__global__ void __launch_bounds__((64 * Geo<H, T>::NW)) k_wave_bwd(BwdArgs a) {
+__global__ void __launch_bounds__((64 * WIDE_WAVES)) k_wave_bwd(BwdArgs a) {
     if constexpr (QUEUE) for_units(a, [&](int unit) { wave_bwd_big<H, NT, T>(a, unit); });
     else wave_bwd_big<H, NT, T>(a, a.units[blockIdx.x]);
 }
 
 template <bool QUEUE>
 static WaveKernel wide_bwd_kernel(int nt) {
-    constexpr int th = 64 * Geo<128, bf16_t>::NW;
+    constexpr int th = 64 * WIDE_WAVES;
     switch (nt) {
         case 1: return {reinterpret_cast<const void*>(&k_wave_bwd<128, 1, bf16_t, QUEUE>), th};
         case 2: return {reinterpret_cast<const void*>(&k_wave_bwd<128, 2, bf16_t, QUEUE>), th};
@@ -601,7 +508,7 @@ static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
         case 32: return fwd_kernel_bf16_h32(nt, ck);
         case 64: return fwd_kernel_bf16_h64(nt, ck);
         case 128: {
-            constexpr int th = 64 * Geo<128, bf16_t>::NW;
+            constexpr int th = 64 * WIDE_WAVES;
             switch (nt) {
                 case 1: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 1, bf16_t>), th};
                 case 2: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 2, bf16_t>), th};

@@ -11,7 +11,8 @@
 //
 // An infinite value has no such form (inf - inf is NaN): operands that come
 // from outside (inputs, weights) are clamped to the largest bf16, which
-// saturates every gate the same way; NaN stays NaN.
+// saturates every gate the same way; NaN stays NaN. Gate gradients are not
+// clamped: an infinite one reaches its predecessors as NaN.
 #pragma once
 
 #include "common.hpp"
@@ -68,8 +69,9 @@ __device__ __forceinline__ void make_op(const float (&v)[8], bf16x8 (&o)[Pieces<
 // MFMAs on different accumulators. The products of fp32 pieces below the
 // leading one go to `low`: added there they are rounded at their own size, and
 // the leading sum takes one rounding per 32 reduction values (error of the
-// layer's output against 64 bits 1.7e-7 at H = 32, as with fp32 MFMAs; 2.1e-7
-// with one accumulator). Types of one piece leave `low` alone.
+// layer's output against 64 bits at H = 32, with the bias added afterwards:
+// 1.5e-7; 1.7e-7 on the fp32 MFMA, 2.1e-7 with one accumulator from the bias).
+// Types of one piece leave `low` alone.
 template <int P, int TILES, int KS>
 __device__ __forceinline__ void mma_tiles(const bf16x8 (&a)[TILES][KS][P], int ks, const bf16x8 (&b)[P],
                                           floatx4 (&acc)[TILES], floatx4 (&low)[TILES]) {

@@ -537,15 +537,15 @@ size_t fwd_x_bytes(const LayerGeom& g) {
 // output rows of the invalid cells, and the fp32 inputs of the rectangles'
 // cells as the wavefront reads them: three bf16 pieces, channels padded with
 // zeros to 32 CK, then 16 bytes whose first word says whether the cell is
-// valid. A workgroup takes 256 cells; it first lists the rectangles that meet
+// valid; a rectangle with an infinite input in a valid cell is flagged. A workgroup takes 256 cells; it first lists the rectangles that meet
 // them (rectangles are disjoint, so the list's order does not matter). Four
 // launches before (id fill, painting, pieces, zeroing): two small images 678 ->
 // 655 us through the three layers, word batch step 545 -> 528 us.
 constexpr int LAYOUT_LIST = 512;
 __global__ void __launch_bounds__(256)
-k_forward_layout(int n, const RectD* __restrict__ rects, int canvas_w, int64_t n_cells, int32_t* __restrict__ rid,
+k_forward_layout(int n, const RectD* __restrict__ rects, int canvas_w, int64_t n_cells, int32_t* rid,
                  const uint8_t* __restrict__ mask, unsigned* __restrict__ queue, uint2* __restrict__ y, int yrow_words,
-                 int c, int cp, const float* __restrict__ x, bf16_t* __restrict__ xs) {
+                 int c, int cp, const float* __restrict__ x, bf16_t* __restrict__ xs, int* __restrict__ xinf) {
     __shared__ int list[LAYOUT_LIST];
     __shared__ RectD listed[LAYOUT_LIST];
     __shared__ int count;
@@ -608,6 +608,10 @@ k_forward_layout(int n, const RectD* __restrict__ rects, int canvas_w, int64_t n
                 const floatx4 v0 = k < c ? St<float>::ld4(x + pc * c + k) : zero;
                 const floatx4 v1 = k + 4 < c ? St<float>::ld4(x + pc * c + k + 4) : zero;
                 const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                float m = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[e]));
+                if (m > F32_LARGEST && ids[cell] > 0) atomicOr(&xinf[rid[pc]], 1);
                 bf16x8 o[3];
                 make_op<float>(v, o);
 #pragma unroll
@@ -619,14 +623,14 @@ k_forward_layout(int n, const RectD* __restrict__ rects, int canvas_w, int64_t n
 
 hipError_t launch_forward_layout(const LayerGeom& g, int n, const int32_t* d_rects, int32_t* d_rid,
                                  const uint8_t* d_mask, unsigned* d_queue, void* d_y, const void* d_x, void* d_xs,
-                                 hipStream_t s) {
+                                 int* d_xinf, hipStream_t s) {
     const int cp = g.dtype == 0 ? 32 * fwd_fused_steps(g) : 0;
     const int yrow_words = 4 * g.hidden * (g.dtype == 1 ? 2 : 4) / 8;
     const int64_t blocks = std::min<int64_t>((g.n_cells + 255) / 256, 1 << 20);
     hipLaunchKernelGGL(k_forward_layout, dim3((unsigned)blocks), dim3(256), 0, s, n,
                        reinterpret_cast<const RectD*>(d_rects), g.canvas_w, g.n_cells, d_rid, d_mask, d_queue,
                        static_cast<uint2*>(d_y), yrow_words, g.c_in, cp, static_cast<const float*>(d_x),
-                       static_cast<bf16_t*>(cp > 0 ? d_xs : nullptr));
+                       static_cast<bf16_t*>(cp > 0 ? d_xs : nullptr), d_xinf);
     return hipGetLastError();
 }
 
@@ -653,7 +657,8 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
     const WaveKernel k = fwd_kernel_of(g, nt, t.v != nullptr);
     if (!k.fn) return hipErrorInvalidValue;
     const int groups = resident_groups(k);
-    FwdArgs a{d_units, d_rects, d_mask, t.u, t.v, t.wx, t.b, t.x, g.c_in, t.z, t.c, t.y, g.canvas_w, 0, INT_MAX,
+    FwdArgs a{d_units, d_rects, d_mask, t.u, t.v, t.wx, t.b, t.x, t.xf, t.xinf, g.c_in, t.z, t.c, t.y, g.canvas_w, 0,
+              INT_MAX,
               n_units > groups ? d_queue : nullptr, n_units};
     void* params[] = {&a};
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
@@ -713,7 +718,7 @@ hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, in
     if (e != hipSuccess) return e;
     hipGraphNode_t prev = nullptr;
     for (int st = 0; st < max_steps && e == hipSuccess; ++st) {
-        FwdArgs a{d_units, d_rects, d_mask, t.u, t.v,        t.wx, t.b,    t.x,     g.c_in,
+        FwdArgs a{d_units, d_rects, d_mask, t.u, t.v,        t.wx, t.b,    t.x,     t.xf, t.xinf, g.c_in,
                   t.z,     t.c,     t.y,    g.canvas_w, st, st + 1, nullptr, n_units};
         void* params[] = {&a};
         hipKernelNodeParams p{};

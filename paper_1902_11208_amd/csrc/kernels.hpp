@@ -59,6 +59,8 @@ struct FwdTensors {
     const void* wx;
     const void* b;
     const void* x;
+    const float* xf;  // fp32: the layer's own inputs
+    const int* xinf;  // fp32: launch_forward_layout's flag per rectangle
     void* z;
     float* c;
     void* y;
@@ -73,9 +75,11 @@ size_t fwd_x_bytes(const LayerGeom& g);
 // with n: above MAX_LAYOUT_RECTS rectangles callers run launch_rect_ids first
 // and pass n = -1 (the ids are in d_rid).
 constexpr int MAX_LAYOUT_RECTS = 4096;
+// d_xinf[rectangle] is set where a valid cell's input is infinite (fp32; zero on
+// entry).
 hipError_t launch_forward_layout(const LayerGeom& g, int n, const int32_t* d_rects, int32_t* d_rid,
                                  const uint8_t* d_mask, unsigned* d_queue, void* d_y, const void* d_x, void* d_xs,
-                                 hipStream_t s);
+                                 int* d_xinf, hipStream_t s);
 // Forward anti-diagonal wavefront over n_units units (rectangle, direction)
 // in the order of d_units. d_queue: two device counters, zero on entry (the
 // workgroups take units from the first, as many as are resident at once, and

@@ -139,7 +139,7 @@ bool same_shape(const mdlstm_layer_desc* a, const mdlstm_layer_desc& b) {
 }
 
 struct Plan {
-    size_t z, c, rid, rects, units, part, flags, wxt, dvpart, xs, queue, check, total;
+    size_t z, c, rid, rects, units, xinf, part, flags, wxt, dvpart, xs, queue, check, total;
 };
 
 mdl::LayerGeom geom(const mdlstm_layer_desc* d, int32_t ch, int32_t cw) {
@@ -169,6 +169,8 @@ Plan plan(const mdlstm_layer_desc* d, int32_t ch, int32_t cw, int32_t nr) {
     off += align_up((size_t)(nr > 0 ? nr : 1) * 16);
     p.units = off;
     off += align_up((size_t)(nr > 0 ? nr : 1) * 16);
+    p.xinf = off;  // per rectangle: one of its fp32 inputs is infinite
+    off += align_up((size_t)(nr > 0 ? nr : 1) * 4);
     p.part = off;
     const bool strip = mdl::strip_supported(g);
     off += align_up(strip ? mdl::strip_partial_bytes(g) : mdl::big_partial_bytes(g));
@@ -365,9 +367,9 @@ mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* 
         if (it != g_staged.end() && it->second == key) return MDLSTM_OK;
     }
     if (n_rects > 0) {
-        // rectangles and unit order in one copy (adjacent workspace sections)
+        // rectangles, unit order and zero flags in one copy (adjacent workspace sections)
         std::vector<int32_t> units = unit_order(n_rects, rects);
-        const size_t ubytes = units.size() * 4, span = c.p.units - c.p.rects + ubytes;
+        const size_t ubytes = units.size() * 4, span = c.p.xinf - c.p.rects + (size_t)n_rects * 4;
         std::vector<unsigned char> host(span, 0);
         std::memcpy(host.data(), rects, (size_t)n_rects * 16);
         std::memcpy(host.data() + (c.p.units - c.p.rects), units.data(), ubytes);
@@ -680,17 +682,20 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
     HIP_OR_FAIL(mark(0, s));
     int32_t* const rids = reinterpret_cast<int32_t*>(c.ws + c.p.rid);
     unsigned* const queue = reinterpret_cast<unsigned*>(c.ws + c.p.queue);
+    int* const xinf = reinterpret_cast<int*>(c.ws + c.p.xinf);
     int32_t n_layout = n_rects;
     if (n_rects > mdl::MAX_LAYOUT_RECTS) {  // ids painted rectangle by rectangle, and read from there
         HIP_OR_FAIL(mdl::launch_rect_ids(n_rects, drects, c.g.canvas_h, c.g.canvas_w, rids, queue, s));
         n_layout = -1;
     }
-    HIP_OR_FAIL(mdl::launch_forward_layout(c.g, n_layout, drects, rids, d_mask, queue, d_y, d_x, c.ws + c.p.xs, s));
+    HIP_OR_FAIL(mdl::launch_forward_layout(c.g, n_layout, drects, rids, d_mask, queue, d_y, d_x, c.ws + c.p.xs, xinf,
+                                           s));
     if (mdl::fwd_fused_steps(c.g) == 0)
         HIP_OR_FAIL(mdl::launch_projection(c.g, d_x, d_wx, d_b, rid, c.ws + c.p.z, s));
     const int64_t nu = 4 * (int64_t)c.g.hidden * 5 * 2 * c.g.hidden;  // floats of U before V
     const void* d_v = desc->memory_states ? static_cast<const float*>(d_u) + nu : nullptr;
-    const mdl::FwdTensors ft{d_u, d_v, d_wx, d_b, c.g.dtype == 0 ? c.ws + c.p.xs : d_x, c.ws + c.p.z, cs, d_y};
+    const mdl::FwdTensors ft{d_u, d_v, d_wx, d_b, c.g.dtype == 0 ? c.ws + c.p.xs : d_x,
+                             c.g.dtype == 0 ? static_cast<const float*>(d_x) : nullptr, xinf, c.ws + c.p.z, cs, d_y};
     HIP_OR_FAIL(mark(1, s));
     HIP_OR_FAIL(mark(2, s));
     if (!stepwise) {

@@ -2,17 +2,16 @@
 //
 // A float has 24 significant bits; hi = rne_bf16(v), mid = rne_bf16(v - hi),
 // lo = rne_bf16(v - hi - mid) carry 8 each (both differences are exact), so
-// v = hi + mid + lo up to 2^-26 |v|. Of the nine products of two such sums the
-// six largest are kept (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid); the
-// dropped ones are below 2^-25 of the product, less than its rounding to
-// fp32. They accumulate in fp32. One 16x16x32 bf16 MFMA takes 16 cycles, so 32
+// v = hi + mid + lo exactly (down to about 1e-33, where lo falls below bf16's
+// range). Of the nine products of two such sums the six largest are kept (hi
+// hi, hi mid, mid hi, hi lo, lo hi, mid mid); the dropped ones reach 2^-25 of
+// the product each, 2^-24 together: an ulp at most. They accumulate in fp32. One 16x16x32 bf16 MFMA takes 16 cycles, so 32
 // reduction values cost 96 cycles in this form against 256 as eight 16x16x4
 // fp32 MFMAs.
 //
-// An infinite value has no such form (inf - inf is NaN): operands that come
-// from outside (inputs, weights) are clamped to the largest bf16, which
-// saturates every gate the same way; NaN stays NaN. Gate gradients are not
-// clamped: an infinite one reaches its predecessors as NaN.
+// A finite value beyond the largest bf16 keeps its form with hi at that value.
+// An infinite one has none (its products are NaN whatever the sum is): a unit
+// that met one is run again without pieces (wave_plain.hpp).
 #pragma once
 
 #include "common.hpp"
@@ -28,7 +27,7 @@ struct Pieces<float> {
     static constexpr int N = 3;
 };
 
-// Two finite (or NaN) floats to packed pieces, first value in the low halves.
+// Two floats of at most the largest bf16 (or NaN) to packed pieces, first value in the low halves.
 __device__ __forceinline__ void split2(float a, float b, uint32_t (&p)[3]) {
     p[0] = f2bf2(a, b);
     a -= __uint_as_float(p[0] << 16);
@@ -39,10 +38,18 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t (&p)[3]) {
     p[2] = f2bf2(a, b);
 }
 
-// Values beyond the largest bf16 (infinities among them) to it.
-__device__ __forceinline__ float clamp_bf16(float v) {
-    constexpr float big = 3.3895313892515355e38f;
-    return v > big ? big : (v < -big ? -big : v);
+constexpr float BF16_LARGEST = 3.3895313892515355e38f, F32_LARGEST = 3.4028234663852886e38f;
+
+// As split2, for any values.
+__device__ __forceinline__ void split2_any(float a, float b, uint32_t (&p)[3]) {
+    auto lead = [](float v) { return v > BF16_LARGEST ? BF16_LARGEST : (v < -BF16_LARGEST ? -BF16_LARGEST : v); };
+    p[0] = f2bf2(lead(a), lead(b));
+    a -= __uint_as_float(p[0] << 16);
+    b -= __uint_as_float(p[0] & 0xffff0000u);
+    p[1] = f2bf2(a, b);
+    a -= __uint_as_float(p[1] << 16);
+    b -= __uint_as_float(p[1] & 0xffff0000u);
+    p[2] = f2bf2(a, b);
 }
 
 // Eight reduction values of one operand slot as MFMA operands.
@@ -53,7 +60,7 @@ __device__ __forceinline__ void make_op(const float (&v)[8], bf16x8 (&o)[Pieces<
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             uint32_t p[3];
-            split2(clamp_bf16(v[2 * e]), clamp_bf16(v[2 * e + 1]), p);
+            split2_any(v[2 * e], v[2 * e + 1], p);
 #pragma unroll
             for (int k = 0; k < 3; ++k) w[k][e] = p[k];
         }

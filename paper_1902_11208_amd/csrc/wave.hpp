@@ -78,6 +78,8 @@ struct FwdArgs {
     const void* wx;        // [4][5H][c_in]
     const void* b;         // [4][5H]
     const void* x;         // inputs per cell: bf16 [c_in], or the fp32 inputs as bf16 pieces [3][32 CK]
+    const float* xf;       // the fp32 inputs themselves
+    const int* xinf;       // per rectangle: one of its fp32 inputs is infinite (where x is pieces)
     int c_in;
     void* z;               // [n_cells][20H]: pre-activations in where the projection ran apart; gates out
     float* c;              // [n_cells][4H] cell state

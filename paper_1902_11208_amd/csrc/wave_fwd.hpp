@@ -42,6 +42,7 @@
 
 #include "kernels.hpp"
 #include "wave.hpp"
+#include "wave_plain.hpp"
 
 namespace mdl {
 
@@ -91,6 +92,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     __shared__ __attribute__((aligned(16))) bf16_t hop[2][P][ROWS][KP];
     // with memory-state matrices, the same operand rows of the cell states
     __shared__ __attribute__((aligned(16))) bf16_t cop[MEM ? 2 : 1][MEM ? P : 1][MEM ? ROWS : 1][KP];
+    __shared__ int plain;  // an infinite value was met
     __shared__ float cedge[2][NG][H];
     __shared__ __attribute__((aligned(16))) u32x4 ist[STAGE_IN ? 2 : 1][STAGE_IN ? NT * 16 * PI : 1];
     __shared__ __attribute__((aligned(16))) u32x4 ost[STAGE_OUT ? OBUF : 1][STAGE_OUT ? NT * 16 : 1][PF];
@@ -120,6 +122,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             reinterpret_cast<uint4*>(&cop[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
     if constexpr (NG > 1)
         for (int i = threadIdx.x; i < 2 * NG * H; i += NTH) (&cedge[0][0][0])[i] = 0.0f;
+    if (P == 3 && threadIdx.x == 0) plain = FUSED ? a.xinf[unit >> 2] : 0;
 
     // values (hidden outputs, cell states) of row yy, the lane's units -> operand
     // rows of the next diagonal
@@ -178,6 +181,13 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     // A operands, lane row n16 = 4 jj + e: tile r < WQ, gate e of unit
     // UW w + WQ jj + r; tile WQ, candidate of unit UW w + WQ jj + e.
     // Memory-state matrices: gates i, f_L, f_T of the sigmoid tiles (V rows).
+    float wmax = 0.0f;  // largest magnitude of the wave's fp32 weights, NaN left out
+    auto seen = [&](const float (&v)[8]) {
+        if constexpr (P == 3) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wmax = fmaxf(wmax, fabsf(v[e]));
+        }
+    };
     bf16x8 Ah[TILES][KS][P], Ax[TILES][FUSED ? CK : 1][P], Ac[MEM ? WQ : 1][MEM ? KS : 1][P];
     const T* const U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
     const T* const Wx = static_cast<const T*>(a.wx) + (int64_t)d * G * a.c_in;
@@ -196,6 +206,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             const bool in = ok && k < 2 * H;
             const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
             const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            seen(v);
             make_op<T>(v, Ah[t][ks]);
         }
         if constexpr (MEM) {
@@ -208,6 +219,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                     const bool in = e < 3 && k < 2 * H;
                     const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
                     const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                    seen(v);
                     make_op<T>(v, Ac[t < WQ ? t : 0][ks]);
                 }
             }
@@ -220,6 +232,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             const floatx4 v0 = ok && k < a.c_in ? St<T>::ld4(p) : zero;
             const floatx4 v1 = ok && k + 4 < a.c_in ? St<T>::ld4(p + 4) : zero;
             const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            seen(v);
             make_op<T>(v, Ax[t][ks]);
         }
     }
@@ -232,6 +245,9 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 bias[t][e] = t < WQ ? St<T>::ld1(Bd + e * H + u0 + t) : (e < WQ ? St<T>::ld1(Bd + 4 * H + u0 + e) : 0.0f);
     }
     __builtin_amdgcn_s_waitcnt(0);  // operands in registers before the step loop
+    // taken here, or the weights would live until its use at the end
+    const bool winf = P == 3 && __any(wmax > F32_LARGEST);
+    float cmax = 0.0f;  // largest cell state
 
     char* const sink = sink_ptr();
     const DiagMap M(R, d, a.canvas_w);
@@ -472,10 +488,8 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 ct[r] = row_above(cprev[lt][r], edge);
             }
             const bool in = yy >= ylo && yy <= yhi, live = in && mk != 0;
-            // With memory-state matrices the states feed the gates: there the
-            // library functions, as exact as the arithmetic around them.
-            auto sg = [](float z) { return MEM ? 1.0f / (1.0f + __expf(-z)) : sigm_fast(z); };
-            auto th = [](float z) { return MEM ? tanhf(z) : tanh_fast(z); };
+            auto sg = [](float z) { return cell_sigm<MEM>(z); };
+            auto th = [](float z) { return cell_tanh<MEM>(z); };
             float gv[5][WQ], hv[WQ], cv[WQ];
 #pragma unroll
             for (int r = 0; r < WQ; ++r) {
@@ -492,10 +506,9 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             }
             put(hop, cur, yy, hv);
             if constexpr (MEM) {
-                float cc[WQ];  // an overflowed state saturates its gates instead of becoming NaN pieces
 #pragma unroll
-                for (int r = 0; r < WQ; ++r) cc[r] = clamp_bf16(cv[r]);
-                put(cop, cur, yy, cc);
+                for (int r = 0; r < WQ; ++r) cmax = fmaxf(cmax, fabsf(cv[r]));
+                put(cop, cur, yy, cv);
             }
             if constexpr (NG > 1) {
                 if (lt == TPG - 1 && n16 == 15) {
@@ -524,6 +537,8 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
         if constexpr (AHEAD) start(s + 1, 0, nxt);
     };
 
+    // split2 keeps no cell states beyond the largest bf16
+    auto met = [&] { return winf || (MEM && cmax > BF16_LARGEST); };
     Set s0, s1;
     constexpr bool ONE = !STAGE_IN && !AHEAD;
     load(sb, s0);
@@ -551,6 +566,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             step(s, ONE ? s0 : s1, s0, std::true_type{});
             ++s;
         }
+        if (P == 3 && met()) plain = 1;
         lds_barrier();
         flush(se - 1);
     } else {
@@ -572,6 +588,13 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             step(s, ONE ? s0 : s1, s0, std::false_type{});
             if (++s >= se) break;
         }
+        if constexpr (P == 3) {
+            if (met()) plain = 1;
+            lds_barrier();
+        }
+    }
+    if constexpr (P == 3) {
+        if (__builtin_amdgcn_readfirstlane(plain)) plain_fwd_unit<H, MEM>(kern_args<FwdArgs>(), unit, sb, se);
     }
 }
 

@@ -635,8 +635,8 @@ hipError_t launch_forward_layout(const LayerGeom& g, int n, const int32_t* d_rec
 }
 
 // Workgroups of a kernel that the device holds at once (256 CUs assumed when
-// the query fails).
-static int resident_groups(const WaveKernel& k) {
+// the query fails), up to `most` on a CU.
+static int resident_groups(const WaveKernel& k, int most = INT_MAX) {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
@@ -647,7 +647,7 @@ static int resident_groups(const WaveKernel& k) {
         (void)hipGetLastError();
         per = 1;
     }
-    return cus * per;
+    return cus * std::min(per, most);
 }
 
 hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
@@ -690,19 +690,22 @@ static WaveKernel bwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
 }
 
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
-                                const int32_t* d_rects, const uint8_t* d_mask, const void* d_u, const void* d_v,
-                                const void* d_dy, void* d_z, const float* d_c, unsigned* d_queue, hipStream_t s) {
+                                const int32_t* d_rects, const uint8_t* d_mask, const BwdTensors& t, unsigned* d_queue,
+                                hipStream_t s) {
     if (n_units == 0) return hipSuccess;
-    WaveKernel k = bwd_kernel_of(g, nt, d_v != nullptr);
+    WaveKernel k = bwd_kernel_of(g, nt, t.v != nullptr);
     if (!k.fn) return hipErrorInvalidValue;
-    int groups = resident_groups(k);
+    // Two waves per SIMD at most: a third reads and writes more than the memory
+    // takes (word batch, fp32 H 16: 396 us with three, 355 with two; 128 images of
+    // 32 rows, bf16 H 32: 1314 and 1249).
+    int groups = resident_groups(k, std::max(1, 512 / k.threads));
     if (g.dtype == 1 && g.hidden == 128 && n_units <= 2 * groups) {  // one workgroup per CU is resident
         k = wide_bwd_kernel<false>(nt);
         groups = n_units;
     }
-    BwdArgs a{d_units, d_rects, d_mask, d_u,        d_v,
-              d_z,     d_c,     d_dy,   g.canvas_w, n_units > groups ? d_queue : nullptr,
-              n_units};
+    const float* xf = g.dtype == 0 ? static_cast<const float*>(t.x) : nullptr;
+    BwdArgs a{d_units, d_rects, d_mask, t.u, t.v, t.z, t.c, t.dy, t.wx, t.b, xf, g.c_in, t.y, g.canvas_w,
+              n_units > groups ? d_queue : nullptr, n_units};
     void* params[] = {&a};
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }

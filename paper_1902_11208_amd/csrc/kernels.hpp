@@ -96,9 +96,19 @@ hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, in
                                      hipGraphExec_t* exec);
 
 // --- backward --------------------------------------------------------------
+struct BwdTensors {
+    const void* u;
+    const void* v;  // memory-state matrices, or NULL
+    const void* wx;
+    const void* b;
+    const void* x;
+    const void* y;
+    const void* dy;
+    void* z;
+    const float* c;
+};
 hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
-                                const int32_t* d_rects, const uint8_t* d_mask, const void* d_u,
-                                const void* d_v, const void* d_dy, void* d_z, const float* d_c, unsigned* d_queue,
+                                const int32_t* d_rects, const uint8_t* d_mask, const BwdTensors& t, unsigned* d_queue,
                                 hipStream_t s);
 // Input and weight gradients as tiled MFMA products (any built shape), in
 // two launches: first a validity byte per cell (d_flags, n_cells bytes),

@@ -770,8 +770,8 @@ mdlstm_status backward_impl(const mdlstm_layer_desc* desc, int32_t canvas_h, int
     if (c.g.n_cells > 0)
         HIP_OR_FAIL(mdl::launch_wavefront_bwd(c.g, c.nt, 4 * n_rects,
                                               reinterpret_cast<const int32_t*>(c.ws + c.p.units),
-                                              reinterpret_cast<const int32_t*>(c.ws + c.p.rects), d_mask, d_u, d_v,
-                                              d_dy, c.ws + c.p.z, cs,
+                                              reinterpret_cast<const int32_t*>(c.ws + c.p.rects), d_mask,
+                                              {d_u, d_v, d_wx, d_b, d_x, d_y, d_dy, c.ws + c.p.z, cs},
                                               reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
     else if (desc->memory_states)
         HIP_OR_FAIL(mdl::launch_zero_f32(d_du + nu, nv, s));

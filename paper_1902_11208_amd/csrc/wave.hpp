@@ -90,6 +90,25 @@ struct FwdArgs {
     int n_units;
 };
 
+struct BwdArgs {
+    const int32_t* units;  // unit = rect*4 + direction, in launch order
+    const int32_t* rects;  // [n_rects][4]
+    const uint8_t* mask;   // [n_cells] (wide bf16 layers, plain_bwd_unit)
+    const void* u;         // [4][5H][2H]
+    const void* v;         // [4][3H][2H] memory-state matrices, or NULL
+    void* z;               // [n_cells][20H]: gates in (other layers: a masked cell's input gates are negative), dZ out
+    const float* c;        // [n_cells][4H] cell state
+    const void* dy;        // [n_cells][4H] upstream gradient
+    const void* wx;        // the forward's operands, for plain_bwd_unit
+    const void* b;
+    const float* xf;
+    int c_in;
+    const void* y;
+    int canvas_w;
+    unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
+    int n_units;
+};
+
 // Target of the stores of lanes whose cell is outside the diagonal: every lane
 // stores on every path, so the number of memory operations in flight is the
 // same on all paths and the compiler waits for exactly the loads it needs (a

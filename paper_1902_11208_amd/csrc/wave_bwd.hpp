@@ -31,22 +31,9 @@
 
 #include "kernels.hpp"
 #include "wave.hpp"
+#include "wave_plain.hpp"
 
 namespace mdl {
-
-struct BwdArgs {
-    const int32_t* units;  // unit = rect*4 + direction, in launch order
-    const int32_t* rects;  // [n_rects][4]
-    const uint8_t* mask;   // [n_cells] (wide bf16 layers)
-    const void* u;         // [4][5H][2H]
-    const void* v;         // [4][3H][2H] memory-state matrices, or NULL
-    void* z;               // [n_cells][20H]: gates in (other layers: a masked cell's input gates are negative), dZ out
-    const float* c;        // [n_cells][4H] cell state
-    const void* dy;        // [n_cells][4H] upstream gradient
-    int canvas_w;
-    unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
-    int n_units;
-};
 
 template <int H, int NT, typename T, int WQ, int NG, bool MEM>
 struct BwdK {
@@ -92,6 +79,8 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     __shared__ __attribute__((aligned(16))) u32x4 dzs[NB][P == 3 && STAGE ? NT * 16 : 1][PZ];
     __shared__ __attribute__((aligned(16))) u32x4 ist[NB][STAGE ? NT * 16 * PB : 1];
     // between tile groups: the top parts and dc f_T of a group's first row
+    __shared__ int plain;  // a gate gradient without pieces was met
+    static_assert(P == 1 || sizeof(dap) >= sizeof(float) * 4 * H * NT * 16, "scratch of plain_bwd_unit");
     __shared__ float gedge[NG][H], dedge[2][NG][H];
 
     const int lane = threadIdx.x & 63;
@@ -107,6 +96,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
 
     for (int i = threadIdx.x; i < (int)(sizeof(dap) / 16); i += NTH)
         reinterpret_cast<uint4*>(&dap[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
+    if (P == 3 && threadIdx.x == 0) plain = 0;
     if constexpr (NG > 1) {
         for (int i = threadIdx.x; i < NG * H; i += NTH) (&gedge[0][0])[i] = 0.0f;
         for (int i = threadIdx.x; i < 2 * NG * H; i += NTH) (&dedge[0][0][0])[i] = 0.0f;
@@ -156,6 +146,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
 
     // What the next diagonal (s - 1) takes over: the lane's own products (left
     // and top part), dc f_L, dc f_T, and the cell state of its own rows.
+    float dmax = 0.0f;  // fp32: the largest gate gradient, NaN left out
     float gl[TPG][WQ], gt[TPG][WQ], dcl[TPG][WQ], dct[TPG][WQ], co[TPG][WQ];
 #pragma unroll
     for (int lt = 0; lt < TPG; ++lt) {
@@ -298,6 +289,10 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
             da[2][r] = live ? dc * cT * gft * (1.0f - gft) : 0.0f;
             da[3][r] = live ? dh * tc * go * (1.0f - go) : 0.0f;
             da[4][r] = live ? dc * gi * (1.0f - gg * gg) : 0.0f;
+            if constexpr (P == 3) {
+#pragma unroll
+                for (int t = 0; t < 5; ++t) dmax = fmaxf(dmax, fabsf(da[t][r]));
+            }
             dcl[lt][r] = live ? dc * gfl : 0.0f;
             dct[lt][r] = live ? dc * gft : 0.0f;
         }
@@ -429,6 +424,12 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         if (--s < 0) break;
         step(s, STAGE ? s1 : s0);
         --s;
+    }
+    if constexpr (P == 3) {  // split2 keeps no values beyond the largest bf16
+        if (dmax > BF16_LARGEST) plain = 1;
+        lds_barrier();
+        if (__builtin_amdgcn_readfirstlane(plain))
+            plain_bwd_unit<H, MEM>(kern_args<BwdArgs>(), unit, reinterpret_cast<float*>(&dap[0][0][0][0]), NT * 16);
     }
 }
 

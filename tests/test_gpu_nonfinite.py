@@ -90,3 +90,35 @@ def test_overflowed_states_saturate_their_gates(H):
     gpu = gpu_run.run_layer(wl.examples(), params, None, hs, ws, 100, backward=False)
     for k in range(2):
         _same(f"Y[{k}]", gpu["Y"][k], ref["Y"][k], 1e-5)
+
+
+@pytest.mark.parametrize("H,C,mem,tall", [(8, 12, False, 60), (16, 24, False, 20), (32, 16, False, 40),
+                                          (64, 12, False, 9), (64, 68, False, 50), (16, 20, True, 33), (32, 8, True, 60)])
+def test_backward_with_infinite_gradients(H, C, mem, tall):
+    """Positive weights and inputs: an infinite upstream gradient makes every
+    gate gradient of its cell infinite with one sign, and of the cells before
+    it, up to those without a left or top predecessor (inf * 0)."""
+    import gpu_run
+    import oracle_run
+    from synth.configs import custom_workload
+
+    hs, ws = [tall, 3, 4], [7, 9, 5]
+    print(f"case infinite gradients H={H} C={C} memory={mem} h={tall}", flush=True)
+    wl = custom_workload(860 + H + C, hs, ws, 40, C, H)
+    xs = [np.abs(x) * 0.1 for x in wl.examples()]
+    params = [np.abs(p) * (0.3 / H) for p in wl.params()[:2]] + [wl.params()[2]]
+    params[2][:, H:3 * H], params[2][:, 4 * H:] = -1.0, 0.5
+    if mem:
+        params.append(np.abs(wl.memory_params()) * (0.3 / H))
+    dys = [wl.dy(k) for k in range(3)]
+    dys[0][tall // 2, 3, 1], dys[0][tall // 2, 3, 2 * H + 1] = np.inf, np.inf
+    dys[1][1, 4, H] = np.finfo(np.float32).max  # finite, but beyond the largest bf16
+    with np.errstate(all="ignore"):
+        ref = oracle_run.run_layer(xs, params, dys)
+    gpu = gpu_run.run_layer(xs, params, dys, hs, ws, 40)
+    assert np.isinf(ref["dX"][0]).any()
+    for k in (1, 2):
+        _same(f"dX[{k}]", gpu["dX"][k], ref["dX"][k], 1e-5)
+    _same("dX[0]", gpu["dX"][0], ref["dX"][0], 1e-5)
+    for nm in ("dWx", "dU", "db") + (("dV",) if mem else ()):
+        _same(nm, gpu[nm], ref[nm], 1e-5)

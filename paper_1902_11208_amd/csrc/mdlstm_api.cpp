@@ -356,16 +356,28 @@ StagedKey staged_key(const Common& c, int32_t n_rects, const mdlstm_rect* rects)
 std::mutex g_staged_mu;
 std::unordered_map<uintptr_t, StagedKey> g_staged;
 
+void set_staged(const Common& c, const StagedKey* key) {
+    const uintptr_t ws = reinterpret_cast<uintptr_t>(c.ws);
+    std::lock_guard<std::mutex> lock(g_staged_mu);
+    if (!key) {
+        g_staged.erase(ws);
+        return;
+    }
+    if (g_staged.size() >= 4096) g_staged.clear();  // bound the table; a miss only restages
+    g_staged[ws] = *key;
+}
+
 // A backward call stages the rectangle ids and zeroes the unit queue as well; a
-// forward call leaves both to launch_forward_layout.
+// forward call leaves both to launch_forward_layout, and the workspace counts
+// as staged (set_staged) only once that is enqueued.
 mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* rects, bool backward, hipStream_t s) {
     const StagedKey key = staged_key(c, n_rects, rects);
-    const uintptr_t ws = reinterpret_cast<uintptr_t>(c.ws);
     if (backward) {
         std::lock_guard<std::mutex> lock(g_staged_mu);
-        auto it = g_staged.find(ws);
+        auto it = g_staged.find(reinterpret_cast<uintptr_t>(c.ws));
         if (it != g_staged.end() && it->second == key) return MDLSTM_OK;
     }
+    set_staged(c, nullptr);
     if (n_rects > 0) {
         // rectangles, unit order and zero flags in one copy (adjacent workspace sections)
         std::vector<int32_t> units = unit_order(n_rects, rects);
@@ -375,13 +387,12 @@ mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* 
         std::memcpy(host.data() + (c.p.units - c.p.rects), units.data(), ubytes);
         HIP_OR_FAIL(hipMemcpyAsync(c.ws + c.p.rects, host.data(), span, hipMemcpyHostToDevice, s));
     }
-    if (backward)
+    if (backward) {
         HIP_OR_FAIL(mdl::launch_rect_ids(n_rects, reinterpret_cast<const int32_t*>(c.ws + c.p.rects), c.g.canvas_h,
-                                     c.g.canvas_w, reinterpret_cast<int32_t*>(c.ws + c.p.rid),
-                                     reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
-    std::lock_guard<std::mutex> lock(g_staged_mu);
-    if (g_staged.size() >= 4096) g_staged.clear();  // bound the table; a miss only restages
-    g_staged[ws] = key;
+                                         c.g.canvas_w, reinterpret_cast<int32_t*>(c.ws + c.p.rid),
+                                         reinterpret_cast<unsigned*>(c.ws + c.p.queue), s));
+        set_staged(c, &key);
+    }
     return MDLSTM_OK;
 }
 
@@ -664,6 +675,8 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
     if (c.g.n_cells > 0 && !d_y) return fail(MDLSTM_ERR_INVALID_ARG, "y is NULL");
     if (misaligned(d_y)) return fail(MDLSTM_ERR_INVALID_ARG, "y must be 16-byte aligned");
     if (c.g.n_cells == 0) return MDLSTM_OK;
+    if (desc->memory_states && stepwise)
+        return fail(MDLSTM_ERR_UNSUPPORTED, "the per-diagonal schedule is not built with memory-state matrices");
     hipStream_t s = as_stream(stream);
     if (poison_requested()) {
         // gates and cell states, and the gradient scratch the backward writes
@@ -677,8 +690,6 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
     const int32_t* units = reinterpret_cast<const int32_t*>(c.ws + c.p.units);
     const int32_t* drects = reinterpret_cast<const int32_t*>(c.ws + c.p.rects);
     float* cs = reinterpret_cast<float*>(c.ws + c.p.c);
-    if (desc->memory_states && stepwise)
-        return fail(MDLSTM_ERR_UNSUPPORTED, "the per-diagonal schedule is not built with memory-state matrices");
     HIP_OR_FAIL(mark(0, s));
     int32_t* const rids = reinterpret_cast<int32_t*>(c.ws + c.p.rid);
     unsigned* const queue = reinterpret_cast<unsigned*>(c.ws + c.p.queue);
@@ -690,6 +701,8 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
     }
     HIP_OR_FAIL(mdl::launch_forward_layout(c.g, n_layout, drects, rids, d_mask, queue, d_y, d_x, c.ws + c.p.xs, xinf,
                                            s));
+    const StagedKey key = staged_key(c, n_rects, rects);
+    set_staged(c, &key);
     if (mdl::fwd_fused_steps(c.g) == 0)
         HIP_OR_FAIL(mdl::launch_projection(c.g, d_x, d_wx, d_b, rid, c.ws + c.p.z, s));
     const int64_t nu = 4 * (int64_t)c.g.hidden * 5 * 2 * c.g.hidden;  // floats of U before V

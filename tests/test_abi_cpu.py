@@ -119,6 +119,19 @@ def test_forward_rejects_layouts(built_lib):
     assert b"workspace" in _lib().lib().mdlstm_last_error()
 
 
+def test_stepwise_refuses_memory_states_before_the_device(built_lib):
+    """The refusal comes before the layout is staged: the workspace must not
+    count as staged by a call that never wrote its ids and unit queue."""
+    L = _lib()
+    arr = (L.Rect * 1)(L.Rect(0, 0, 4, 5))
+    for hidden in (16, 10):  # a built shape, a padded one
+        desc = L.LayerDesc(8, hidden, 0, 1)
+        need = L.lib().mdlstm_workspace_bytes(ctypes.byref(desc), 4, 5, 1)
+        st = L.lib().mdlstm_forward_stepwise(ctypes.byref(desc), 4, 5, FAKE, FAKE, 1, arr, FAKE, FAKE, FAKE, FAKE,
+                                             FAKE, need, None)
+        assert st == 5 and b"per-diagonal" in L.lib().mdlstm_last_error(), (hidden, st)
+
+
 def test_workspace_bytes_scale():
     L = _lib()
     d = L.LayerDesc(16, 16, 0)

@@ -130,3 +130,33 @@ def test_memory_states_full_batch(cid):
     ref = oracle_run.run_layer(xs, params, dys, workers=oracle_run.default_workers(),
                                progress=f"workload {cid} oracle")
     _cmp(gpu, ref, f"workload {cid} with memory states")
+
+
+def test_refused_stepwise_leaves_the_workspace_usable():
+    """A per-diagonal call on a memory-state layer is refused; the forward and
+    backward after it on the same workspace give what they give without it."""
+    import gpu_run
+    from paper_1902_11208_amd import api
+    from synth.configs import custom_workload
+
+    hs, ws = [5, 18], [9, 30]
+    print("case refused stepwise call", flush=True)
+    wl = custom_workload(77, hs, ws, 40, 8, 16)
+    units, place, ch, cw, mask = gpu_run.layout(hs, ws, 40)
+    wx, u, b = (gpu_run.to_dev(p, "f32") for p in wl.params())
+    v = gpu_run.to_dev(wl.memory_params(), "f32")
+    x = api.pack_data([gpu_run.to_dev(e, "f32") for e in wl.examples()], place, ch, cw)
+    dy = api.pack_data([gpu_run.to_dev(wl.dy(k), "f32") for k in range(2)], place, ch, cw)
+    out = []
+    for refuse in (False, True):
+        layer = api.MDLSTMLayer(wx, u, b, ch, cw, units, mask, v=v)
+        if refuse:
+            with pytest.raises(Exception, match="per-diagonal"):
+                layer.forward_stepwise(x)
+        y = layer.forward(x).clone()
+        if refuse:
+            with pytest.raises(Exception, match="per-diagonal"):
+                layer.forward_stepwise(x)
+        out.append([y, *(t.clone() for t in layer.backward(dy))])
+    for a, c in zip(*out):
+        assert torch.equal(a, c)

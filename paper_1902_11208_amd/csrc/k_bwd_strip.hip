@@ -300,8 +300,9 @@ k_bwd_strip(int canvas_h, int canvas_w, int segs, int ngroups, int list_pitch, c
         // Validity, folded into the staged data: the dZ and X rows of an
         // invalid cell (outside every rectangle, masked, or past the row's
         // end) and every predecessor output that is not in the cell's
-        // rectangle or is masked become zero. Each predecessor segment (row,
-        // halo cell, direction) has one consumer cell.
+        // rectangle or is masked become zero, also those of invalid cells (cell
+        // states, staged in place of the outputs, are undefined out there). Each
+        // predecessor segment (row, halo cell, direction) has one consumer cell.
         // Lanes 0..TC-1 of every wave find the invalid cells (same ballot in every wave).
         bool cv = false;
         if (lane < TC) {
@@ -321,7 +322,7 @@ k_bwd_strip(int canvas_h, int canvas_w, int segs, int ngroups, int list_pitch, c
             const int row = lt ? ((dd & 2) ? 2 : 0) : 1;
             const int k = lt ? c + 1 : ((dd & 1) ? c + 2 : c);
             const int r = srid[1][c + 1];
-            if (!(srid[row][k] == r && smask[row][k])) {
+            if (!(r >= 0 && srid[row][k] == r && smask[row][k])) {
 #pragma unroll
                 for (int j = 0; j < H; j += 4) st_f4(&sy[row][k][dd * H + j], make_float4(0.f, 0.f, 0.f, 0.f));
             }
@@ -631,7 +632,9 @@ k_bwd_strip_dma(int canvas_h, int canvas_w, int segs, int ngroups, int list_pitc
         if (prev >= 0) dx_sum(prev);  // before the next barrier, after which this strip's partials overwrite sdx
         // validity folded into the staged data (as in the staged kernel): a
         // cell is valid with a nonnegative id, a predecessor counts when it is
-        // on the canvas and has the cell's id
+        // on the canvas and has the cell's id. Those of invalid cells are cleared
+        // too: in place of the outputs, zero there, the cell states may be staged,
+        // which nobody writes outside the rectangles.
         auto inside = [&](int row, int k) {
             const int yy = cy + row - 1, xx = cx0 + k - 1;
             return yy >= 0 && yy < canvas_h && xx >= 0 && xx < canvas_w;
@@ -649,7 +652,8 @@ k_bwd_strip_dma(int canvas_h, int canvas_w, int segs, int ngroups, int list_pitc
             const int c = e % TC, lt = (e / TC) & 1, dd = e / (2 * TC);
             const int row = lt ? ((dd & 2) ? 2 : 0) : 1;
             const int k = lt ? c + 1 : ((dd & 1) ? c + 2 : c);
-            if (!(inside(row, k) && vb[row * HW + k] == vb[HW + c + 1])) {
+            const int id = vb[HW + c + 1];
+            if (!(id >= 0 && inside(row, k) && vb[row * HW + k] == id)) {
 #pragma unroll
                 for (int j = 0; j < H; j += 4)
                     st_f4(&yb[(row * HW + k) * (4 * H) + dd * H + j], make_float4(0.f, 0.f, 0.f, 0.f));

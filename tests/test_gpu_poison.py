@@ -46,6 +46,9 @@ CASES = [
     ("f32_H64", [7, 20], [30, 11], 32, 16, 64, "f32", False),
     ("bf16_H128", [9, 30, 2], [40, 12, 7], 48, 64, 128, "bf16", False),
     ("f32_H16_memory", [16, 9, 30], [40, 25, 17], 64, 16, 16, "f32", True),
+    ("f32_H32_memory", [16, 9, 30], [40, 25, 17], 64, 16, 32, "f32", True),
+    ("f32_H32_memory_C32", [16, 9, 30], [40, 25, 17], 64, 32, 32, "f32", True),
+    ("f32_H32_memory_C20", [16, 9, 30], [40, 25, 17], 64, 20, 32, "f32", True),
 ]
 
 

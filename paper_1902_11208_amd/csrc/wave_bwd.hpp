@@ -118,6 +118,11 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         const int o = 4 * t + (n16 & 3), ub = K::UW * w + WQ * (n16 >> 2);
         const bool ok = o < K::OUTS, state = MEM && o >= 2 * WQ;
         const int ol = state ? o - 2 * WQ : o;
+        // A piece MFMA's mean error is a little below zero (some 5e-11 of the sum's
+        // size). With the top parts computed negated, those of a cell's two shares
+        // cancel instead of adding up along the diagonals (gate gradients of the word
+        // batch, summed per gate: 1.6e-7 off, 8.6e-8 this way, 8.5e-8 on the fp32 MFMA).
+        const bool top = P == 3 && ol >= WQ;
         const int col = !ok ? 0 : ol < WQ ? ub + ol : H + ub + ol - WQ;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -132,6 +137,10 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
                                : 0.0f;
                 else
                     v[e] = ok && k < G ? St<T>::ld1(U + (int64_t)row * 2 * H + col) : 0.0f;
+            }
+            if (top) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = -v[e];
             }
             make_op<T>(v, A[t][ks]);
         }
@@ -379,9 +388,9 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
             for (int o = 0; o < K::OUTS; ++o) {
                 const float v = P == 3 ? acc[o >> 2][o & 3] + low[o >> 2][o & 3] : acc[o >> 2][o & 3];
                 if (o < WQ) gl[lt][o % WQ] = v;
-                else if (o < 2 * WQ) gt[lt][o % WQ] = v;
+                else if (o < 2 * WQ) gt[lt][o % WQ] = P == 3 ? -v : v;
                 else if (o < 3 * WQ) dcl[lt][o % WQ] += v;  // the states' share of dc
-                else dct[lt][o % WQ] += v;
+                else dct[lt][o % WQ] += P == 3 ? -v : v;
             }
             if constexpr (NG > 1) {
                 if (lt == 0 && n16 == 0) {

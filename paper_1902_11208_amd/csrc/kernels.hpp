@@ -12,6 +12,7 @@ struct LayerGeom {
     int c_in, hidden, dtype;  // dtype: 0 fp32, 1 bf16
     int canvas_h, canvas_w;
     int64_t n_cells;          // canvas_h * canvas_w
+    int memory;               // memory-state matrices
 };
 
 // --- packing -------------------------------------------------------------
@@ -114,15 +115,16 @@ hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const i
 // two launches: first a validity byte per cell (d_flags, n_cells bytes),
 // Wx_all transposed (d_wxt) and the input gradient; then the weight
 // gradients from chunk partials (d_part) summed in a fixed order (it reads
-// the validity bytes of the first).
+// the validity bytes of the first), with memory-state matrices dV from the cell
+// states d_c too.
 size_t big_flags_bytes(const LayerGeom& g);
 size_t big_wxt_bytes(const LayerGeom& g);
 size_t big_partial_bytes(const LayerGeom& g);
 hipError_t launch_bwd_big_dx(const LayerGeom& g, const void* d_dz, const void* d_wx, const uint8_t* d_mask,
                              const int32_t* d_rid, void* d_dx, uint8_t* d_flags, void* d_wxt, hipStream_t s);
 hipError_t launch_bwd_big_dw(const LayerGeom& g, const void* d_dz, const void* d_x, const void* d_y,
-                             const uint8_t* d_flags, float* d_part, float* d_dwx, float* d_du, float* d_db,
-                             hipStream_t s);
+                             const float* d_c, const uint8_t* d_flags, float* d_part, float* d_dwx, float* d_du,
+                             float* d_db, float* d_dv, hipStream_t s);
 // Input and weight gradients together, staged through LDS by canvas-row
 // strips (the shapes strip_supported lists). d_vid: strip_vid_bytes of
 // workspace for a validity id per cell.

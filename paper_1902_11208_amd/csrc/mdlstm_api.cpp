@@ -150,6 +150,7 @@ mdl::LayerGeom geom(const mdlstm_layer_desc* d, int32_t ch, int32_t cw) {
     g.canvas_h = ch;
     g.canvas_w = cw;
     g.n_cells = (int64_t)ch * cw;
+    g.memory = d->memory_states;
     return g;
 }
 
@@ -178,8 +179,8 @@ Plan plan(const mdlstm_layer_desc* d, int32_t ch, int32_t cw, int32_t nr) {
     off += align_up(strip ? mdl::strip_vid_bytes(g) : mdl::big_flags_bytes(g));
     p.wxt = off;
     off += strip ? 0 : align_up(mdl::big_wxt_bytes(g));
-    p.dvpart = off;  // memory-state matrices: weight gradients of the pass that gives dV
-    off += d->memory_states ? align_up(4 * 5 * H * (d->c_in + 2 * H + 1) * 4) : 0;
+    p.dvpart = off;  // memory-state matrices, strip path: weight gradients of the pass that gives dV
+    off += d->memory_states && strip ? align_up(4 * 5 * H * (d->c_in + 2 * H + 1) * 4) : 0;
     p.xs = off;  // fp32 inputs as the forward wavefront reads them
     off += align_up(mdl::fwd_x_bytes(g));
     p.queue = off;  // unit queue: next unit, workgroups done
@@ -790,10 +791,10 @@ mdlstm_status backward_impl(const mdlstm_layer_desc* desc, int32_t canvas_h, int
         HIP_OR_FAIL(mdl::launch_zero_f32(d_du + nu, nv, s));
     HIP_OR_FAIL(mark(5, s));
     // With memory-state matrices dV is the same product as dU with the cell
-    // states in place of the outputs: the weight-gradient kernel runs a second
-    // time on them (word batch of 128: 75 us, against 63 us for summing
-    // per-unit partials plus their products inside the backward wavefront,
-    // 646 -> 250 us without them), and the rows of i, f_L and f_T are kept.
+    // states in place of the outputs. The strip kernel runs a second time on them
+    // (word batch of 128: 75 us, against 63 us for summing per-unit partials plus
+    // their products inside the backward wavefront, 646 -> 250 us without them),
+    // and the rows of i, f_L and f_T are kept; the tiled products take both at once.
     float* const s_dwx = reinterpret_cast<float*>(c.ws + c.p.dvpart);
     float* const s_du = s_dwx + 4 * (int64_t)5 * c.g.hidden * c.g.c_in;
     float* const s_db = s_du + nu;
@@ -803,21 +804,22 @@ mdlstm_status backward_impl(const mdlstm_layer_desc* desc, int32_t canvas_h, int
         HIP_OR_FAIL(mdl::launch_bwd_strip(c.g, c.ws + c.p.z, d_x, d_y, d_wx, d_mask, rid,
                                           reinterpret_cast<int32_t*>(c.ws + c.p.flags), d_dx,
                                           reinterpret_cast<float*>(c.ws + c.p.part), d_dwx, d_du, d_db, s));
-        if (desc->memory_states)
+        if (desc->memory_states) {
             HIP_OR_FAIL(mdl::launch_bwd_strip(c.g, c.ws + c.p.z, d_x, cs, d_wx, d_mask, rid,
                                               reinterpret_cast<int32_t*>(c.ws + c.p.flags), d_dx,
                                               reinterpret_cast<float*>(c.ws + c.p.part), s_dwx, s_du, s_db, s));
+            HIP_OR_FAIL(mdl::launch_remap(s_du, d_du + nu, 4, 4, 1, 5 * c.g.hidden, 3 * c.g.hidden, 1, 2 * c.g.hidden,
+                                          2 * c.g.hidden, s));
+        }
     } else {
         // tiled products: the input gradient (boundary 6), then the weight gradients
         if (c.g.n_cells > 0) {
             uint8_t* flags = reinterpret_cast<uint8_t*>(c.ws + c.p.flags);
             HIP_OR_FAIL(mdl::launch_bwd_big_dx(c.g, c.ws + c.p.z, d_wx, d_mask, rid, d_dx, flags, c.ws + c.p.wxt, s));
             HIP_OR_FAIL(mark(6, s));
-            HIP_OR_FAIL(mdl::launch_bwd_big_dw(c.g, c.ws + c.p.z, d_x, d_y, flags,
-                                               reinterpret_cast<float*>(c.ws + c.p.part), d_dwx, d_du, d_db, s));
-            if (desc->memory_states)
-                HIP_OR_FAIL(mdl::launch_bwd_big_dw(c.g, c.ws + c.p.z, d_x, cs, flags,
-                                                   reinterpret_cast<float*>(c.ws + c.p.part), s_dwx, s_du, s_db, s));
+            HIP_OR_FAIL(mdl::launch_bwd_big_dw(c.g, c.ws + c.p.z, d_x, d_y, cs, flags,
+                                               reinterpret_cast<float*>(c.ws + c.p.part), d_dwx, d_du, d_db,
+                                               d_du + nu, s));
         } else {
             HIP_OR_FAIL(mark(6, s));
             HIP_OR_FAIL(mdl::launch_zero_f32(d_dwx, (int64_t)4 * 5 * c.g.hidden * c.g.c_in, s));
@@ -825,9 +827,6 @@ mdlstm_status backward_impl(const mdlstm_layer_desc* desc, int32_t canvas_h, int
             HIP_OR_FAIL(mdl::launch_zero_f32(d_db, (int64_t)4 * 5 * c.g.hidden, s));
         }
     }
-    if (c.g.n_cells > 0 && desc->memory_states)
-        HIP_OR_FAIL(mdl::launch_remap(s_du, d_du + nu, 4, 4, 1, 5 * c.g.hidden, 3 * c.g.hidden, 1, 2 * c.g.hidden,
-                                      2 * c.g.hidden, s));
     HIP_OR_FAIL(mark(7, s));
     return MDLSTM_OK;
 }

@@ -656,7 +656,7 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
     if (n_units == 0) return hipSuccess;
     const WaveKernel k = fwd_kernel_of(g, nt, t.v != nullptr);
     if (!k.fn) return hipErrorInvalidValue;
-    const int groups = resident_groups(k);
+    const int groups = resident_groups(k, std::max(1, 512 / k.threads));  // as in the backward
     FwdArgs a{d_units, d_rects, d_mask, t.u, t.v, t.wx, t.b, t.x, t.xf, t.xinf, g.c_in, t.z, t.c, t.y, g.canvas_w, 0,
               INT_MAX,
               n_units > groups ? d_queue : nullptr, n_units};

@@ -67,7 +67,8 @@ struct BwdK {
     static_assert(!MEM || (NG == 1 && P == 3), "memory-state matrices: fp32, one tile group");
 };
 
-template <int H, int NT, typename T, int WQ, int NG, bool MEM>
+// TA: the group's tiles that hold rows of the rectangle.
+template <int H, int NT, typename T, int WQ, int NG, bool MEM, int TA>
 __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     using K = BwdK<H, NT, T, WQ, NG, MEM>;
     constexpr int P = K::P, NWU = K::NWU, TPG = K::TPG, KS = K::KS, KP = K::KP, OT = K::OT, NTH = K::NTH;
@@ -75,16 +76,22 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     constexpr bool STAGE = K::STAGE, DB = K::DB;
     constexpr int G = 5 * H;
     using V = Vec<T, WQ>;
-    __shared__ __attribute__((aligned(16))) bf16_t dap[NB][P][NT * 16][KP];
-    __shared__ __attribute__((aligned(16))) u32x4 dzs[NB][P == 3 && STAGE ? NT * 16 : 1][PZ];
-    __shared__ __attribute__((aligned(16))) u32x4 ist[NB][STAGE ? NT * 16 * PB : 1];
+    auto& dap = lds_array<bf16_t[NB][P][NT * 16][KP], K, 0>();
+    auto& dzs = lds_array<u32x4[NB][P == 3 && STAGE ? NT * 16 : 1][PZ], K, 1>();
+    auto& ist = lds_array<u32x4[NB][STAGE ? NT * 16 * PB : 1], K, 2>();
     // between tile groups: the top parts and dc f_T of a group's first row
-    __shared__ int plain;  // a gate gradient without pieces was met
+    int& plain = lds_array<int, K, 3>();  // a gate gradient without pieces was met
     static_assert(P == 1 || sizeof(dap) >= sizeof(float) * 4 * H * NT * 16, "scratch of plain_bwd_unit");
-    __shared__ float gedge[NG][H], dedge[2][NG][H];
+    auto& gedge = lds_array<float[NG][H], K, 4>();
+    auto& dedge = lds_array<float[2][NG][H], K, 5>();
 
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int tid = threadIdx.x;
+    // Opaque, or addresses that follow from it would be computed ahead of the
+    // bodies and of the unit queue's loop and hold registers in all of them (fp32
+    // H 64, 48 rows: 70 -> 13 spilled, 6.6 -> 5.6 ms).
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tg = NG == 1 ? 0 : wv / NWU, w = NG == 1 ? wv : wv % NWU;
     const int q = lane >> 4, n16 = lane & 15;
     const int u0 = K::UW * w + WQ * q;
@@ -94,12 +101,12 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     T* const Z = static_cast<T*>(a.z);
     const T* const DY = static_cast<const T*>(a.dy);
 
-    for (int i = threadIdx.x; i < (int)(sizeof(dap) / 16); i += NTH)
+    for (int i = tid; i < (int)(sizeof(dap) / 16); i += NTH)
         reinterpret_cast<uint4*>(&dap[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
-    if (P == 3 && threadIdx.x == 0) plain = 0;
+    if (P == 3 && tid == 0) plain = 0;
     if constexpr (NG > 1) {
-        for (int i = threadIdx.x; i < NG * H; i += NTH) (&gedge[0][0])[i] = 0.0f;
-        for (int i = threadIdx.x; i < 2 * NG * H; i += NTH) (&dedge[0][0][0])[i] = 0.0f;
+        for (int i = tid; i < NG * H; i += NTH) (&gedge[0][0])[i] = 0.0f;
+        for (int i = tid; i < 2 * NG * H; i += NTH) (&dedge[0][0][0])[i] = 0.0f;
     }
 
     // Order of da along an operand row. Three pieces: (unit, sigmoid gate),
@@ -156,9 +163,10 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     // What the next diagonal (s - 1) takes over: the lane's own products (left
     // and top part), dc f_L, dc f_T, and the cell state of its own rows.
     float dmax = 0.0f;  // fp32: the largest gate gradient, NaN left out
-    float gl[TPG][WQ], gt[TPG][WQ], dcl[TPG][WQ], dct[TPG][WQ], co[TPG][WQ];
+    constexpr int TN = TA > 0 ? TA : 1;  // sizes of the tiles' registers
+    float gl[TN][WQ], gt[TN][WQ], dcl[TN][WQ], dct[TN][WQ], co[TN][WQ];
 #pragma unroll
-    for (int lt = 0; lt < TPG; ++lt) {
+    for (int lt = 0; lt < TA; ++lt) {
         const int yy = 16 * (tg * TPG + lt) + n16;
         const int yc = min(max(yy, max(0, steps - R.w)), R.h - 1);  // a row of the last diagonal
         const float* cp = cb + (int64_t)(M.sx * (steps - 1) + yc * M.ky) * (4 * H) + u0;
@@ -179,10 +187,10 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     constexpr int NIT = (NT * 16 + RPI - 1) / RPI;
     struct Set {
         u32x4 v[STAGE ? NIT : 1];
-        typename V::R g[STAGE ? 1 : TPG][5], dy[STAGE ? 1 : TPG];
-        typename Vec<float, WQ>::R cl[STAGE ? 1 : TPG], ct[STAGE ? 1 : TPG];
+        typename V::R g[STAGE ? 1 : TN][5], dy[STAGE ? 1 : TN];
+        typename Vec<float, WQ>::R cl[STAGE ? 1 : TN], ct[STAGE ? 1 : TN];
     };
-    const int it0 = (int)threadIdx.x % (RPI * QF), ic0 = it0 / QF, ir = it0 - ic0 * QF;
+    const int it0 = tid % (RPI * QF), ic0 = it0 / QF, ir = it0 - ic0 * QF;
     const int back = ir >= QZ + QY ? 1 : 0;
     const char* const ibase = ir < QZ        ? reinterpret_cast<const char*>(zb) + 16 * ir
                               : ir < QZ + QY ? reinterpret_cast<const char*>(dyb) + 16 * (ir - QZ)
@@ -231,7 +239,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     // non-temporal stores took 233 us on the word batch, these 217).
     constexpr int RPF = STAGE ? (NTH / QZ < NT * 16 ? NTH / QZ : NT * 16) : 1;
     constexpr int NITF = (NT * 16 + RPF - 1) / RPF;
-    const int ft0 = (int)threadIdx.x % (RPF * QZ), fc0 = ft0 / QZ, fr = ft0 - fc0 * QZ;
+    const int ft0 = tid % (RPF * QZ), fc0 = ft0 / QZ, fr = ft0 - fc0 * QZ;
     char* const fbase = reinterpret_cast<char*>(zb) + 16 * fr;
     auto flush = [&](int s) {
         if constexpr (STAGE) {
@@ -345,15 +353,15 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         // From the top: a tile's bottom edge is the first row of the tile
         // below it, of the previous diagonal.
 #pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
+        for (int lt = 0; lt < TA; ++lt) {
             float gtv[WQ], dtv[WQ];
 #pragma unroll
             for (int r = 0; r < WQ; ++r) {
                 float eg = 0.0f, ed = 0.0f;
-                if (lt + 1 < TPG) {
-                    eg = first_to_last(gt[lt + 1 < TPG ? lt + 1 : 0][r]);
-                    ed = first_to_last(dct[lt + 1 < TPG ? lt + 1 : 0][r]);
-                } else if (NG > 1 && tg + 1 < NG) {
+                if (lt + 1 < TA) {
+                    eg = first_to_last(gt[lt + 1 < TA ? lt + 1 : 0][r]);
+                    ed = first_to_last(dct[lt + 1 < TA ? lt + 1 : 0][r]);
+                } else if (NG > 1 && TA == TPG && tg + 1 < NG) {
                     eg = gedge[tg + 1 < NG ? tg + 1 : 0][u0 + r];
                     ed = dedge[(s & 1) ^ 1][tg + 1 < NG ? tg + 1 : 0][u0 + r];
                 }
@@ -371,7 +379,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         }
         lds_barrier();  // da of the diagonal written
 #pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
+        for (int lt = 0; lt < TA; ++lt) {
             const int yy = 16 * (tg * TPG + lt) + n16;
             floatx4 acc[OT], low[OT];
 #pragma unroll
@@ -417,7 +425,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         load(steps - 2 - NB, s1);
     } else {
 #pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) load_tile(steps - 1, lt, s0);
+        for (int lt = 0; lt < TA; ++lt) load_tile(steps - 1, lt, s0);
     }
     lds_barrier();
     // two steps ahead of the loop: it is entered with the memory operations in
@@ -445,7 +453,18 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
 template <int H, int NT, typename T, int WQ, int NG, bool MEM>
 __global__ void __launch_bounds__((BwdK<H, NT, T, WQ, NG, MEM>::NTH))
 __attribute__((amdgpu_waves_per_eu(BwdK<H, NT, T, WQ, NG, MEM>::WPE))) k_bwd(BwdArgs a) {
-    for_units(a, [&](int unit) { bwd_unit<H, NT, T, WQ, NG, MEM>(a, unit); });
+    using K = BwdK<H, NT, T, WQ, NG, MEM>;
+    if constexpr (NT == 1) {
+        for_units(a, [&](int unit) { bwd_unit<H, NT, T, WQ, NG, MEM, 1>(a, unit); });
+    } else {
+        for_units(a, [&](int unit) {
+            const int rows = reinterpret_cast<const RectD*>(a.rects)[unit >> 2].h;
+            const int tg = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) / K::NWU;
+            with_tiles<K::TPG, NG == 1 ? 1 : 0>((rows + 15) / 16 - tg * K::TPG, [&](auto ta) {
+                bwd_unit<H, NT, T, WQ, NG, MEM, decltype(ta)::value>(a, unit);
+            });
+        });
+    }
 }
 
 template <int H, int NT, typename T, int WQ, int NG, bool MEM = false>

@@ -80,7 +80,8 @@ struct FwdK {
     static_assert(H % UW == 0 && NT % NG == 0 && NTH <= 1024, "wave split");
 };
 
-template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
+// TA: the group's tiles that hold rows of the rectangle.
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM, int TA>
 __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     using K = FwdK<H, NT, T, CK, WQ, NG, MEM>;
     constexpr int P = K::P, NWU = K::NWU, TPG = K::TPG, KS = K::KS, KP = K::KP, TILES = K::TILES, NTH = K::NTH;
@@ -88,18 +89,25 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     constexpr int OBUF = K::OBUF, PI = K::PI, QI = K::QI, PF = K::PF, QF = K::QF, QZ = K::QZ, QY = K::QY;
     constexpr int G = 5 * H, ROWS = NT * 16 + 1, CP = 32 * CK;
     constexpr bool FUSED = CK > 0;
+    constexpr int TN = TA > 0 ? TA : 1;  // sizes of the tiles' registers
     using V = Vec<T, WQ>;
-    __shared__ __attribute__((aligned(16))) bf16_t hop[2][P][ROWS][KP];
+    auto& hop = lds_array<bf16_t[2][P][ROWS][KP], K, 0>();
     // with memory-state matrices, the same operand rows of the cell states
-    __shared__ __attribute__((aligned(16))) bf16_t cop[MEM ? 2 : 1][MEM ? P : 1][MEM ? ROWS : 1][KP];
-    __shared__ int plain;  // an infinite value was met
-    __shared__ float cedge[2][NG][H];
-    __shared__ __attribute__((aligned(16))) u32x4 ist[STAGE_IN ? 2 : 1][STAGE_IN ? NT * 16 * PI : 1];
-    __shared__ __attribute__((aligned(16))) u32x4 ost[STAGE_OUT ? OBUF : 1][STAGE_OUT ? NT * 16 : 1][PF];
-    __shared__ uint32_t mst[2][STAGE_IN && !(FUSED && P == 3) ? NTH : 1];
+    auto& cop = lds_array<bf16_t[MEM ? 2 : 1][MEM ? P : 1][MEM ? ROWS : 1][KP], K, 1>();
+    int& plain = lds_array<int, K, 2>();  // an infinite value was met
+    auto& cedge = lds_array<float[2][NG][H], K, 3>();
+    auto& ist = lds_array<u32x4[STAGE_IN ? 2 : 1][STAGE_IN ? NT * 16 * PI : 1], K, 4>();
+    auto& ost = lds_array<u32x4[STAGE_OUT ? OBUF : 1][STAGE_OUT ? NT * 16 : 1][PF], K, 5>();
+    auto& mst = lds_array<uint32_t[2][STAGE_IN && !(FUSED && P == 3) ? NTH : 1], K, 6>();
 
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int tid = threadIdx.x;
+    // Opaque, or addresses that follow from it would be computed ahead of the
+    // bodies and of the unit queue's loop and hold registers in all of them (fp32
+    // H 32, 48 rows: 1150 -> 1075 us; not so with fp32 H 64 and four tiles, 4170
+    // instead of 3480, whose loop leaves no registers for computing them again).
+    if constexpr (!(H == 64 && NT == 4 && P == 3)) asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tg = NG == 1 ? 0 : wv / NWU, w = NG == 1 ? wv : wv % NWU;
     const int q = lane >> 4, n16 = lane & 15;
     const int u0 = K::UW * w + WQ * q;
@@ -115,14 +123,14 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     T* const Y = static_cast<T*>(a.y);
     float* const Cs = a.c;
 
-    for (int i = threadIdx.x; i < (int)(sizeof(hop) / 16); i += NTH)
+    for (int i = tid; i < (int)(sizeof(hop) / 16); i += NTH)
         reinterpret_cast<uint4*>(&hop[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
     if constexpr (MEM)
-        for (int i = threadIdx.x; i < (int)(sizeof(cop) / 16); i += NTH)
+        for (int i = tid; i < (int)(sizeof(cop) / 16); i += NTH)
             reinterpret_cast<uint4*>(&cop[0][0][0][0])[i] = make_uint4(0, 0, 0, 0);
     if constexpr (NG > 1)
-        for (int i = threadIdx.x; i < 2 * NG * H; i += NTH) (&cedge[0][0][0])[i] = 0.0f;
-    if (P == 3 && threadIdx.x == 0) plain = FUSED ? a.xinf[unit >> 2] : 0;
+        for (int i = tid; i < 2 * NG * H; i += NTH) (&cedge[0][0][0])[i] = 0.0f;
+    if (P == 3 && tid == 0) plain = FUSED ? a.xinf[unit >> 2] : 0;
 
     // values (hidden outputs, cell states) of row yy, the lane's units -> operand
     // rows of the next diagonal
@@ -148,16 +156,16 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
         }
     };
 
-    float cprev[TPG][WQ];  // cell states of the lane's rows on the previous diagonal
+    float cprev[TN][WQ];  // cell states of the lane's rows on the previous diagonal
 #pragma unroll
-    for (int lt = 0; lt < TPG; ++lt)
+    for (int lt = 0; lt < TA; ++lt)
 #pragma unroll
         for (int r = 0; r < WQ; ++r) cprev[lt][r] = 0.0f;
     if (sb > 0) {
         lds_barrier();  // every zero written before the read-back fills the same rows
         const int pb = (sb & 1) ^ 1;
 #pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
+        for (int lt = 0; lt < TA; ++lt) {
             const int yy = 16 * (tg * TPG + lt) + n16, xx = sb - 1 - yy;
             if (yy < R.h && xx >= 0 && xx < R.w) {
                 const int64_t p = canvas_index(R, d, yy, xx, a.canvas_w) * (4 * H) + d * H + u0;
@@ -268,13 +276,13 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     struct Set {
         u32x4 v[STAGE_IN ? NIT : 1];
         uint32_t mb;
-        u32x4 x[TPG][!STAGE_IN && FUSED ? CK * P : 1];
-        typename V::R z[TPG][!STAGE_IN && !FUSED ? 5 : 1];
-        uint32_t m[TPG];
+        u32x4 x[TN][!STAGE_IN && FUSED ? CK * P : 1];
+        typename V::R z[TN][!STAGE_IN && !FUSED ? 5 : 1];
+        uint32_t m[TN];
     };
     constexpr int ZROW = 4 * G * (int)sizeof(T);
     const int irow = FUSED ? 2 * xrow : ZROW;
-    const int it0 = (int)threadIdx.x % (RPI * QI), ic0 = it0 / QI, ir = it0 - ic0 * QI;
+    const int it0 = tid % (RPI * QI), ic0 = it0 / QI, ir = it0 - ic0 * QI;
     const bool iok = !(FUSED && P == 1) || 8 * ir < a.c_in;
     const char* const ibase = (FUSED ? reinterpret_cast<const char*>(xb) : reinterpret_cast<const char*>(zb)) +
                               (iok ? 16 * ir : 0);
@@ -314,10 +322,10 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 in.v[it] = *reinterpret_cast<const u32x4*>(
                     ibase + (int64_t)(sxs + min(max(ic0 + it * RPI, ylo), yhi) * M.ky) * irow);
             if constexpr (!MASKCHUNK)
-                in.mb = mrow[sxs + min(max(min((int)threadIdx.x, NT * 16 - 1), ylo), yhi) * M.ky];
+                in.mb = mrow[sxs + min(max(min(tid, NT * 16 - 1), ylo), yhi) * M.ky];
         } else {
 #pragma unroll
-            for (int lt = 0; lt < TPG; ++lt) load_tile(s, lt, in);
+            for (int lt = 0; lt < TA; ++lt) load_tile(s, lt, in);
         }
     };
     // registers -> LDS buffers of diagonal s
@@ -331,7 +339,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 // moved past the next ones, for those
                 uint32_t mb = in.mb;
                 asm volatile("" : "+v"(mb));
-                mst[s & 1][threadIdx.x] = mb;
+                mst[s & 1][tid] = mb;
             }
         }
     };
@@ -408,7 +416,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     constexpr int RPF = STAGE_OUT ? (NTH / QF < NT * 16 ? (NTH / QF > 0 ? NTH / QF : 1) : NT * 16) : 1;
     constexpr int NITF = (NT * 16 + RPF - 1) / RPF;
     static_assert(!STAGE_OUT || NTH >= QF, "a row per pass");
-    const int ft0 = (int)threadIdx.x % (RPF * QF), fc0 = ft0 / QF, fr = ft0 - fc0 * QF;
+    const int ft0 = tid % (RPF * QF), fc0 = ft0 / QF, fr = ft0 - fc0 * QF;
     char* const fbase = fr < QZ        ? reinterpret_cast<char*>(zb) + 16 * fr
                         : fr < QZ + QY ? reinterpret_cast<char*>(yb) + 16 * (fr - QZ)
                                        : reinterpret_cast<char*>(cb) + 16 * (fr - QZ - QY);
@@ -465,14 +473,14 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 }
             }
         };
-        if constexpr (AHEAD) contract(0);
+        if constexpr (AHEAD && TA > 0) contract(0);
         if constexpr (decltype(with_flush)::value) flush(s - 1);
         stage_in(s + LEAD, far);
         if constexpr (STAGE_IN) load(s + LEAD + 2, far);
         else if constexpr (AHEAD) load(s + 2, far);
         if constexpr (OBUF == 1) lds_barrier();  // the write-back's reads are done
 #pragma unroll
-        for (int lt = TPG - 1; lt >= 0; --lt) {
+        for (int lt = TA - 1; lt >= 0; --lt) {
             const int yy = 16 * (tg * TPG + lt) + n16;
             if constexpr (!AHEAD) {
                 start(s, lt, far);
@@ -541,7 +549,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             }
             if constexpr (!AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (AHEAD) start(s + 1, 0, nxt);
+        if constexpr (AHEAD && TA > 0) start(s + 1, 0, nxt);
     };
 
     // split2 keeps no cell states beyond the largest bf16
@@ -557,7 +565,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
         load(sb + LEAD + 1, s1);
         lds_barrier();
     }
-    if constexpr (AHEAD) start(sb, 0, s0);
+    if constexpr (AHEAD && TA > 0) start(sb, 0, s0);
     if constexpr (STAGE_OUT) {
         // two steps ahead of the loop: it is entered with the memory operations
         // in flight that its own steps leave, so its waits are exact
@@ -579,7 +587,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     } else {
         // as many stores as a step has, into the sink, for the same reason
 #pragma unroll
-        for (int lt = 0; lt < TPG; ++lt) {
+        for (int lt = 0; lt < TA; ++lt) {
             float zero[WQ];
 #pragma unroll
             for (int r = 0; r < WQ; ++r) zero[r] = 0.0f;
@@ -608,7 +616,18 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
 template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
 __global__ void __launch_bounds__((FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH))
 __attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG, MEM>::WPE))) k_fwd(FwdArgs a) {
-    for_units(a, [&](int unit) { fwd_unit<H, NT, T, CK, WQ, NG, MEM>(a, unit); });
+    using K = FwdK<H, NT, T, CK, WQ, NG, MEM>;
+    if constexpr (NT == 1) {
+        for_units(a, [&](int unit) { fwd_unit<H, NT, T, CK, WQ, NG, MEM, 1>(a, unit); });
+    } else {
+        for_units(a, [&](int unit) {
+            const int rows = reinterpret_cast<const RectD*>(a.rects)[unit >> 2].h;
+            const int tg = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) / K::NWU;
+            with_tiles<K::TPG, NG == 1 ? 1 : 0>((rows + 15) / 16 - tg * K::TPG, [&](auto ta) {
+                fwd_unit<H, NT, T, CK, WQ, NG, MEM, decltype(ta)::value>(a, unit);
+            });
+        });
+    }
 }
 
 // Hidden sizes whose forward wavefront takes over the projection: where Wx's

@@ -54,6 +54,36 @@ def test_wavefronts_against_oracle(shape, nt):
         assert e <= RTOL[dt] and m <= RTOL[dt], (nm, e, m)
 
 
+@pytest.mark.parametrize("H,dt,C,mem", [(4, "f32", 8, False), (16, "f32", 8, False), (32, "f32", 20, False),
+                                        (64, "f32", 8, False), (32, "bf16", 16, False), (64, "bf16", 8, False),
+                                        (16, "f32", 8, True), (32, "f32", 8, True)])
+def test_units_of_every_height_in_one_launch(H, dt, C, mem):
+    """300 narrow images of 1 to 64 rows: a workgroup runs units of one to four
+    tiles one after another in the same LDS."""
+    import gpu_run
+    import oracle_run
+    from conftest import rel_err, rel_max
+    from synth.configs import custom_workload
+
+    rng = np.random.default_rng(H)
+    hs, ws = rng.integers(1, 65, 300), rng.integers(1, 5, 300)
+    hs[:4] = [64, 1, 17, 48]
+    print(f"case every height H={H} C={C} {dt} memory={mem}", flush=True)
+    wl = custom_workload(640 + H + C + (dt == "bf16"), hs, ws, 200, C, H, dt)
+    xs, params = wl.examples(), wl.params()
+    if mem:
+        params = (*params, wl.memory_params())
+    dys = [wl.dy(k) for k in range(wl.n)]
+    gpu = gpu_run.run_layer(xs, params, dys, hs, ws, 200, dtype=dt)
+    ref = oracle_run.run_layer(xs, params, dys, workers=oracle_run.default_workers())
+    pairs = [(nm, np.concatenate([t.ravel() for t in gpu[nm]]), np.concatenate([t.ravel() for t in ref[nm]]))
+             for nm in ("Y", "dX")]
+    pairs += [(nm, gpu[nm], ref[nm]) for nm in ("dWx", "dU", "db") + (("dV",) if mem else ())]
+    for nm, g, r in pairs:
+        e, m = rel_err(g, r), rel_max(g, r)
+        assert e <= RTOL[dt] and m <= RTOL[dt], (nm, e, m)
+
+
 @pytest.mark.parametrize("H,dt,C", [(16, "f32", 48), (32, "f32", 20), (64, "bf16", 40)])
 def test_per_diagonal_schedule_gives_the_same_bits(H, dt, C):
     """The state read back between launches is the state kept in a unit."""

@@ -456,18 +456,32 @@ __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
 // unit shares its CU with fewer others than when every unit has its own
 // workgroup from the start; without one, workgroup b runs unit b.
 // ---------------------------------------------------------------------------
-template <int H, int NT, typename T>
+// One unit per workgroup where the units are at most one per CU (forward) or two
+// (backward): the loop over the queue costs registers (forward, three tiles: 9
+// spilled against none, 256 units of 48 rows 4565 against 4422 us; backward
+// sixteen more spilled, 512 units 22.5 against 21.7 ms).
+template <int H, int NT, typename T, bool QUEUE>
 __global__ void __launch_bounds__((64 * WIDE_WAVES)) k_wave_fwd(FwdArgs a) {
-    for_units(a, [&](int unit) { wave_fwd_big<H, NT, T>(a, unit); });
+    if constexpr (QUEUE) for_units(a, [&](int unit) { wave_fwd_big<H, NT, T>(a, unit); });
+    else wave_fwd_big<H, NT, T>(a, a.units[blockIdx.x]);
 }
 
-// One unit per workgroup where the units are at most two per CU: the loop over
-// the queue costs it sixteen more spilled registers (wide batch 22.5 against
-// 21.7 ms).
 template <int H, int NT, typename T, bool QUEUE>
 __global__ void __launch_bounds__((64 * WIDE_WAVES)) k_wave_bwd(BwdArgs a) {
     if constexpr (QUEUE) for_units(a, [&](int unit) { wave_bwd_big<H, NT, T>(a, unit); });
     else wave_bwd_big<H, NT, T>(a, a.units[blockIdx.x]);
+}
+
+template <bool QUEUE>
+static WaveKernel wide_fwd_kernel(int nt) {
+    constexpr int th = 64 * WIDE_WAVES;
+    switch (nt) {
+        case 1: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 1, bf16_t, QUEUE>), th};
+        case 2: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 2, bf16_t, QUEUE>), th};
+        case 3: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 3, bf16_t, QUEUE>), th};
+        case 4: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 4, bf16_t, QUEUE>), th};
+        default: return {};
+    }
 }
 
 template <bool QUEUE>
@@ -486,7 +500,7 @@ static WaveKernel wide_bwd_kernel(int nt) {
 // Dispatch over hidden size, tiles per diagonal and storage type.
 // ---------------------------------------------------------------------------
 // The forward kernel of a shape. bf16 H = 128 has its own kernel: its operands
-// alone take 160 registers a lane at eight waves.
+// alone take 160 registers a lane at eight waves (here the one without a queue).
 static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
     const int ck = fwd_fused_steps(g);
     if (memory)
@@ -507,16 +521,7 @@ static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
     switch (g.hidden) {
         case 32: return fwd_kernel_bf16_h32(nt, ck);
         case 64: return fwd_kernel_bf16_h64(nt, ck);
-        case 128: {
-            constexpr int th = 64 * WIDE_WAVES;
-            switch (nt) {
-                case 1: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 1, bf16_t>), th};
-                case 2: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 2, bf16_t>), th};
-                case 3: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 3, bf16_t>), th};
-                case 4: return {reinterpret_cast<const void*>(&k_wave_fwd<128, 4, bf16_t>), th};
-                default: return {};
-            }
-        }
+        case 128: return wide_fwd_kernel<false>(nt);
         default: return {};
     }
 }
@@ -654,12 +659,12 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
                                 const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t, unsigned* d_queue,
                                 hipStream_t s) {
     if (n_units == 0) return hipSuccess;
-    const WaveKernel k = fwd_kernel_of(g, nt, t.v != nullptr);
+    WaveKernel k = fwd_kernel_of(g, nt, t.v != nullptr);
     if (!k.fn) return hipErrorInvalidValue;
     const int groups = resident_groups(k, std::max(1, 512 / k.threads));  // as in the backward
+    if (g.dtype == 1 && g.hidden == 128 && n_units > groups) k = wide_fwd_kernel<true>(nt);
     FwdArgs a{d_units, d_rects, d_mask, t.u, t.v, t.wx, t.b, t.x, t.xf, t.xinf, g.c_in, t.z, t.c, t.y, g.canvas_w, 0,
-              INT_MAX,
-              n_units > groups ? d_queue : nullptr, n_units};
+              INT_MAX, n_units > groups ? d_queue : nullptr, n_units};
     void* params[] = {&a};
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }

@@ -501,7 +501,7 @@ static WaveKernel wide_bwd_kernel(int nt) {
 // ---------------------------------------------------------------------------
 // The forward kernel of a shape. bf16 H = 128 has its own kernel: its operands
 // alone take 160 registers a lane at eight waves (here the one without a queue).
-static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
+static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory, bool one_step) {
     const int ck = fwd_fused_steps(g);
     if (memory)
         return g.dtype != 0      ? WaveKernel{}
@@ -510,17 +510,17 @@ static WaveKernel fwd_kernel_of(const LayerGeom& g, int nt, bool memory) {
                                  : WaveKernel{};
     if (g.dtype == 0) {
         switch (g.hidden) {
-            case 4: return fwd_kernel_f32_h4(nt, ck);
-            case 8: return fwd_kernel_f32_h8(nt, ck);
-            case 16: return fwd_kernel_f32_h16(nt, ck);
-            case 32: return fwd_kernel_f32_h32(nt, ck);
-            case 64: return fwd_kernel_f32_h64(nt, ck);
+            case 4: return fwd_kernel_f32_h4(nt, ck, one_step);
+            case 8: return fwd_kernel_f32_h8(nt, ck, one_step);
+            case 16: return fwd_kernel_f32_h16(nt, ck, one_step);
+            case 32: return fwd_kernel_f32_h32(nt, ck, one_step);
+            case 64: return fwd_kernel_f32_h64(nt, ck, one_step);
             default: return {};
         }
     }
     switch (g.hidden) {
-        case 32: return fwd_kernel_bf16_h32(nt, ck);
-        case 64: return fwd_kernel_bf16_h64(nt, ck);
+        case 32: return fwd_kernel_bf16_h32(nt, ck, one_step);
+        case 64: return fwd_kernel_bf16_h64(nt, ck, one_step);
         case 128: return wide_fwd_kernel<false>(nt);
         default: return {};
     }
@@ -542,7 +542,7 @@ size_t fwd_x_bytes(const LayerGeom& g) {
 // output rows of the invalid cells, and the fp32 inputs of the rectangles'
 // cells as the wavefront reads them: three bf16 pieces, channels padded with
 // zeros to 32 CK, then 16 bytes whose first word says whether the cell is
-// valid; a rectangle with an infinite input in a valid cell is flagged. A workgroup takes 256 cells; it first lists the rectangles that meet
+// valid; a rectangle with an input beyond the largest bf16 in a valid cell is flagged. A workgroup takes 256 cells; it first lists the rectangles that meet
 // them (rectangles are disjoint, so the list's order does not matter). Four
 // launches before (id fill, painting, pieces, zeroing): two small images 678 ->
 // 655 us through the three layers, word batch step 545 -> 528 us.
@@ -616,7 +616,7 @@ k_forward_layout(int n, const RectD* __restrict__ rects, int canvas_w, int64_t n
                 float m = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[e]));
-                if (m > F32_LARGEST && ids[cell] > 0) atomicOr(&xinf[rid[pc]], 1);
+                if (m > BF16_LARGEST && ids[cell] > 0) atomicOr(&xinf[rid[pc]], 1);
                 bf16x8 o[3];
                 make_op<float>(v, o);
 #pragma unroll
@@ -639,9 +639,11 @@ hipError_t launch_forward_layout(const LayerGeom& g, int n, const int32_t* d_rec
     return hipGetLastError();
 }
 
-// Workgroups of a kernel that the device holds at once (256 CUs assumed when
-// the query fails), up to `most` on a CU.
-static int resident_groups(const WaveKernel& k, int most = INT_MAX) {
+// Workgroups of a kernel that the device holds at once (256 CUs assumed when the
+// query fails), two waves per SIMD at most: a third reads and writes more than
+// the memory takes (word batch backward, fp32 H 16: 396 us with three, 355 with
+// two; 128 images of 32 rows, bf16 H 32: 1314 and 1249).
+static int resident_groups(const WaveKernel& k) {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
@@ -652,19 +654,19 @@ static int resident_groups(const WaveKernel& k, int most = INT_MAX) {
         (void)hipGetLastError();
         per = 1;
     }
-    return cus * std::min(per, most);
+    return cus * std::min(per, std::max(1, 512 / k.threads));
 }
 
 hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const int32_t* d_units,
                                 const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t, unsigned* d_queue,
                                 hipStream_t s) {
     if (n_units == 0) return hipSuccess;
-    WaveKernel k = fwd_kernel_of(g, nt, t.v != nullptr);
+    WaveKernel k = fwd_kernel_of(g, nt, t.v != nullptr, false);
     if (!k.fn) return hipErrorInvalidValue;
-    const int groups = resident_groups(k, std::max(1, 512 / k.threads));  // as in the backward
+    const int groups = resident_groups(k);
     if (g.dtype == 1 && g.hidden == 128 && n_units > groups) k = wide_fwd_kernel<true>(nt);
     FwdArgs a{d_units, d_rects, d_mask, t.u, t.v, t.wx, t.b, t.x, t.xf, t.xinf, g.c_in, t.z, t.c, t.y, g.canvas_w, 0,
-              INT_MAX, n_units > groups ? d_queue : nullptr, n_units};
+              INT_MAX, n_units > groups ? d_queue : nullptr, n_units, nullptr};
     void* params[] = {&a};
     return hipLaunchKernel(k.fn, dim3(std::min(n_units, groups)), dim3(k.threads), params, 0, s);
 }
@@ -700,10 +702,7 @@ hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const i
     if (n_units == 0) return hipSuccess;
     WaveKernel k = bwd_kernel_of(g, nt, t.v != nullptr);
     if (!k.fn) return hipErrorInvalidValue;
-    // Two waves per SIMD at most: a third reads and writes more than the memory
-    // takes (word batch, fp32 H 16: 396 us with three, 355 with two; 128 images of
-    // 32 rows, bf16 H 32: 1314 and 1249).
-    int groups = resident_groups(k, std::max(1, 512 / k.threads));
+    int groups = resident_groups(k);
     if (g.dtype == 1 && g.hidden == 128 && n_units <= 2 * groups) {  // one workgroup per CU is resident
         k = wide_bwd_kernel<false>(nt);
         groups = n_units;
@@ -717,9 +716,9 @@ hipError_t launch_wavefront_bwd(const LayerGeom& g, int nt, int n_units, const i
 
 hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, int max_steps, const int32_t* d_units,
                                      const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t,
-                                     hipGraphExec_t* exec) {
+                                     const StepTensors* d_now, hipGraphExec_t* exec) {
     if (n_units <= 0 || max_steps <= 0) return hipErrorInvalidValue;
-    const WaveKernel k = fwd_kernel_of(g, nt, false);
+    const WaveKernel k = fwd_kernel_of(g, nt, false, true);
     if (!k.fn) return hipErrorInvalidValue;
     hipGraph_t graph;
     hipError_t e = hipGraphCreate(&graph, 0);
@@ -727,7 +726,7 @@ hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, in
     hipGraphNode_t prev = nullptr;
     for (int st = 0; st < max_steps && e == hipSuccess; ++st) {
         FwdArgs a{d_units, d_rects, d_mask, t.u, t.v,        t.wx, t.b,    t.x,     t.xf, t.xinf, g.c_in,
-                  t.z,     t.c,     t.y,    g.canvas_w, st, st + 1, nullptr, n_units};
+                  t.z,     t.c,     t.y,    g.canvas_w, st, st + 1, nullptr, n_units, d_now};
         void* params[] = {&a};
         hipKernelNodeParams p{};
         p.func = const_cast<void*>(k.fn);

@@ -66,6 +66,14 @@ struct FwdTensors {
     float* c;
     void* y;
 };
+// Tensors of a per-diagonal schedule that may differ from call to call: its
+// recorded launches read them from the device.
+struct StepTensors {
+    const void* wx;
+    const void* b;
+    const void* x;
+    const float* xf;
+};
 // K steps of 32 input channels the forward wavefront computes itself; 0 where
 // launch_projection has to run first.
 int fwd_fused_steps(const LayerGeom& g);
@@ -76,8 +84,8 @@ size_t fwd_x_bytes(const LayerGeom& g);
 // with n: above MAX_LAYOUT_RECTS rectangles callers run launch_rect_ids first
 // and pass n = -1 (the ids are in d_rid).
 constexpr int MAX_LAYOUT_RECTS = 4096;
-// d_xinf[rectangle] is set where a valid cell's input is infinite (fp32; zero on
-// entry).
+// d_xinf[rectangle] is set where a valid cell's input lies beyond the largest
+// bf16 (fp32; zero on entry).
 hipError_t launch_forward_layout(const LayerGeom& g, int n, const int32_t* d_rects, int32_t* d_rid,
                                  const uint8_t* d_mask, unsigned* d_queue, void* d_y, const void* d_x, void* d_xs,
                                  int* d_xinf, hipStream_t s);
@@ -91,10 +99,11 @@ hipError_t launch_wavefront_fwd(const LayerGeom& g, int nt, int n_units, const i
 
 // The forward wavefront as one launch per local diagonal (diagonal s of every
 // unit in launch s), recorded as a chain of max_steps kernel nodes into an
-// instantiated graph; same results as launch_wavefront_fwd.
+// instantiated graph; same results as launch_wavefront_fwd. The launches take
+// wx, b, x and xf from d_now.
 hipError_t build_wavefront_fwd_graph(const LayerGeom& g, int nt, int n_units, int max_steps, const int32_t* d_units,
                                      const int32_t* d_rects, const uint8_t* d_mask, const FwdTensors& t,
-                                     hipGraphExec_t* exec);
+                                     const StepTensors* d_now, hipGraphExec_t* exec);
 
 // --- backward --------------------------------------------------------------
 struct BwdTensors {

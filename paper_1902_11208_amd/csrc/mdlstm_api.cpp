@@ -139,7 +139,7 @@ bool same_shape(const mdlstm_layer_desc* a, const mdlstm_layer_desc& b) {
 }
 
 struct Plan {
-    size_t z, c, rid, rects, units, xinf, part, flags, wxt, dvpart, xs, queue, check, total;
+    size_t z, c, rid, rects, units, xinf, now, part, flags, wxt, dvpart, xs, queue, check, total;
 };
 
 mdl::LayerGeom geom(const mdlstm_layer_desc* d, int32_t ch, int32_t cw) {
@@ -170,8 +170,10 @@ Plan plan(const mdlstm_layer_desc* d, int32_t ch, int32_t cw, int32_t nr) {
     off += align_up((size_t)(nr > 0 ? nr : 1) * 16);
     p.units = off;
     off += align_up((size_t)(nr > 0 ? nr : 1) * 16);
-    p.xinf = off;  // per rectangle: one of its fp32 inputs is infinite
+    p.xinf = off;  // per rectangle: one of its fp32 inputs has no pieces
     off += align_up((size_t)(nr > 0 ? nr : 1) * 4);
+    p.now = off;  // the per-diagonal schedule's tensors of this call
+    off += align_up(sizeof(mdl::StepTensors));
     p.part = off;
     const bool strip = mdl::strip_supported(g);
     off += align_up(strip ? mdl::strip_partial_bytes(g) : mdl::big_partial_bytes(g));
@@ -371,7 +373,8 @@ void set_staged(const Common& c, const StagedKey* key) {
 // A backward call stages the rectangle ids and zeroes the unit queue as well; a
 // forward call leaves both to launch_forward_layout, and the workspace counts
 // as staged (set_staged) only once that is enqueued.
-mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* rects, bool backward, hipStream_t s) {
+mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* rects, bool backward, hipStream_t s,
+                           const mdl::StepTensors* now = nullptr) {
     const StagedKey key = staged_key(c, n_rects, rects);
     if (backward) {
         std::lock_guard<std::mutex> lock(g_staged_mu);
@@ -380,12 +383,15 @@ mdlstm_status stage_layout(const Common& c, int32_t n_rects, const mdlstm_rect* 
     }
     set_staged(c, nullptr);
     if (n_rects > 0) {
-        // rectangles, unit order and zero flags in one copy (adjacent workspace sections)
+        // rectangles, unit order, zero flags and the per-diagonal schedule's tensors in
+        // one copy (adjacent workspace sections)
         std::vector<int32_t> units = unit_order(n_rects, rects);
-        const size_t ubytes = units.size() * 4, span = c.p.xinf - c.p.rects + (size_t)n_rects * 4;
+        const size_t ubytes = units.size() * 4;
+        const size_t span = now ? c.p.now - c.p.rects + sizeof(*now) : c.p.xinf - c.p.rects + (size_t)n_rects * 4;
         std::vector<unsigned char> host(span, 0);
         std::memcpy(host.data(), rects, (size_t)n_rects * 16);
         std::memcpy(host.data() + (c.p.units - c.p.rects), units.data(), ubytes);
+        if (now) std::memcpy(host.data() + (c.p.now - c.p.rects), now, sizeof(*now));
         HIP_OR_FAIL(hipMemcpyAsync(c.ws + c.p.rects, host.data(), span, hipMemcpyHostToDevice, s));
     }
     if (backward) {
@@ -685,7 +691,10 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
         if ((st = poison(c.ws, c.p.part, c.p.flags, s)) != MDLSTM_OK) return st;
         if ((st = poison(c.ws, c.p.wxt, c.p.queue, s)) != MDLSTM_OK) return st;
     }
-    st = stage_layout(c, n_rects, rects, false, s);
+    const float* const xf = c.g.dtype == 0 ? static_cast<const float*>(d_x) : nullptr;
+    const void* const xk = c.g.dtype == 0 ? c.ws + c.p.xs : d_x;  // the inputs as the wavefront reads them
+    const mdl::StepTensors now{d_wx, d_b, xk, xf};
+    st = stage_layout(c, n_rects, rects, false, s, stepwise ? &now : nullptr);
     if (st != MDLSTM_OK) return st;
     const int32_t* rid = reinterpret_cast<const int32_t*>(c.ws + c.p.rid);
     const int32_t* units = reinterpret_cast<const int32_t*>(c.ws + c.p.units);
@@ -708,8 +717,7 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
         HIP_OR_FAIL(mdl::launch_projection(c.g, d_x, d_wx, d_b, rid, c.ws + c.p.z, s));
     const int64_t nu = 4 * (int64_t)c.g.hidden * 5 * 2 * c.g.hidden;  // floats of U before V
     const void* d_v = desc->memory_states ? static_cast<const float*>(d_u) + nu : nullptr;
-    const mdl::FwdTensors ft{d_u, d_v, d_wx, d_b, c.g.dtype == 0 ? c.ws + c.p.xs : d_x,
-                             c.g.dtype == 0 ? static_cast<const float*>(d_x) : nullptr, xinf, c.ws + c.p.z, cs, d_y};
+    const mdl::FwdTensors ft{d_u, d_v, d_wx, d_b, xk, xf, xinf, c.ws + c.p.z, cs, d_y};
     HIP_OR_FAIL(mark(1, s));
     HIP_OR_FAIL(mark(2, s));
     if (!stepwise) {
@@ -720,7 +728,7 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
         static thread_local StepGraph* cache = new StepGraph;
         std::vector<uintptr_t> key = {(uintptr_t)desc->c_in, (uintptr_t)desc->hidden, (uintptr_t)desc->dtype,
                                       (uintptr_t)canvas_h, (uintptr_t)canvas_w, (uintptr_t)d_mask, (uintptr_t)d_u,
-                                      (uintptr_t)d_wx, (uintptr_t)d_b, (uintptr_t)d_x, (uintptr_t)d_y, (uintptr_t)d_workspace, (uintptr_t)n_rects};
+                                      (uintptr_t)d_y, (uintptr_t)d_workspace, (uintptr_t)n_rects};
         for (int32_t k = 0; k < n_rects; ++k) {
             key.push_back(((uintptr_t)(uint32_t)rects[k].y0 << 32) | (uint32_t)rects[k].x0);
             key.push_back(((uintptr_t)(uint32_t)rects[k].h << 32) | (uint32_t)rects[k].w);
@@ -731,6 +739,7 @@ mdlstm_status forward_impl(bool stepwise, const mdlstm_layer_desc* desc, int32_t
                 cache->exec = nullptr;
             }
             HIP_OR_FAIL(mdl::build_wavefront_fwd_graph(c.g, c.nt, 4 * n_rects, max_steps, units, drects, d_mask, ft,
+                                                       reinterpret_cast<const mdl::StepTensors*>(c.ws + c.p.now),
                                                        &cache->exec));
             cache->key = std::move(key);
         }

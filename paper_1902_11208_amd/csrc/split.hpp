@@ -9,9 +9,9 @@
 // reduction values cost 96 cycles in this form against 256 as eight 16x16x4
 // fp32 MFMAs.
 //
-// A finite value beyond the largest bf16 keeps its form with hi at that value.
-// An infinite one has none (its products are NaN whatever the sum is): a unit
-// that met one is run again without pieces (wave_plain.hpp).
+// A value beyond the largest bf16 has no such form, an infinite one least of all
+// (its products are NaN whatever the sum is): a unit that met one is run again
+// without pieces (wave_plain.hpp).
 #pragma once
 
 #include "common.hpp"
@@ -38,19 +38,7 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t (&p)[3]) {
     p[2] = f2bf2(a, b);
 }
 
-constexpr float BF16_LARGEST = 3.3895313892515355e38f, F32_LARGEST = 3.4028234663852886e38f;
-
-// As split2, for any values.
-__device__ __forceinline__ void split2_any(float a, float b, uint32_t (&p)[3]) {
-    auto lead = [](float v) { return v > BF16_LARGEST ? BF16_LARGEST : (v < -BF16_LARGEST ? -BF16_LARGEST : v); };
-    p[0] = f2bf2(lead(a), lead(b));
-    a -= __uint_as_float(p[0] << 16);
-    b -= __uint_as_float(p[0] & 0xffff0000u);
-    p[1] = f2bf2(a, b);
-    a -= __uint_as_float(p[1] << 16);
-    b -= __uint_as_float(p[1] & 0xffff0000u);
-    p[2] = f2bf2(a, b);
-}
+constexpr float BF16_LARGEST = 3.3895313892515355e38f;
 
 // Eight reduction values of one operand slot as MFMA operands.
 template <typename T>
@@ -60,7 +48,7 @@ __device__ __forceinline__ void make_op(const float (&v)[8], bf16x8 (&o)[Pieces<
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             uint32_t p[3];
-            split2_any(v[2 * e], v[2 * e + 1], p);
+            split2(v[2 * e], v[2 * e + 1], p);
 #pragma unroll
             for (int k = 0; k < 3; ++k) w[k][e] = p[k];
         }

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "kernels.hpp"
 #include "split.hpp"
 
 namespace mdl {
@@ -80,7 +81,7 @@ struct FwdArgs {
     const void* b;         // [4][5H]
     const void* x;         // inputs per cell: bf16 [c_in], or the fp32 inputs as bf16 pieces [3][32 CK]
     const float* xf;       // the fp32 inputs themselves
-    const int* xinf;       // per rectangle: one of its fp32 inputs is infinite (where x is pieces)
+    const int* xinf;       // per rectangle: one of its fp32 inputs has no pieces (where x is pieces)
     int c_in;
     void* z;               // [n_cells][20H]: pre-activations in where the projection ran apart; gates out
     float* c;              // [n_cells][4H] cell state
@@ -89,7 +90,20 @@ struct FwdArgs {
     int s0, s1;            // local diagonals [s0, s1) of every unit
     unsigned* queue;       // next unit to take (zeroed before the launch), or NULL: unit = block
     int n_units;
+    const StepTensors* now;  // per-diagonal launches: wx, b, x and xf are read from here
 };
+
+// The arguments of a per-diagonal launch with the tensors of this call.
+__device__ __forceinline__ FwdArgs step_args(FwdArgs a) {
+    using G = const __attribute__((address_space(1))) char*;  // keeps the loads global
+    const StepTensors t = *a.now;
+    a.wx = (const void*)(G)t.wx;
+    a.b = (const void*)(G)t.b;
+    a.x = (const void*)(G)t.x;
+    a.xf = (const float*)(G)t.xf;
+    return a;
+}
+
 
 struct BwdArgs {
     const int32_t* units;  // unit = rect*4 + direction, in launch order

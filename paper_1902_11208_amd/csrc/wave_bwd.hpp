@@ -118,6 +118,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
     };
     // A operands, lane row n16 = 4 jj + e of tile t: output o = 4t + e, the left
     // part (column) of unit UW w + WQ jj + o for o < WQ, then the top parts.
+    float wmax = 0.0f;  // largest magnitude of the wave's fp32 weights, NaN left out
     bf16x8 A[OT][KS][P];
     const T* const U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
 #pragma unroll
@@ -144,6 +145,10 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
                                : 0.0f;
                 else
                     v[e] = ok && k < G ? St<T>::ld1(U + (int64_t)row * 2 * H + col) : 0.0f;
+            }
+            if constexpr (P == 3) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) wmax = fmaxf(wmax, fabsf(v[e]));
             }
             if (top) {
 #pragma unroll
@@ -428,6 +433,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         for (int lt = 0; lt < TA; ++lt) load_tile(steps - 1, lt, s0);
     }
     lds_barrier();
+    if (P == 3 && wmax > BF16_LARGEST) plain = 1;
     // two steps ahead of the loop: it is entered with the memory operations in
     // flight that its own steps leave, so its waits are exact
     int s = steps - 1;
@@ -442,7 +448,7 @@ __device__ __forceinline__ void bwd_unit(const BwdArgs& a, const int unit) {
         step(s, STAGE ? s1 : s0);
         --s;
     }
-    if constexpr (P == 3) {  // split2 keeps no values beyond the largest bf16
+    if constexpr (P == 3) {
         if (dmax > BF16_LARGEST) plain = 1;
         lds_barrier();
         if (__builtin_amdgcn_readfirstlane(plain))

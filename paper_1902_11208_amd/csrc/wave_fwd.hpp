@@ -81,7 +81,11 @@ struct FwdK {
 };
 
 // TA: the group's tiles that hold rows of the rectangle.
-template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM, int TA>
+// STEP: one diagonal per launch, [a.s0, a.s0 + 1), with the state of the one
+// before read back from the outputs and cell states. Its loads are all on their
+// way before the first wait, nothing is loaded ahead or left for a next diagonal
+// (line batch, 621 launches: 7.6 -> 6.9 ms).
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM, int TA, bool STEP>
 __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     using K = FwdK<H, NT, T, CK, WQ, NG, MEM>;
     constexpr int P = K::P, NWU = K::NWU, TPG = K::TPG, KS = K::KS, KP = K::KP, TILES = K::TILES, NTH = K::NTH;
@@ -114,9 +118,6 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     const int d = unit & 3;
     const RectD R = reinterpret_cast<const RectD*>(a.rects)[unit >> 2];
     const int steps = R.h + R.w - 1;
-    // Diagonals [sb, se) of the unit: all of them in one launch, or one per
-    // launch, in which case the state of diagonal sb - 1 is read back from the
-    // outputs and cell states the previous launch wrote.
     const int sb = a.s0, se = min(a.s1, steps);
     if (sb >= se) return;
     T* const Z = static_cast<T*>(a.z);
@@ -161,31 +162,6 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     for (int lt = 0; lt < TA; ++lt)
 #pragma unroll
         for (int r = 0; r < WQ; ++r) cprev[lt][r] = 0.0f;
-    if (sb > 0) {
-        lds_barrier();  // every zero written before the read-back fills the same rows
-        const int pb = (sb & 1) ^ 1;
-#pragma unroll
-        for (int lt = 0; lt < TA; ++lt) {
-            const int yy = 16 * (tg * TPG + lt) + n16, xx = sb - 1 - yy;
-            if (yy < R.h && xx >= 0 && xx < R.w) {
-                const int64_t p = canvas_index(R, d, yy, xx, a.canvas_w) * (4 * H) + d * H + u0;
-                float hv[WQ];
-#pragma unroll
-                for (int r = 0; r < WQ; ++r) {
-                    hv[r] = St<T>::ld1(Y + p + r);
-                    cprev[lt][r] = Cs[p + r];
-                }
-                put(hop, pb, yy, hv);
-            }
-            if constexpr (NG > 1) {
-                if (lt == TPG - 1 && n16 == 15) {
-#pragma unroll
-                    for (int r = 0; r < WQ; ++r) cedge[pb][tg][u0 + r] = cprev[lt][r];
-                }
-            }
-        }
-    }
-
     // A operands, lane row n16 = 4 jj + e: tile r < WQ, gate e of unit
     // UW w + WQ jj + r; tile WQ, candidate of unit UW w + WQ jj + e.
     // Memory-state matrices: gates i, f_L, f_T of the sigmoid tiles (V rows).
@@ -200,61 +176,65 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     const T* const U = static_cast<const T*>(a.u) + (int64_t)d * G * 2 * H;
     const T* const Wx = static_cast<const T*>(a.wx) + (int64_t)d * G * a.c_in;
     const T* const Bd = static_cast<const T*>(a.b) + d * G;
+    floatx4 bias[TILES];
+    bool winf = false;
+    auto load_weights = [&] {
 #pragma unroll
-    for (int t = 0; t < TILES; ++t) {
-        const int jj = n16 >> 2, e = n16 & 3;
-        const bool ok = t < WQ || e < WQ;
-        const int ul = K::UW * w + WQ * jj + (t < WQ ? t : (ok ? e : 0));
-        const int row = (t < WQ ? e : 4) * H + ul;
+        for (int t = 0; t < TILES; ++t) {
+            const int jj = n16 >> 2, e = n16 & 3;
+            const bool ok = t < WQ || e < WQ;
+            const int ul = K::UW * w + WQ * jj + (t < WQ ? t : (ok ? e : 0));
+            const int row = (t < WQ ? e : 4) * H + ul;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int k = 32 * ks + 8 * q;
-            const T* p = U + (int64_t)row * 2 * H + k;
-            const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-            const bool in = ok && k < 2 * H;
-            const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
-            const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-            seen(v);
-            make_op<T>(v, Ah[t][ks]);
-        }
-        if constexpr (MEM) {
-            if (t < WQ) {
+            for (int ks = 0; ks < KS; ++ks) {
+                const int k = 32 * ks + 8 * q;
+                const T* p = U + (int64_t)row * 2 * H + k;
+                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                const bool in = ok && k < 2 * H;
+                const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
+                const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                seen(v);
+                make_op<T>(v, Ah[t][ks]);
+            }
+            if constexpr (MEM) {
+                if (t < WQ) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const int k = 32 * ks + 8 * q;
-                    const T* p = static_cast<const T*>(a.v) + ((int64_t)d * 3 * H + (e < 3 ? e : 0) * H + ul) * 2 * H + k;
-                    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-                    const bool in = e < 3 && k < 2 * H;
-                    const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
-                    const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                    seen(v);
-                    make_op<T>(v, Ac[t < WQ ? t : 0][ks]);
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const int k = 32 * ks + 8 * q;
+                        const T* p = static_cast<const T*>(a.v) + ((int64_t)d * 3 * H + (e < 3 ? e : 0) * H + ul) * 2 * H + k;
+                        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                        const bool in = e < 3 && k < 2 * H;
+                        const floatx4 v0 = in ? St<T>::ld4(p) : zero, v1 = in ? St<T>::ld4(p + 4) : zero;
+                        const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                        seen(v);
+                        make_op<T>(v, Ac[t < WQ ? t : 0][ks]);
+                    }
                 }
             }
+#pragma unroll
+            for (int ks = 0; ks < CK; ++ks) {
+                const int k = 32 * ks + 8 * q;
+                const T* p = Wx + (int64_t)row * a.c_in + k;
+                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                const floatx4 v0 = ok && k < a.c_in ? St<T>::ld4(p) : zero;
+                const floatx4 v1 = ok && k + 4 < a.c_in ? St<T>::ld4(p + 4) : zero;
+                const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                seen(v);
+                make_op<T>(v, Ax[t][ks]);
+            }
         }
+        if constexpr (FUSED) {
 #pragma unroll
-        for (int ks = 0; ks < CK; ++ks) {
-            const int k = 32 * ks + 8 * q;
-            const T* p = Wx + (int64_t)row * a.c_in + k;
-            const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-            const floatx4 v0 = ok && k < a.c_in ? St<T>::ld4(p) : zero;
-            const floatx4 v1 = ok && k + 4 < a.c_in ? St<T>::ld4(p + 4) : zero;
-            const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-            seen(v);
-            make_op<T>(v, Ax[t][ks]);
+            for (int t = 0; t < TILES; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    bias[t][e] = t < WQ ? St<T>::ld1(Bd + e * H + u0 + t) : (e < WQ ? St<T>::ld1(Bd + 4 * H + u0 + e) : 0.0f);
         }
-    }
-    floatx4 bias[TILES];
-    if constexpr (FUSED) {
-#pragma unroll
-        for (int t = 0; t < TILES; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                bias[t][e] = t < WQ ? St<T>::ld1(Bd + e * H + u0 + t) : (e < WQ ? St<T>::ld1(Bd + 4 * H + u0 + e) : 0.0f);
-    }
-    __builtin_amdgcn_s_waitcnt(0);  // operands in registers before the step loop
-    // taken here, or the weights would live until its use at the end
-    const bool winf = P == 3 && __any(wmax > F32_LARGEST);
+        __builtin_amdgcn_s_waitcnt(0);  // operands in registers before the step loop
+        // taken here, or the weights would live until its use at the end
+        winf = P == 3 && __any(wmax > BF16_LARGEST);
+    };
+    if constexpr (!STEP) load_weights();
     float cmax = 0.0f;  // largest cell state
 
     char* const sink = sink_ptr();
@@ -328,6 +308,28 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             for (int lt = 0; lt < TA; ++lt) load_tile(s, lt, in);
         }
     };
+    Set s0, s1;
+    float hback[TN][WQ];
+    auto behind = [&](int lt) {  // the lane's row of a tile has a cell on diagonal sb - 1
+        const int yy = 16 * (tg * TPG + lt) + n16;
+        return sb > 0 && yy < R.h && yy < sb && sb - 1 - yy < R.w;
+    };
+    if constexpr (STEP) {
+        load(sb, s0);
+#pragma unroll
+        for (int lt = 0; lt < TA; ++lt)
+            if (behind(lt)) {
+                const int64_t p = M.at(M.base(sb - 1), 16 * (tg * TPG + lt) + n16) * (4 * H) + d * H + u0;
+                const typename V::R hr = ldw<T, WQ>(Y + p);
+                const typename Vec<float, WQ>::R cr = ldw<float, WQ>(Cs + p);
+#pragma unroll
+                for (int r = 0; r < WQ; ++r) {
+                    hback[lt][r] = V::get(hr, r);
+                    cprev[lt][r] = Vec<float, WQ>::get(cr, r);
+                }
+            }
+        load_weights();
+    }
     // registers -> LDS buffers of diagonal s
     auto stage_in = [&](int s, const Set& in) {
         if constexpr (STAGE_IN) {
@@ -475,16 +477,18 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
         };
         if constexpr (AHEAD && TA > 0) contract(0);
         if constexpr (decltype(with_flush)::value) flush(s - 1);
-        stage_in(s + LEAD, far);
-        if constexpr (STAGE_IN) load(s + LEAD + 2, far);
-        else if constexpr (AHEAD) load(s + 2, far);
+        if constexpr (!STEP) {
+            stage_in(s + LEAD, far);
+            if constexpr (STAGE_IN) load(s + LEAD + 2, far);
+            else if constexpr (AHEAD) load(s + 2, far);
+        }
         if constexpr (OBUF == 1) lds_barrier();  // the write-back's reads are done
 #pragma unroll
         for (int lt = TA - 1; lt >= 0; --lt) {
             const int yy = 16 * (tg * TPG + lt) + n16;
             if constexpr (!AHEAD) {
                 start(s, lt, far);
-                if constexpr (!STAGE_IN) load_tile(s + 1, lt, far);
+                if constexpr (!STAGE_IN && !STEP) load_tile(s + 1, lt, far);
                 contract(lt);
             }
             float ct[WQ];  // cell states of the row above
@@ -519,7 +523,7 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
                 cprev[lt][r] = cv[r];
                 gv[0][r] = mk != 0 ? gv[0][r] : -1.0f;  // marks a masked cell for the backward
             }
-            put(hop, cur, yy, hv);
+            if constexpr (!STEP) put(hop, cur, yy, hv);
             if constexpr (MEM) {
 #pragma unroll
                 for (int r = 0; r < WQ; ++r) cmax = fmaxf(cmax, fabsf(cv[r]));
@@ -549,13 +553,35 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
             }
             if constexpr (!AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (AHEAD && TA > 0) start(s + 1, 0, nxt);
+        if constexpr (AHEAD && TA > 0 && !STEP) start(s + 1, 0, nxt);
     };
 
-    // split2 keeps no cell states beyond the largest bf16
     auto met = [&] { return winf || (MEM && cmax > BF16_LARGEST); };
-    Set s0, s1;
     constexpr bool ONE = !STAGE_IN && !AHEAD;
+    if constexpr (STEP) {
+        lds_barrier();  // every zero written before the read-back fills the same rows
+#pragma unroll
+        for (int lt = 0; lt < TA; ++lt) {
+            if (behind(lt)) put(hop, (sb & 1) ^ 1, 16 * (tg * TPG + lt) + n16, hback[lt]);
+            if constexpr (NG > 1) {
+                if (lt == TPG - 1 && n16 == 15) {
+#pragma unroll
+                    for (int r = 0; r < WQ; ++r) cedge[(sb & 1) ^ 1][tg][u0 + r] = cprev[lt][r];
+                }
+            }
+        }
+        stage_in(sb, s0);
+        if constexpr (STAGE_IN) lds_barrier();
+        if constexpr (AHEAD && TA > 0) start(sb, 0, s0);
+        step(sb, s0, s0, std::false_type{});
+        if (P == 3 && met()) plain = 1;
+        lds_barrier();
+        if constexpr (STAGE_OUT) flush(sb);
+        if constexpr (P == 3) {
+            if (__builtin_amdgcn_readfirstlane(plain)) plain_fwd_unit<H, MEM>(kern_args<FwdArgs>(), unit, sb, se);
+        }
+        return;
+    }
     load(sb, s0);
     if constexpr (!ONE) load(sb + 1, s1);
     if constexpr (STAGE_IN) {
@@ -613,21 +639,24 @@ __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int unit) {
     }
 }
 
-template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
+template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM, bool STEP>
 __global__ void __launch_bounds__((FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH))
-__attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG, MEM>::WPE))) k_fwd(FwdArgs a) {
+__attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG, MEM>::WPE))) k_fwd(FwdArgs args) {
+    const FwdArgs a = STEP ? step_args(args) : args;
     using K = FwdK<H, NT, T, CK, WQ, NG, MEM>;
-    if constexpr (NT == 1) {
-        for_units(a, [&](int unit) { fwd_unit<H, NT, T, CK, WQ, NG, MEM, 1>(a, unit); });
-    } else {
-        for_units(a, [&](int unit) {
+    auto run = [&](int unit) {
+        if constexpr (NT == 1) {
+            fwd_unit<H, NT, T, CK, WQ, NG, MEM, 1, STEP>(a, unit);
+        } else {
             const int rows = reinterpret_cast<const RectD*>(a.rects)[unit >> 2].h;
             const int tg = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) / K::NWU;
             with_tiles<K::TPG, NG == 1 ? 1 : 0>((rows + 15) / 16 - tg * K::TPG, [&](auto ta) {
-                fwd_unit<H, NT, T, CK, WQ, NG, MEM, decltype(ta)::value>(a, unit);
+                fwd_unit<H, NT, T, CK, WQ, NG, MEM, decltype(ta)::value, STEP>(a, unit);
             });
-        });
-    }
+        }
+    };
+    if constexpr (STEP) run(a.units[blockIdx.x]);
+    else for_units(a, run);
 }
 
 // Hidden sizes whose forward wavefront takes over the projection: where Wx's
@@ -639,28 +668,33 @@ constexpr bool fwd_fusable(int hidden) {
 }
 
 template <int H, int NT, typename T, int CK, int WQ, int NG, bool MEM>
-WaveKernel fwd_kernel_ck() {
-    return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, CK, WQ, NG, MEM>), FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH};
+WaveKernel fwd_kernel_ck(bool one_step) {
+    constexpr int th = FwdK<H, NT, T, CK, WQ, NG, MEM>::NTH;
+    if constexpr (!MEM) {
+        if (one_step) return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, CK, WQ, NG, MEM, true>), th};
+    }
+    return {reinterpret_cast<const void*>(&k_fwd<H, NT, T, CK, WQ, NG, MEM, false>), th};
 }
 
 template <int H, int NT, typename T, int WQ, int NG, bool MEM = false>
-WaveKernel fwd_kernel(int ck) {
-    if (ck == 0) return fwd_kernel_ck<H, NT, T, 0, WQ, NG, MEM>();
+WaveKernel fwd_kernel(int ck, bool one_step = false) {
+    if (ck == 0) return fwd_kernel_ck<H, NT, T, 0, WQ, NG, MEM>(one_step);
     if constexpr (fwd_fusable<T>(H)) {
-        if (ck == 1) return fwd_kernel_ck<H, NT, T, 1, WQ, NG, MEM>();
-        if (ck == 2) return fwd_kernel_ck<H, NT, T, 2, WQ, NG, MEM>();
+        if (ck == 1) return fwd_kernel_ck<H, NT, T, 1, WQ, NG, MEM>(one_step);
+        if (ck == 2) return fwd_kernel_ck<H, NT, T, 2, WQ, NG, MEM>(one_step);
     }
     return {};
 }
 
-// One translation unit per hidden size (k_wave_fwd_*.hip).
-WaveKernel fwd_kernel_f32_h4(int nt, int ck);
-WaveKernel fwd_kernel_f32_h8(int nt, int ck);
-WaveKernel fwd_kernel_f32_h16(int nt, int ck);
-WaveKernel fwd_kernel_f32_h32(int nt, int ck);
-WaveKernel fwd_kernel_f32_h64(int nt, int ck);
-WaveKernel fwd_kernel_bf16_h32(int nt, int ck);
-WaveKernel fwd_kernel_bf16_h64(int nt, int ck);
+// One translation unit per hidden size (k_wave_fwd_*.hip). one_step: the kernel
+// of the per-diagonal schedule.
+WaveKernel fwd_kernel_f32_h4(int nt, int ck, bool one_step);
+WaveKernel fwd_kernel_f32_h8(int nt, int ck, bool one_step);
+WaveKernel fwd_kernel_f32_h16(int nt, int ck, bool one_step);
+WaveKernel fwd_kernel_f32_h32(int nt, int ck, bool one_step);
+WaveKernel fwd_kernel_f32_h64(int nt, int ck, bool one_step);
+WaveKernel fwd_kernel_bf16_h32(int nt, int ck, bool one_step);
+WaveKernel fwd_kernel_bf16_h64(int nt, int ck, bool one_step);
 WaveKernel fwd_kernel_mem_h16(int nt, int ck);
 WaveKernel fwd_kernel_mem_h32(int nt, int ck);
 

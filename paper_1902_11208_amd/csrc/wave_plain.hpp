@@ -1,6 +1,6 @@
 // A unit of the fp32 wavefronts by plain FMAs over the layer's own operands.
 //
-// An infinite value has no bf16 pieces (split.hpp), so a wavefront kernel that
+// A value beyond the largest bf16 has no pieces (split.hpp), so a wavefront kernel that
 // met one (an input, weight, cell state or gate gradient) runs its unit again
 // here: inf * 0 and inf - inf give NaN, a sum with infinities of one sign keeps
 // it. Every value passes through memory, every thread takes (cell, hidden unit)
@@ -74,6 +74,7 @@ template <int H, bool MEM>
 __device__ __attribute__((noinline)) void plain_fwd_unit(KernArgs<FwdArgs>* args, int unit, int sb, int se) {
     FwdArgs a;
     __builtin_memcpy(&a, (const void*)args, sizeof(a));
+    if (a.now) a = step_args(a);
     const int d = unit & 3;
     const RectD R = reinterpret_cast<const RectD*>(a.rects)[unit >> 2];
     float *const Z = static_cast<float*>(a.z), *const Y = static_cast<float*>(a.y);

@@ -102,6 +102,30 @@ def test_per_diagonal_schedule_gives_the_same_bits(H, dt, C):
     assert torch.equal(y, layer.forward_stepwise(x))
 
 
+@pytest.mark.parametrize("H,dt,C", [(16, "f32", 48), (64, "f32", 20), (64, "bf16", 40)])
+def test_recorded_diagonals_take_the_tensors_of_the_call(H, dt, C):
+    """The launches recorded by one per-diagonal call serve the next one's
+    inputs, input weights and biases, in other buffers."""
+    import gpu_run
+    from paper_1902_11208_amd import api
+    from synth.configs import custom_workload
+
+    hs, ws = [20, 17], [12, 9]
+    print(f"case recorded diagonals H={H} C={C} {dt}", flush=True)
+    units, place, ch, cw, mask = gpu_run.layout(hs, ws, 40)
+    layer = None
+    for seed in (720, 721, 722):
+        wl = custom_workload(seed + H, hs, ws, 40, C, H, dt)
+        wx, u, b = (gpu_run.to_dev(p, dt) for p in wl.params())
+        x = api.pack_data([gpu_run.to_dev(e, dt) for e in wl.examples()], place, ch, cw)
+        if layer is None:
+            layer = api.MDLSTMLayer(wx, u, b, ch, cw, units, mask)
+        layer.wx, layer.b = wx, b  # the same u, workspace and outputs: the same graph
+        y = layer.forward(x).clone()
+        layer.y.fill_(7)
+        assert torch.equal(y, layer.forward_stepwise(x)), seed
+
+
 def test_more_rectangles_than_the_layout_pass_lists():
     """5000 one-row examples: the ids are painted first and read from there;
     every output against the same examples in two smaller calls, bit for bit,

@@ -23,22 +23,11 @@ namespace mdl {
 
 namespace {
 
-// 16x16x32 bf16 MFMA operands: eight consecutive values per slot and step.
-template <typename T>
-struct Ops;
-template <>
-struct Ops<bf16_t> {
-    using Op = bf16x8;
-    static constexpr int PER = 8;
-    static __device__ __forceinline__ Op lds(const bf16_t* p) { return as_bf16x8(*reinterpret_cast<const uint4*>(p)); }
-    static __device__ __forceinline__ floatx4 mma(Op a, Op b, floatx4 c) { return mfma_bf16(a, b, c); }
-};
-
 // A-operand values of one reduction slot from global memory: element stride
 // `es` between consecutive k.
-template <typename T, int NSTEP>
-__device__ __forceinline__ void load_slot(const T* __restrict__ base, int64_t es, bool ok,
-                                          typename Ops<T>::Op (&v)[NSTEP]) {
+template <int NSTEP>
+__device__ __forceinline__ void load_slot(const bf16_t* __restrict__ base, int64_t es, bool ok,
+                                          bf16x8 (&v)[NSTEP]) {
 #pragma unroll
     for (int ks = 0; ks < NSTEP; ++ks) {
         uint32_t w[4];
@@ -74,25 +63,10 @@ constexpr int WIDE_WAVES = 8;  // waves per unit of the wide kernels, sixteen hi
 // workgroup as contiguous 16-byte chunks (a lane's own values would be
 // 8-byte pieces of sixteen canvas rows per store).
 // ---------------------------------------------------------------------------
-// Target of the gate-gradient stores of lanes whose cell is outside the
-// diagonal in the wide-layer backward: every lane stores on every path, so the
-// number of memory operations in flight is the same on all paths and the
-// compiler waits for exactly the loads it needs (a skipped store would make it
-// wait for everything). 1536 bytes per lane (room for a cell's gate gradients
-// of one direction), shared by workgroups eight apart; never read.
-constexpr int SINK_LANE = 96;  // 16-byte slots per lane
-__device__ __attribute__((aligned(256))) uint4 g_wave_sink[8 * 64 * SINK_LANE];
-
-template <typename T>
-__device__ __forceinline__ T* wave_sink() {
-    return reinterpret_cast<T*>(&g_wave_sink[((blockIdx.x & 7) * 64 + (threadIdx.x & 63)) * SINK_LANE]);
-}
-
 template <int H, int NT, typename T>
 __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
-    using O = Ops<T>;
-    using Op = typename O::Op;
-    constexpr int G = 5 * H, KRUN = H / 2, NSTEP = KRUN / O::PER, NTH = 512;
+    using Op = bf16x8;
+    constexpr int G = 5 * H, KRUN = H / 2, NSTEP = KRUN / 8, NTH = 512;
     constexpr int ROWS = NT * 16 + 1;            // row 0: zero row above local row 0
     constexpr int HP = H + 16 / (int)sizeof(T);  // padded LDS row pitches
     constexpr int CP = H + 4;
@@ -141,9 +115,9 @@ __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int row = (n16 & 3) * H + 16 * w + 4 * (n16 >> 2) + k;
-        load_slot<T, NSTEP>(U + (int64_t)row * 2 * H + q * KRUN, 1, true, Aown[k]);
+        load_slot<NSTEP>(U + (int64_t)row * 2 * H + q * KRUN, 1, true, Aown[k]);
     }
-    load_slot<T, NSTEP>(U + (int64_t)(4 * H + 16 * w + n16) * 2 * H + q * KRUN, 1, true, Ag);
+    load_slot<NSTEP>(U + (int64_t)(4 * H + 16 * w + n16) * 2 * H + q * KRUN, 1, true, Ag);
     __builtin_amdgcn_s_waitcnt(0);
 
     const DiagMap M(R, d, a.canvas_w);
@@ -220,10 +194,10 @@ __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
         for (int k = 0; k < 4; ++k) acc[k] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < NSTEP; ++ks) {
-            const Op b = O::lds(brow + ks * O::PER);
-            ag = O::mma(Ag[ks], b, ag);
+            const Op b = as_bf16x8(*reinterpret_cast<const uint4*>(brow + ks * 8));
+            ag = mfma_bf16(Ag[ks], b, ag);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc[k] = O::mma(Aown[k][ks], b, acc[k]);
+            for (int k = 0; k < 4; ++k) acc[k] = mfma_bf16(Aown[k][ks], b, acc[k]);
         }
         const float4 cl = *reinterpret_cast<const float4*>(&cbuf[yy + 1][u0]);
         const float4 ct = *reinterpret_cast<const float4*>(&cbuf[yy][u0]);
@@ -300,9 +274,8 @@ __device__ __forceinline__ void wave_fwd_big(const FwdArgs& a, const int unit) {
 // ---------------------------------------------------------------------------
 template <int H, int NT, typename T>
 __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
-    using O = Ops<T>;
-    using Op = typename O::Op;
-    constexpr int G = 5 * H, KRUNB = G / 4, NSTEPB = KRUNB / O::PER;
+    using Op = bf16x8;
+    constexpr int G = 5 * H, KRUNB = G / 4, NSTEPB = KRUNB / 8;
     constexpr int GP = G + 16 / (int)sizeof(T);  // padded LDS row pitches
     constexpr int CP = H + 4;
     __shared__ __attribute__((aligned(16))) T dabuf[NT * 16][GP];
@@ -331,7 +304,7 @@ __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
     Op A[2][NSTEPB];
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt)
-        load_slot<T, NSTEPB>(U + (int64_t)(q * KRUNB) * 2 * H + tt * H + 16 * w + n16, 2 * H, true, A[tt]);
+        load_slot<NSTEPB>(U + (int64_t)(q * KRUNB) * 2 * H + tt * H + 16 * w + n16, 2 * H, true, A[tt]);
     floatx4 gl[NT], dcl[NT];  // left-successor parts of dh and dc, per tile row
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) gl[nt] = dcl[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -407,7 +380,7 @@ __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
 #pragma unroll
         for (int t = 0; t < 5; ++t) *reinterpret_cast<uint2*>(&dabuf[yy][t * H + u0]) = pack(da[t]);
         {
-            T* const zp = inr ? zb + (int64_t)(M.sx * s + yy * M.ky) * (4 * G) : wave_sink<T>();
+            T* const zp = inr ? zb + (int64_t)(M.sx * s + yy * M.ky) * (4 * G) : reinterpret_cast<T*>(sink_ptr());
 #pragma unroll
             for (int t = 0; t < 5; ++t) *reinterpret_cast<uint2*>(zp + t * H) = pack(da[t]);
         }
@@ -418,9 +391,9 @@ __device__ __forceinline__ void wave_bwd_big(const BwdArgs& a, const int unit) {
         floatx4 al = floatx4{0.f, 0.f, 0.f, 0.f}, at = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < NSTEPB; ++ks) {
-            const Op b = O::lds(brow + ks * O::PER);
-            al = O::mma(A[0][ks], b, al);
-            at = O::mma(A[1][ks], b, at);
+            const Op b = as_bf16x8(*reinterpret_cast<const uint4*>(brow + ks * 8));
+            al = mfma_bf16(A[0][ks], b, al);
+            at = mfma_bf16(A[1][ks], b, at);
         }
         gl[nt] = al;
         *reinterpret_cast<float4*>(&gtop[16 * nt + n16][u0]) = make_float4(at[0], at[1], at[2], at[3]);

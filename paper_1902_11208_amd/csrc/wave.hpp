@@ -129,13 +129,13 @@ struct BwdArgs {
 // same on all paths and the compiler waits for exactly the loads it needs (a
 // skipped store would make it wait for everything). 1536 bytes per lane (room
 // for a cell's gates of one direction), shared by workgroups eight apart;
-// never read.
+// never read. Internal to a translation unit: one whose kernels all stage their
+// rows keeps none.
 constexpr int WAVE_SINK_LANE = 96;  // 16-byte slots per lane
-template <int TAG>
-__device__ __attribute__((aligned(256))) uint4 g_sink[8 * 64 * WAVE_SINK_LANE];
+static __device__ __attribute__((aligned(256))) uint4 g_sink[8 * 64 * WAVE_SINK_LANE];
 
 __device__ __forceinline__ char* sink_ptr() {
-    return reinterpret_cast<char*>(&g_sink<0>[((blockIdx.x & 7) * 64 + (threadIdx.x & 63)) * WAVE_SINK_LANE]);
+    return reinterpret_cast<char*>(&g_sink[((blockIdx.x & 7) * 64 + (threadIdx.x & 63)) * WAVE_SINK_LANE]);
 }
 
 // An LDS array of a kernel, the same for every body of it (K: the kernel's

@@ -190,7 +190,11 @@ mdlstm_status mdlstm_unpack_data(int32_t n, void* const* d_examples, const mdlst
 /* Device workspace needed by mdlstm_forward followed by mdlstm_backward
  * (with the zero-padded copies of a shape between the built ones); 0 when the
  * descriptor is invalid or unsupported, or the canvas or the number of
- * rectangles is out of range (mdlstm_last_error says which). */
+ * rectangles is out of range (mdlstm_last_error says which). The gates, 80H
+ * (fp32) or 40H bytes per canvas cell, and the cell states, 16H, are most of it.
+ * fp32 layers with up to 64 input channels and H <= 32 also keep the inputs as
+ * the wavefront reads them: 192 bytes per cell and 32 channels (rounded up), and
+ * every fp32 layer 16 more per cell. */
 size_t mdlstm_workspace_bytes(const mdlstm_layer_desc* desc, int32_t canvas_h, int32_t canvas_w,
                               int32_t n_rects);
 
@@ -238,9 +242,9 @@ mdlstm_status mdlstm_forward(const mdlstm_layer_desc* desc, int32_t canvas_h, in
  * persistent launch: the alternative schedule of Section IV-A, kept for
  * comparison. Same arguments, contract and results (bit for bit) as
  * mdlstm_forward. The launches are recorded once into a HIP graph, which is
- * replayed while the arguments (pointers, sizes, rectangles) stay the same; the
- * graph of the last call is kept per calling thread until the next call with
- * different arguments.
+ * replayed while the sizes, the rectangles and the pointers of mask, U, y and
+ * workspace stay the same (x, Wx and b may change); the graph of the last call
+ * is kept per calling thread until the next call with other arguments.
  */
 mdlstm_status mdlstm_forward_stepwise(const mdlstm_layer_desc* desc, int32_t canvas_h, int32_t canvas_w,
                                       const void* d_x, const uint8_t* d_mask,

@@ -21,9 +21,9 @@
 //
 // Measured before (scalar operand exchange, fp32 MFMA, partial sums of the
 // products through LDS; bf16 H 64 with tall rectangles unstaged) and after:
-//   fp32 H 32, 64 lines of 32 rows    1590 -> 1560 us (4.5 TB/s of traffic)
+//   fp32 H 32, 64 lines of 32 rows    1670 -> 1550 us (4.84 GB, 3.1 TB/s)
 //   fp32 H 32, 32 images of 16 rows    163 ->  134 us
-//   fp32 H 64, 64 images of 8 rows     292 ->  205 us
+//   fp32 H 64, 64 images of 8 rows     292 ->  198 us
 //   bf16 H 64, 24 lines of 20-60 rows 11.9 ->  2.9 ms
 #pragma once
 

@@ -31,11 +31,11 @@
 // two waves of a SIMD overlap), memory traffic where they fill the chip.
 // Measured, projection included, before (fp32 MFMA, candidate partials through
 // LDS, two barriers, separate projection) and after:
-//   fp32 H 32, one 31 x 777 line      1753 -> 1270 us (1.6 us a diagonal)
-//   fp32 H 32, 64 lines of 32 rows    2270 -> 1350 us (3.9 GB moved)
-//   fp32 H 16, 32 images of 32 rows    601 ->  400 us
-//   fp32 H 16, 256 words               305 ->  240 us
-//   bf16 H 64, 24 lines of 20-60 rows 14.2 ->  2.5 ms
+//   fp32 H 32, one 31 x 777 line      1753 -> 1172 us (1.45 us a diagonal)
+//   fp32 H 32, 64 lines of 32 rows    2270 -> 1175 us (3.63 GB, 3.1 TB/s)
+//   fp32 H 16, 32 images of 32 rows    601 ->  388 us
+//   fp32 H 16, 256 words               305 ->  174 us
+//   bf16 H 64, 24 lines of 20-60 rows 14.2 ->  2.7 ms
 #pragma once
 
 #include <type_traits>
@@ -661,7 +661,23 @@ __attribute__((amdgpu_waves_per_eu(FwdK<H, NT, T, CK, WQ, NG, MEM>::WPE))) k_fwd
 
 // Hidden sizes whose forward wavefront takes over the projection: where Wx's
 // operands fit in registers beside U's. fp32 H = 64 has 240 registers of U in
-// each of four waves already (with Wx it spills over a hundred).
+// each of four waves already (with Wx it spills over a hundred). With 33-64
+// channels some of the others spill too; forward with the projection inside
+// against apart, us, 64 channels, 16 / 128 images of 16 t rows:
+//   fp32 H 4,  t = 1    256 /  238 against  242 /  258
+//              t = 4    470 /  857          511 /  829
+//   fp32 H 16, t = 1    237 /  216          325 /  450
+//              t = 4    655 /  986          863 / 1586
+//   fp32 H 32, t = 1    554 /  429          491 /  758
+//              t = 2    827 /  929          783 / 1405
+//              t = 3   1338 / 1420         1372 / 2160
+//              t = 4   2784 / 3706         2117 / 3871
+//   memory H 16, t = 3 1118 / 1357          739 / 1226
+//   memory H 32, t = 1  490 /  510          630 /  882
+//                t = 4 2442 / 2971         2774 / 4317
+// (fp32 H 8, the other heights of the memory layers and bf16: inside is faster.)
+// Full batches gain from it all but everywhere; a few images of H 32 or of
+// memory H 16 with 33-48 rows lose.
 template <typename T>
 constexpr bool fwd_fusable(int hidden) {
     return hidden <= (std::is_same<T, float>::value ? 32 : 64);

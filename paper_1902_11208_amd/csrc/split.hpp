@@ -5,9 +5,9 @@
 // v = hi + mid + lo exactly (down to about 1e-33, where lo falls below bf16's
 // range). Of the nine products of two such sums the six largest are kept (hi
 // hi, hi mid, mid hi, hi lo, lo hi, mid mid); the dropped ones reach 2^-25 of
-// the product each, 2^-24 together: an ulp at most. They accumulate in fp32. One 16x16x32 bf16 MFMA takes 16 cycles, so 32
-// reduction values cost 96 cycles in this form against 256 as eight 16x16x4
-// fp32 MFMAs.
+// the product each, 2^-24 together: an ulp at most. They accumulate in fp32.
+// One 16x16x32 bf16 MFMA takes 16 cycles, so 32 reduction values cost 96 cycles
+// in this form against 256 as eight 16x16x4 fp32 MFMAs.
 //
 // A value beyond the largest bf16 has no such form, an infinite one least of all
 // (its products are NaN whatever the sum is): a unit that met one is run again
